@@ -112,9 +112,10 @@ struct Plan {
   int64_t n, chunk;
   int nb, n_solvers, n_helpers;
   int rchunks_all, rchunks_dom;   // routing: source-domain chunks (divisors of M)
+  int s1_waves;   // stage-1 ranks: solver waves per domain (0: fewer waves than domains)
   uint32_t spin_limit;   // polls of a bounded wait (0: every such wait gives up at once)
   uint32_t iter_limit;   // committed refinement moves per domain before ITER
-  FastDiv fE, fG, fGP, fP, fI, fPN, fCap, fN, fMI;
+  FastDiv fE, fG, fGP, fP, fI, fPN, fCap, fN, fMI, fS1;
   const int32_t *gl, *topk;
   int32_t *slots_out, *dest_out, *send_out, *status_out;
   int32_t *recv_out;   // receive counts [R], or null
@@ -1648,12 +1649,13 @@ __device__ void stage1_domain_wave(const Plan &p, int d, const int *om, uint64_t
 // after every candidate) from the domain's LDS counter ccnt[d] (the slots'
 // order is arbitrary).  Each candidate's rank among its domain's candidates
 // by key (D descending, e ascending; keys are distinct) is then counted in
-// parts of 16 keys: the workgroup's threads are split into one block per
-// domain (whole waves; one domain after another when there are more domains
-// than waves), a block's items being (candidate c, part h) with Hp parts
-// per candidate (ceil(nc / 16) rounded up to a power of two).  rk[d E + c]
-// = the rank of the domain's candidate in slot c.  The ranks below cap1
-// name the domain's stage-1 replicas.  rk: M E words.
+// parts of 16 keys: the waves are split among the domains (one domain after
+// another when there are more domains than waves), and a wave takes 64
+// candidates, one per lane, against one part, whose keys every lane reads
+// alike (broadcast reads; with lanes on different parts the reads, 128 bytes
+// apart, met on one LDS bank: a plan of 1.6 M ids with 192 candidates in each
+// of 4 domains took 111.6 us, 52.2 with broadcast reads).  rk[d E + c] = the rank of the domain's candidate in slot c.
+// The ranks below cap1 name the domain's stage-1 replicas.  rk: M E words.
 __device__ __forceinline__ void stage1_ranks(const Plan &p, const int *om, uint64_t *ck, int *ccnt, int *rk) {
   const int tid = threadIdx.x, nt = blockDim.x, E = p.E, G = p.G, M = p.M, E16 = (E + 15) & ~15;
   // item idx = d E + e, walked with (d, e) kept as the index advances
@@ -1677,28 +1679,28 @@ __device__ __forceinline__ void stage1_ranks(const Plan &p, const int *om, uint6
   }
   lds_barrier();
   STAMP(p, 24);
-  const int nw = nt >> 6;
-  const int wpd = M <= nw ? nw / M : 0;
-  const int d0 = wpd ? (tid >> 6) / wpd : 0;
-  const int tpd = wpd ? wpd * 64 : nt;
-  const int lt = wpd ? tid - d0 * tpd : tid;
+  const int nw = nt >> 6, wave = uniform_i32(tid >> 6), lane = tid & 63;
+  const int wpd = p.s1_waves;
+  const int d0 = wpd ? (int)fdiv((uint32_t)wave, p.fS1) : 0;
+  const int step = wpd ? wpd : nw, first = wpd ? wave - d0 * wpd : wave;
   for (d = d0; d < (wpd ? imin(d0 + 1, M) : M); ++d) {
     const int nc = uniform_i32(ccnt[d]);   // (d is the same in the whole wave)
-    const int parts = (nc + 15) >> 4;
-    const int lh = parts <= 1 ? 0 : 32 - __clz(parts - 1);
+    const int blocks = (nc + 63) >> 6, parts = (nc + 15) >> 4;
+    const int lb = blocks <= 1 ? 0 : 32 - __clz(blocks - 1);
     const uint64_t *kd = ck + d * E16;
-    for (int v = lt; v < (nc << lh); v += tpd) {
-      const int c = v >> lh, h = v & ((1 << lh) - 1);
-      if (16 * h >= nc) continue;
-      const uint64_t kc = kd[c];
-      const uint64_t *kp = kd + 16 * h;
+    for (int u = first; u < (parts << lb); u += step) {
+      const int blk = u & ((1 << lb) - 1), part = u >> lb;
+      if (blk >= blocks) continue;
+      const int c = blk * 64 + lane;
+      const uint64_t kc = kd[imin(c, nc - 1)];
+      const uint64_t *kp = kd + 16 * part;
       uint64_t k[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) k[i] = kp[i];
       int below = 0;
 #pragma unroll
       for (int i = 0; i < 16; ++i) below += k[i] < kc ? 1 : 0;
-      if (below) atomicAdd(&rk[d * E + c], below);
+      if (c < nc && below) atomicAdd(&rk[d * E + c], below);
     }
   }
   lds_barrier();
@@ -3819,6 +3821,8 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
   };
   q.rchunks_all = chunks_for((int64_t)q.M * q.I);
   q.rchunks_dom = chunks_for(q.I);
+  q.s1_waves = (s.st / 64) / q.M;
+  q.fS1 = make_fastdiv((uint32_t)imax(q.s1_waves, 1));
 
   size_t off = 0;
   auto take = [&](size_t bytes) {

@@ -3,10 +3,8 @@
 //
 // Three kernels per plan, enqueued back to back on one stream:
 //
-//   hist     one block per contiguous chunk of the flattened [T, k] ids.
-//            LDS-privatised histogram; within a wave the lanes holding the
-//            same expert are found with ballots over the id bits, and only
-//            the lowest such lane adds the group's popcount.  Writes the
+//   hist     one block per contiguous chunk of the flattened [T, k] ids, one
+//            LDS row of counts per wave, one LDS atomic per id.  Writes the
 //            block's partial histogram (this rank's row of the routing
 //            matrix Omega, Eq. 3, Section 3.1).
 //   solve    the placement solver, in one of two shapes:
@@ -24,10 +22,10 @@
 //            reductions and no barrier per iteration.  Extra workgroups of
 //            the same launch compute each histogram block's exclusive
 //            per-expert offsets for the reroute, off the solver's path.
-//   reroute  same chunking as hist.  Stable rank of every assignment among
-//            the earlier assignments of its expert (ballot peer masks inside
-//            a wave, per-wave counts scanned across waves, block offsets),
-//            then the instance whose prefix range holds it.
+//   reroute  same chunking as hist.  An expert whose occurrences in the chunk
+//            all belong to one instance is a table lookup; only an expert
+//            whose instance changes inside the chunk has its ids ranked
+//            (ballots inside a wave, per-wave counts scanned across waves).
 //
 // All arithmetic is integer; no atomic decides an order or a placement
 // (LDS/global integer atomics only accumulate commutative counts, masks and
@@ -89,7 +87,9 @@ constexpr int kLdsLimit = 160 * 1024;   // LDS per workgroup on gfx950
 constexpr int kMaxSolveGroups = 128;    // co-resident by a wide margin (256 CUs)
 constexpr int kMinBlocks = 2048;        // histogram/reroute blocks to aim for, at least
 constexpr int kMaxBlocks = 8192;        // and at most
-constexpr int kOffsetExperts = 64;      // experts per offset workgroup
+constexpr int64_t kOneTileIds = 1 << 20;   // above: blocks of 1024 threads
+constexpr int kLongBlocks = 512;        // and at most this many of them (two per CU)
+constexpr int kOffsetExperts = 32;      // experts per offset workgroup
 // chunk workgroups the single-launch plan aims for: each chunk reads the
 // instance list and up to nb / 2 rows of the other chunks' counts, so 32
 // rather than 64 cut the DeepSeek-V3-like plan's HBM traffic from 1.16 to
@@ -466,98 +466,23 @@ __device__ void hist_from_partials(const Plan &p, int *hs, int *scratch) {
   lds_barrier();
 }
 
-// Load phase of the single-workgroup solver when the sizes are small
-// (E % 4 == 0, Omega at most 4 int4 and the partials at most 8 int4 per
-// thread): every global load (the histogram blocks' partials, Omega and the
-// blocks' error flags) is issued before any is used, branch-free with
-// clamped indices.  Fills om (Omega, row self replaced by the histogram) and
-// hs, and accumulates status bits and the total load in misc.
-__device__ inline bool load_fast_ok(const Plan &p) {
-  const int nt = blockDim.x, E4 = p.E >> 2;
-  if ((p.E & 3) || E4 > nt || ((reinterpret_cast<uintptr_t>(p.gl)) & 15)) return false;
-  const int G4 = nt / E4;
-  return (p.R * p.E) / 4 <= 4 * nt && (p.nb + G4 - 1) / G4 <= 8 && p.nb <= nt;
-}
-
-__device__ void load_fast(const Plan &p, int *om, int *hs, int *scratch, int *misc) {
-  const int tid = threadIdx.x, nt = blockDim.x, E = p.E, R = p.R, nb = p.nb;
-  const int E4 = E >> 2, G4 = nt / E4;
-  const int n4 = (R * E) >> 2;
-  const int g = tid / E4, e4 = tid - g * E4;
-  const int4 *part4 = reinterpret_cast<const int4 *>(p.partials);
-  const int4 *gl4 = reinterpret_cast<const int4 *>(p.gl);
-  const int4 z = make_int4(0, 0, 0, 0);
-  int4 pv[8], ov[4];
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const int b = g + u * G4;
-    pv[u] = part4[(int64_t)imin(b, nb - 1) * E4 + e4];
-    if (b >= nb || g >= G4) pv[u] = z;
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u) ov[u] = gl4[imin(tid + u * nt, n4 - 1)];
-  const int be = p.blk_err[imin(tid, nb - 1)];
-  // Omega to LDS; negative entries and the total of positive loads
-  int4 *om4 = reinterpret_cast<int4 *>(om);
-  bool neg = false;
-  uint64_t tot = 0;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int i = tid + u * nt;
-    if (i < n4) {
-      om4[i] = ov[u];
-      neg |= (ov[u].x | ov[u].y | ov[u].z | ov[u].w) < 0;
-      tot += (uint64_t)(ov[u].x > 0 ? ov[u].x : 0) + (uint64_t)(ov[u].y > 0 ? ov[u].y : 0) +
-             (uint64_t)(ov[u].z > 0 ? ov[u].z : 0) + (uint64_t)(ov[u].w > 0 ? ov[u].w : 0);
-    }
-  }
-  int4 s = z;
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    s.x += pv[u].x;
-    s.y += pv[u].y;
-    s.z += pv[u].z;
-    s.w += pv[u].w;
-  }
-  if (g < G4) reinterpret_cast<int4 *>(scratch)[g * E4 + e4] = s;
-  lds_barrier();
-  // histogram; row self of Omega := histogram
-  bool diff = false;
-  for (int e = tid; e < E; e += nt) {
-    int h = 0;
-    for (int gg = 0; gg < G4; ++gg) h += scratch[gg * E + e];
-    hs[e] = h;
-    const int gself = om[p.self * E + e];
-    diff |= gself != h;
-    if (gself > 0) tot -= (uint64_t)gself;
-    if (h > 0) tot += (uint64_t)h;
-    om[p.self * E + e] = h;
-  }
-  tot = wave_sum_u64(tot);
-  const uint64_t any_neg = __ballot(neg), any_diff = __ballot(diff), any_bad = __ballot(tid < nb && be != 0);
-  if (lane_id() == 0) {
-    const uint32_t w = (any_neg ? TOPOEP_ST_NEG_LOAD : 0u) | (any_diff ? TOPOEP_ST_SELF_DIFF : 0u) |
-                       (any_bad ? TOPOEP_ST_BAD_ID : 0u);
-    if (w) atomicOr(reinterpret_cast<unsigned *>(&misc[0]), w);
-    if (tot) atomicAdd(reinterpret_cast<unsigned long long *>(misc + 8), (unsigned long long)tot);
-  }
-  lds_barrier();
-}
-
 // Exclusive per-expert offset of every histogram block, for the reroute
 // (offset workgroup h of n_helpers handles kOffsetExperts experts at a time),
 // and each expert's count over all blocks (htot, the histogram of
 // local_topk), announced by one increment of the helpers' counter as soon
 // as the totals are written: the offsets follow in a second pass (only the
-// next launch reads them).  scratch: nw x 64 words per expert group of this
-// workgroup (one group when n_helpers covers E, as the host sets it).
-__device__ void block_offsets(const Plan &p, int h, int *scratch, bool announce) {
-  const int tid = threadIdx.x, nt = blockDim.x, nw = nt >> 6, E = p.E, nb = p.nb;
-  const int el = tid & 63, g = tid >> 6;
-  const int per = (nb + nw - 1) / nw;
+// next launch reads them).  A group of kOffsetExperts lanes sums one share
+// of the blocks, eight loads in flight.  scratch: one word per thread for
+// each expert group of this workgroup (one group when n_helpers covers E, as
+// the host sets it).
+__device__ void block_offsets(const Plan &p, int h, int *scratch) {
+  const int tid = threadIdx.x, nt = blockDim.x, E = p.E, nb = p.nb;
+  const int ng = nt / kOffsetExperts;
+  const int el = tid % kOffsetExperts, g = tid / kOffsetExperts;
+  const int per = (nb + ng - 1) / ng;
   const int b0 = g * per, b1 = imin(nb, b0 + per);
   const int gstride = p.n_helpers * kOffsetExperts;
-  // pass 1: each wave's sum over its blocks, per expert of every group
+  // pass 1: each group's sum over its blocks, per expert
   int grp = 0;
   for (int e0 = h * kOffsetExperts; e0 < E; e0 += gstride, ++grp) {
     const int e = e0 + el;
@@ -571,32 +496,30 @@ __device__ void block_offsets(const Plan &p, int h, int *scratch, bool announce)
         for (int u = 0; u < 8; ++u) run += v[u];
       }
     }
-    scratch[(grp * nw + g) * 64 + el] = run;
+    scratch[grp * nt + tid] = run;
   }
   __syncthreads();
   // the totals (the expert's count over every block), then the announcement
   grp = 0;
   for (int e0 = h * kOffsetExperts; e0 < E; e0 += gstride, ++grp) {
     const int e = e0 + el;
-    if (g == nw - 1 && e < E) {
+    if (g == ng - 1 && e < E) {
       int tot = 0;
-      for (int g2 = 0; g2 < nw; ++g2) tot += scratch[(grp * nw + g2) * 64 + el];
+#pragma unroll 8
+      for (int g2 = 0; g2 < ng; ++g2) tot += scratch[grp * nt + g2 * kOffsetExperts + el];
       p.htot[e] = tot;
     }
   }
-  if (announce) {
-    // publish: every total written before the count of finished helpers
-    // (only the per-domain solver reads it)
-    drain_then_barrier();
-    if (tid == 0) __hip_atomic_fetch_add(&p.ctrl[kCtrlHelpers], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  // publish: every total written before the count of finished helpers
+  drain_then_barrier();
+  if (tid == 0) __hip_atomic_fetch_add(&p.ctrl[kCtrlHelpers], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
   // pass 2: the blocks' exclusive offsets
   grp = 0;
   for (int e0 = h * kOffsetExperts; e0 < E; e0 += gstride, ++grp) {
     const int e = e0 + el;
     if (e >= E) continue;
     int base = 0;
-    for (int g2 = 0; g2 < g; ++g2) base += scratch[(grp * nw + g2) * 64 + el];
+    for (int g2 = 0; g2 < g; ++g2) base += scratch[grp * nt + g2 * kOffsetExperts + el];
     for (int b = b0; b < b1; b += 8) {
       int v[8];
 #pragma unroll
@@ -610,8 +533,8 @@ __device__ void block_offsets(const Plan &p, int h, int *scratch, bool announce)
   }
 }
 
-// The histogram of local_topk (row self of Omega) for the per-domain
-// solver: the offset helpers' totals once all of them have published, else
+// The histogram of local_topk (row self of Omega) for the solvers of the
+// three-kernel plan: the offset helpers' totals once all of them have published, else
 // the sum of the blocks' counts made here.  The helpers normally finish in
 // a few microseconds beside the solver workgroups; the wait is bounded by
 // kHelperSpin polls (~0.2 ms), not by the hang guard, so a dispatch whose
@@ -687,37 +610,67 @@ __device__ bool grid_barrier(uint32_t *count, uint32_t groups, uint32_t spin_lim
 
 // ---------------------------------------------------------------- histogram
 
-template <int IPT>
-__global__ __launch_bounds__(1024) void hist_kernel(Plan p) {
+typedef int v4i __attribute__((ext_vector_type(4)));   // one 16-byte word
+
+// V 16-byte loads of four consecutive ids per lane from base on (256 V ids a
+// wave; base a multiple of 64 ids), -1 from `end` on; vec: the array is
+// 16-byte aligned.  The ids are read once per kernel: non-temporal loads.
+template <int V>
+__device__ inline void load_ids(const int32_t *ids, int64_t base, int64_t end, bool vec, int (&v)[4 * V]) {
+#pragma unroll
+  for (int j = 0; j < V; ++j) {
+    const int64_t idx = base + (int64_t)(j * 64 + lane_id()) * 4;
+    if (vec && idx + 4 <= end) {
+      const v4i x = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(ids + idx));
+      v[4 * j] = x.x;
+      v[4 * j + 1] = x.y;
+      v[4 * j + 2] = x.z;
+      v[4 * j + 3] = x.w;
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[4 * j + c] = idx + c < end ? ids[idx + c] : -1;
+    }
+  }
+}
+
+// One contiguous chunk per block, in tiles of 256 V ids per wave; each wave
+// counts into its own LDS row, one atomic per id, the next tile's loads in
+// flight meanwhile.
+template <int V>
+__global__ __launch_bounds__(1024, 8) void hist_kernel(Plan p) {
   extern __shared__ int smem_h[];
-  int *h = smem_h;
-  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, nt = blockDim.x, nw = nt >> 6, lane = tid & 63, wave = tid >> 6, E = p.E;
   const int b = blockIdx.x;
-  for (int e = tid; e < p.E; e += nt) h[e] = 0;
-  __syncthreads();
+  int *h = smem_h + wave * E;
   const int64_t lo = (int64_t)b * p.chunk;
   const int64_t hi = lo + p.chunk < p.n ? lo + p.chunk : p.n;
-  const int64_t tile = (int64_t)nt * IPT;
+  const bool vec = (reinterpret_cast<uintptr_t>(p.topk) & 15) == 0;
+  const int64_t tile = (int64_t)nw * 256 * V, wofs = (int64_t)wave * 256 * V;
+  int nx[4 * V];
+  load_ids<V>(p.topk, lo + wofs, hi, vec, nx);
+  for (int e = lane; e < E; e += 64) h[e] = 0;
+  wave_sync();
   int bad = 0;
-  for (int64_t base = lo; base < hi; base += tile) {
-    const int64_t wbase = base + (int64_t)wave * 64 * IPT + lane;
-    int ev[IPT];
+  for (int64_t base = lo + wofs; base < hi; base += tile) {
+    int ev[4 * V];
 #pragma unroll
-    for (int i = 0; i < IPT; ++i) {
-      const int64_t idx = wbase + i * 64;
-      ev[i] = idx < hi ? p.topk[idx] : -1;
-    }
+    for (int i = 0; i < 4 * V; ++i) ev[i] = nx[i];
+    if (base + tile < hi) load_ids<V>(p.topk, base + tile, hi, vec, nx);
+    // ids of the wave's piece that exist
+    const int lim = (int)(hi - base < 256 * V ? hi - base : 256 * V);
 #pragma unroll
-    for (int i = 0; i < IPT; ++i) {
-      const int64_t idx = wbase + i * 64;
-      const bool inr = idx < hi;
-      const bool valid = inr && (unsigned)ev[i] < (unsigned)p.E;
-      bad |= (inr && !valid) ? 1 : 0;
+    for (int i = 0; i < 4 * V; ++i) {
+      const bool valid = (unsigned)ev[i] < (unsigned)E;   // (-1 past the end)
+      bad |= !valid && ((i >> 2) * 64 + lane) * 4 + (i & 3) < lim ? 1 : 0;
       if (valid) atomicAdd(&h[ev[i]], 1);
     }
   }
   bad = __syncthreads_or(bad);
-  for (int e = tid; e < p.E; e += nt) p.partials[(int64_t)b * p.E + e] = h[e];
+  for (int e = tid; e < E; e += nt) {
+    int sum = 0;
+    for (int w = 0; w < nw; ++w) sum += smem_h[w * E + e];
+    p.partials[(int64_t)b * E + e] = sum;
+  }
   if (tid == 0) p.blk_err[b] = bad;
 }
 
@@ -1885,7 +1838,7 @@ __global__ __launch_bounds__(NT) void solve_kernel(Plan p0) {
   extern __shared__ int64_t smem_s[];
   int *sm = reinterpret_cast<int *>(smem_s);
   if ((int)blockIdx.x >= p0.n_solvers) {
-    block_offsets(p0, blockIdx.x - p0.n_solvers, sm, true);
+    block_offsets(p0, blockIdx.x - p0.n_solvers, sm);
     return;
   }
   const Plan p = solver_plan(p0);
@@ -2684,345 +2637,6 @@ __device__ __forceinline__ void solver_send_offsets(const Plan &p, const int *se
   if (lane == 63) p.offs_out[R] = run;
 }
 
-// The same steps with every domain's state in the LDS of one CU; each
-// domain's refinement runs on its own wave.  Used when Omega and all q
-// columns fit in LDS.  Workgroups beyond the first compute the histogram
-// blocks' offsets for the reroute.
-__global__ __launch_bounds__(1024) void solve_single_kernel(Plan p0) {
-  extern __shared__ int64_t smem_1[];
-  int *sm = reinterpret_cast<int *>(smem_1);
-  if (blockIdx.x > 0) {
-    block_offsets(p0, blockIdx.x - 1, sm, false);
-    return;
-  }
-  const Plan p = solver_plan(p0);
-  const SingleState t = single_state(p, sm);
-  const int tid = threadIdx.x, nt = blockDim.x, E = p.E, R = p.R;
-  single_init(p, t);
-  // ---- Omega to LDS; histogram of local_topk from the blocks' partials
-  lds_barrier();
-  if (load_fast_ok(p)) {
-    load_fast(p, t.om, t.hs, t.qcol, t.misc);
-  } else {
-    copy_to_lds(t.om, p.gl, R * E);
-    hist_from_partials(p, t.hs, t.qcol);
-    for (int b = tid; b < p.nb; b += nt)
-      if (p.blk_err[b]) atomicOr(reinterpret_cast<unsigned *>(&t.misc[0]), TOPOEP_ST_BAD_ID);
-    scan_rows(p, 0, R, t.om, t.hs, t.misc);
-    lds_barrier();
-    for (int e = tid; e < E; e += nt) t.om[p.self * E + e] = t.hs[e];
-  }
-  uint32_t gst = (uint32_t)t.misc[0];
-  if (out_of_range(p, *reinterpret_cast<unsigned long long *>(t.misc + 8))) gst |= TOPOEP_ST_RANGE;
-  single_plan(p, t, gst, false);
-  if (p.recv_out && !(gst & kNoPlan)) single_recv_counts(p, t);
-}
-
-// ---------------------------------------------------------------- send-buffer slots
-//
-// The send buffer groups the assignments by destination (ranks ascending,
-// row-major order inside one destination).  An assignment's slot is
-// offs[d] + (assignments to d before its tile) + (those of earlier waves of
-// the tile) + (its rank among its wave's earlier assignments to d).  The
-// count before a tile follows from the per-expert counts before it, with no
-// pass over earlier ids: expert e's occurrences are dealt to its instances
-// in occurrence order, instance j taking [end(j-1), end(j)), so
-// clamp(run[e] - end(j-1), 0, end(j) - end(j-1)) of them went to j's rank.
-
-// offs[0..R) holds the send counts: it becomes their exclusive prefix with
-// the total at offs[R] (tmp: blockDim/64 + 1 words); `first` writes it out.
-__device__ void slot_offsets(const Plan &p, int *offs, int *tmp, bool first) {
-  lds_barrier();
-  offs[p.R] = block_excl_scan(offs, p.R, tmp);
-  if (first && p.offs_out)
-    for (int r = threadIdx.x; r <= p.R; r += blockDim.x) p.offs_out[r] = offs[r];
-}
-
-// excl[r] = assignments to rank r before the tile (run[e]: occurrences of e
-// before it; ptr/er/eend: this rank's instance list).  Ends with a barrier.
-__device__ void slot_before(const Plan &p, const int *run, const int *ptr, const int2 *ent, int *excl) {
-  const int tid = threadIdx.x, nt = blockDim.x;
-  for (int r = tid; r < p.R; r += nt) excl[r] = 0;
-  lds_barrier();
-  for (int e = tid; e < p.E; e += nt) {
-    const int re = run[e], j1 = ptr[e + 1];
-    int start = 0;
-    for (int j = ptr[e]; j < j1; ++j) {
-      const int2 en = ent[j];   // (cumulative share, rank)
-      const int c = imin(imax(re - start, 0), en.x - start);
-      if (c > 0 && (unsigned)en.y < (unsigned)p.R) atomicAdd(&excl[en.y], c);
-      start = en.x;
-    }
-  }
-  lds_barrier();
-}
-
-// Per-wave counts to offsets, one column per key: wc[(w * ws + k) * S] (w <
-// nw <= 16 waves, k < n keys, ws > n odd so a column's words sit in distinct
-// banks; S: words per element) becomes base[k] + the counts of waves
-// 0..w-1, and base[k] grows by the column's total (base may be null:
-// offsets from 0).  Beyond four waves a group of g lanes (g = nw rounded up
-// to a power of two) per key scans the column in registers instead of
-// walking it with nw dependent LDS round trips.
-template <int S = 1>
-__device__ inline void scan_wave_columns(int *wc, int ws, int n, int nw, int *base) {
-  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
-  if (nw <= 4) {
-    // short columns: one thread walks each
-    for (int k = tid; k < n; k += nt) {
-      int run = base ? base[k] : 0;
-      for (int w = 0; w < nw; ++w) {
-        const int t = wc[(w * ws + k) * S];
-        wc[(w * ws + k) * S] = run;
-        run += t;
-      }
-      if (base) base[k] = run;
-    }
-    return;
-  }
-  const int lg = nw <= 1 ? 0 : 32 - __clz(nw - 1);   // log2 of the group size
-  const int g = 1 << lg, w = lane & (g - 1);
-  for (int k = tid >> lg; k < n; k += nt >> lg) {
-    const int v = w < nw ? wc[(w * ws + k) * S] : 0;
-    int x = v;
-    // inclusive scan inside the group (row shifts; a group never crosses a row)
-    int y;
-    y = (int)dpp_mov<0x111>((uint32_t)x); x += w >= 1 ? y : 0;
-    y = (int)dpp_mov<0x112>((uint32_t)x); x += w >= 2 ? y : 0;
-    y = (int)dpp_mov<0x114>((uint32_t)x); x += w >= 4 ? y : 0;
-    y = (int)dpp_mov<0x118>((uint32_t)x); x += w >= 8 ? y : 0;
-    const int tot = __shfl(x, lane | (g - 1));
-    const int b0 = base ? base[k] : 0;
-    if (w < nw) wc[(w * ws + k) * S] = b0 + x - v;
-    if (base && w == 0) base[k] = b0 + tot;
-  }
-}
-
-// Slots of one tile (destinations dv in registers; index order: wave, then
-// i, then lane); wcd: blockDim/64 * (R | 1) words of scratch.
-template <int IPT>
-__device__ void slot_write(const Plan &p, const int (&dv)[IPT], int64_t wbase, int64_t hi, const int *offs,
-                           const int *excl, int *wcd) {
-  const int nt = blockDim.x, nw = nt >> 6, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, R = p.R;
-  const int ws = R | 1;
-  int *mw = wcd + wave * ws;
-  for (int r = lane; r < R; r += 64) mw[r] = 0;
-  wave_sync();
-  int lr[IPT];
-#pragma unroll
-  for (int i = 0; i < IPT; ++i) {
-    // (dv is -1 past the end)
-    lr[i] = wave_rank(dv[i], (unsigned)dv[i] < (unsigned)R, p.rbits, mw);
-  }
-  lds_barrier();
-  scan_wave_columns(wcd, ws, R, nw, nullptr);
-  lds_barrier();
-#pragma unroll
-  for (int i = 0; i < IPT; ++i) {
-    const int64_t idx = wbase + i * 64;
-    if (idx < hi) {
-      const int d = dv[i];
-      p.slot_out[idx] = (unsigned)d < (unsigned)R ? offs[d] + excl[d] + mw[d] + lr[i] : -1;
-    }
-  }
-}
-
-// ---------------------------------------------------------------- reroute
-
-template <int IPT>
-__global__ __launch_bounds__(1024) void reroute_kernel(Plan p) {
-  extern __shared__ int smem_r[];
-  const int nt = blockDim.x, nw = nt >> 6;
-  const int E = p.E, ws = E | 1;
-  int2 *ent = reinterpret_cast<int2 *>(smem_r);   // nent_cap + 1: (cumulative share, rank) per entry
-  int2 *cur = ent + p.nent_cap + 1;  // E: (entry holding the next occurrence, end of e's entries)
-  int2 *wc = cur + E;                // nw * ws: per wave and expert the count, then (offset, entry)
-  int *run = reinterpret_cast<int *>(wc + nw * ws);   // E: running offset per expert
-  int *ptr = run + E;                // E + 1
-  int *wcd = ptr + E + 1;            // nw * (R | 1): send-buffer slots: per-wave counts
-  int *excl = wcd + nw * (p.R | 1);  // R: assignments per rank before the tile
-  int *so = excl + p.R;              // R + 1 + nw + 1: send offsets, scan scratch
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int b = blockIdx.x;
-  const int64_t lo = (int64_t)b * p.chunk;
-  const int64_t hi = lo + p.chunk < p.n ? lo + p.chunk : p.n;
-  const uint32_t fin = p.ctrl[kCtrlFinal];
-  if (fin & (kNoPlan | TOPOEP_ST_SYNC)) {
-    for (int64_t i = lo + tid; i < hi; i += nt) p.dest_out[i] = -1;
-    if (p.slot_out)
-      for (int64_t i = lo + tid; i < hi; i += nt) p.slot_out[i] = -1;
-    if (b == 0 && p.offs_out)
-      for (int r = tid; r <= p.R; r += nt) p.offs_out[r] = 0;
-    return;
-  }
-  // the first tile's ids are on their way while the block reads its offsets
-  // and the instance list
-  const int64_t tile = (int64_t)nt * IPT;
-  int evn[IPT];
-  auto load_tile = [&](int64_t base) {
-    const int64_t wbase = base + (int64_t)wave * 64 * IPT + lane;
-#pragma unroll
-    for (int i = 0; i < IPT; ++i) {
-      const int64_t idx = wbase + i * 64;
-      evn[i] = idx < hi ? p.topk[idx] : -1;
-    }
-  };
-  load_tile(lo);
-  if (p.offs_out) {
-    for (int r = tid; r < p.R; r += nt) so[r] = p.send_out[r];
-    slot_offsets(p, so, so + p.R + 1, b == 0);
-  }
-  for (int e = tid; e < E; e += nt) run[e] = p.offsets[(int64_t)b * E + e];
-  for (int e = tid; e <= E; e += nt) {
-    const int v = p.csr_ptr[e];
-    ptr[e] = v < 0 ? 0 : (v > p.nent_cap ? p.nent_cap : v);
-  }
-  __syncthreads();
-  const int nent = ptr[E];
-  for (int j = tid; j < nent; j += nt) ent[j] = make_int2(p.csr_end[j], p.csr_r[j]);
-  // past the last entry: a sentinel no occurrence lies below
-  if (tid == 0) ent[p.nent_cap] = make_int2(INT_MIN, -1);
-  __syncthreads();
-  // run[e] counts e's occurrences before the chunk: each expert's cursor
-  // starts at the entry holding occurrence run[e], the first of [ptr[e],
-  // ptr[e + 1]) whose cumulative share exceeds it (shares ascend: a binary
-  // search); each tile moves it on past its own occurrences.  (The thread
-  // that sets a cursor is the one that walks it below: no barrier.)
-  for (int e = tid; e < E; e += nt) {
-    const int re = run[e], j1 = ptr[e + 1];
-    int lo2 = ptr[e], hi2 = j1;
-    while (lo2 < hi2) {
-      const int mid = (lo2 + hi2) >> 1;
-      if (ent[mid].x <= re) lo2 = mid + 1;
-      else hi2 = mid;
-    }
-    cur[e] = make_int2(lo2, j1);
-  }
-  int2 *mywc = wc + wave * ws;
-  for (int64_t base = lo; base < hi; base += tile) {
-    int ev[IPT];
-#pragma unroll
-    for (int i = 0; i < IPT; ++i) ev[i] = evn[i];
-    // the next tile's ids load while this one is ranked (the barriers below
-    // order LDS only, so they do not wait for these loads)
-    if (base + tile < hi) load_tile(base + tile);
-    if (p.slot_out) slot_before(p, run, ptr, ent, excl);
-    for (int e = lane; e < E; e += 64) mywc[e].x = 0;
-    wave_sync();
-    const int64_t wbase = base + (int64_t)wave * 64 * IPT + lane;
-    // ids of this lane left in the chunk (the stores' bound)
-    const int lim = (int)(hi - wbase < 64 * IPT ? hi - wbase : 64 * IPT);
-    int lr[IPT];
-#pragma unroll
-    for (int i = 0; i < IPT; ++i)   // (ev is -1 past the end)
-      lr[i] = wave_rank<2>(ev[i], (unsigned)ev[i] < (unsigned)E, p.nbits, reinterpret_cast<int *>(mywc));
-    lds_barrier();
-    // each wave's offset of e, and the entry holding that first occurrence
-    // (the sentinel when it lies past e's entries), found from e's cursor
-    // (offsets grow with the wave), which then moves past the tile: up to
-    // four waves one thread walks each expert's column once, else the
-    // columns are scanned first
-    // (the current entry's share end stays in a register: LDS is read only
-    // when the walk moves on)
-    auto entry_of = [&](int2 c, int &j, int &ej, int off) {
-      while (j < c.y && ej <= off) {
-        ++j;
-        ej = j < c.y ? ent[j].x : INT_MAX;
-      }
-      return j < c.y ? j : p.nent_cap;
-    };
-    if (nw <= 4) {
-      for (int e = tid; e < E; e += nt) {
-        const int2 c = cur[e];
-        int j = c.x, r = run[e];
-        int ej = j < c.y ? ent[j].x : INT_MAX;
-        for (int w = 0; w < nw; ++w) {
-          int2 *x = wc + w * ws + e;
-          const int t = x->x;
-          *x = make_int2(r, entry_of(c, j, ej, r));
-          r += t;
-        }
-        run[e] = r;
-        entry_of(c, j, ej, r);
-        if (j != c.x) cur[e].x = j;
-      }
-    } else {
-      scan_wave_columns<2>(reinterpret_cast<int *>(wc), ws, E, nw, run);
-      lds_barrier();
-      for (int e = tid; e < E; e += nt) {
-        const int2 c = cur[e];
-        int j = c.x;
-        int ej = j < c.y ? ent[j].x : INT_MAX;
-        for (int w = 0; w < nw; ++w) {
-          int2 *x = wc + w * ws + e;
-          x->y = entry_of(c, j, ej, x->x);
-        }
-        entry_of(c, j, ej, run[e]);
-        if (j != c.x) cur[e].x = j;
-      }
-    }
-    lds_barrier();
-    int dv[IPT];
-#pragma unroll
-    for (int i = 0; i < IPT; ++i) {
-      // occurrence rho of e: the entry of the wave's first occurrence holds
-      // it unless the wave's occurrences run past that instance's share
-      // (then the entries after it, or none past e's last)
-      const int e = ev[i];
-      const bool valid = (unsigned)e < (unsigned)E;
-      const int2 r = mywc[valid ? e : 0];
-      const int rho = r.x + lr[i];
-      const int2 en = ent[r.y];
-      const bool hit = rho < en.x;
-      int dest = valid && hit ? en.y : -1;
-      const bool slow = valid && !hit;
-      if (slow) {   // (skipped when no lane of the wave needs it)
-        const int j1 = ptr[e + 1];
-        for (int j = r.y + 1; j < j1; ++j) {
-          const int2 en2 = ent[j];
-          if (rho < en2.x) {
-            dest = en2.y;
-            break;
-          }
-        }
-      }
-      if (i * 64 < lim) p.dest_out[wbase + i * 64] = dest;
-      dv[i] = dest;
-    }
-    if (p.slot_out) slot_write<IPT>(p, dv, wbase, hi, so, excl, wcd);
-    lds_barrier();
-  }
-}
-
-// ---------------------------------------------------------------- single-launch plan
-//
-// Workgroup 0 solves; workgroups 1..nb each hold one chunk of ids.  The
-// plan's generation g orders the hand-overs (control words 8..11 above):
-//   chunk -> everyone: chunk b writes its count of every expert to
-//     pub[b][e] and adds it to the histogram ghist[g & 1][e] with an
-//     agent-scope atomic (integer adds commute: the sum does not depend on
-//     their order; word E counts bad ids), then makes one release increment
-//     of the 64-bit arrival counter; the value it moves the counter from,
-//     g nb + c, gives g and tells the last arrival (c = nb - 1).  A chunk
-//     reads g from word 10 to pick the histogram buffer before it arrives;
-//     that read can only be stale when the solver has already given up on
-//     this plan, and the chunk then takes its adds back.
-//   last chunk -> chunks: word 1 of every chunk's flag line = g + 1
-//     (release): every count is written.  Chunk b then sums its first
-//     occurrence index of each expert from the counts of the chunks before
-//     it, or from the histogram less the counts of the chunks from b on,
-//     whichever reads fewer rows (at most nb / 2).
-//   last chunk -> solver: the histogram against row self of Omega, released
-//     as the verdict ((g + 1) << 2) | v.  Only the solver polls that word.
-//   solver -> chunk b: word 0 of chunk b's flag line = g + 1 (release) once
-//     the outputs, this rank's instance list and the final status are
-//     written.  Chunk b polls only its own 128-byte flag line, acquires, and
-//     reads the instance list in one round trip.
-// No word is cleared between plans except the other histogram buffer (by
-// the solver, before any chunk of the next plan can use it): a workspace is
-// zero-filled before its first plan, and a plan whose bounded wait gave up
-// (SYNC) leaves nothing that a later plan's waits could mistake for its own.
-
 // Omega to LDS with its status bits and total load (row self included as
 // gathered; the caller swaps in the histogram later).  `between` runs on
 // every thread once the first loads are issued (LDS set-up that overlaps
@@ -3072,6 +2686,385 @@ __device__ __forceinline__ void load_omega(const Plan &p, int *om, int *misc, Be
     if (tot) atomicAdd(reinterpret_cast<unsigned long long *>(misc + 8), (unsigned long long)tot);
   }
 }
+
+// Row self of Omega' in om := the histogram hs; SELF_DIFF in misc[0] when the
+// gathered row differs, and the total load of misc[8..9] follows.  Ends with
+// a barrier.
+__device__ __forceinline__ void swap_self_row(const Plan &p, const SingleState &t) {
+  bool diff = false;
+  int64_t adj = 0;
+  for (int e = threadIdx.x; e < p.E; e += blockDim.x) {
+    const int h = t.hs[e], g = t.om[p.self * p.E + e];
+    diff |= g != h;
+    adj += (int64_t)(h > 0 ? h : 0) - (int64_t)(g > 0 ? g : 0);
+    t.om[p.self * p.E + e] = h;
+  }
+  adj = (int64_t)wave_sum_u64((uint64_t)adj);
+  const uint64_t any_diff = __ballot(diff);
+  if (lane_id() == 0) {
+    if (any_diff) atomicOr(reinterpret_cast<unsigned *>(&t.misc[0]), TOPOEP_ST_SELF_DIFF);
+    if (adj) atomicAdd(reinterpret_cast<unsigned long long *>(t.misc + 8), (unsigned long long)adj);
+  }
+  lds_barrier();
+}
+
+// The same steps with every domain's state in the LDS of one CU; each
+// domain's refinement runs on its own wave.  Used when Omega and all q
+// columns fit in LDS.  Workgroups beyond the first compute the histogram
+// blocks' offsets for the reroute.  Form: kRefineReg or kRefineLds, whichever
+// the shape takes (both in one kernel spilled registers).
+template <int Form>
+__global__ __launch_bounds__(1024) void solve_single_kernel(Plan p0) {
+  extern __shared__ int64_t smem_1[];
+  int *sm = reinterpret_cast<int *>(smem_1);
+  if (blockIdx.x > 0) {
+    block_offsets(p0, blockIdx.x - 1, sm);
+    return;
+  }
+  {
+    // the blocks' bad-id flags and Omega on their way together; row self of
+    // Omega := the histogram once the helpers have its totals
+    const Plan p = solver_plan(role_plan(p0));
+    const SingleState t = single_state(p, sm);
+    int bad = 0;
+    for (int b = threadIdx.x; b < p.nb; b += blockDim.x) bad |= p.blk_err[b];
+    load_omega(p, t.om, t.misc, [&] { single_init(p, t); });
+    const uint64_t any_bad = __ballot(bad != 0);
+    if (lane_id() == 0 && any_bad) atomicOr(reinterpret_cast<unsigned *>(&t.misc[0]), TOPOEP_ST_BAD_ID);
+    row_self(p, t.hs, t.qcol, &t.misc[10]);
+    swap_self_row(p, t);
+  }
+  // (the plan's fields load again: see role_plan)
+  const Plan p = solver_plan(role_plan(p0));
+  const SingleState t = single_state(p, sm);
+  uint32_t gst = (uint32_t)t.misc[0];
+  if (out_of_range(p, *reinterpret_cast<const unsigned long long *>(t.misc + 8))) gst |= TOPOEP_ST_RANGE;
+  single_plan<Form>(p, t, gst, false);
+  if (threadIdx.x == 0)   // (a helper still running adds its own last)
+    __hip_atomic_fetch_sub(&p.ctrl[kCtrlHelpers], (uint32_t)p.n_helpers, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (p.recv_out && !(gst & kNoPlan)) single_recv_counts(p, t);
+}
+
+// ---------------------------------------------------------------- send-buffer slots
+//
+// The send buffer groups the assignments by destination (ranks ascending,
+// row-major order inside one destination).  An assignment's slot is
+// offs[d] + (assignments to d before its tile) + (those of earlier waves of
+// the tile) + (its rank among its wave's earlier assignments to d).  The
+// count before a tile follows from the per-expert counts before it, with no
+// pass over earlier ids: expert e's occurrences are dealt to its instances
+// in occurrence order, instance j taking [end(j-1), end(j)), so
+// clamp(run[e] - end(j-1), 0, end(j) - end(j-1)) of them went to j's rank.
+
+// offs[0..R) holds the send counts: it becomes their exclusive prefix with
+// the total at offs[R] (tmp: blockDim/64 + 1 words); `first` writes it out.
+__device__ void slot_offsets(const Plan &p, int *offs, int *tmp, bool first) {
+  lds_barrier();
+  offs[p.R] = block_excl_scan(offs, p.R, tmp);
+  if (first && p.offs_out)
+    for (int r = threadIdx.x; r <= p.R; r += blockDim.x) p.offs_out[r] = offs[r];
+}
+
+// Per-wave counts to offsets, one column per key: wc[(w * ws + k) * S] (w <
+// nw <= 16 waves, k < n keys, ws > n odd so a column's words sit in distinct
+// banks; S: words per element) becomes base[k] + the counts of waves
+// 0..w-1, and base[k] grows by the column's total (base may be null:
+// offsets from 0).  Beyond four waves a group of g lanes (g = nw rounded up
+// to a power of two) per key scans the column in registers instead of
+// walking it with nw dependent LDS round trips.
+template <int S = 1>
+__device__ inline void scan_wave_columns(int *wc, int ws, int n, int nw, int *base) {
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
+  if (nw <= 4) {
+    // short columns: one thread walks each
+    for (int k = tid; k < n; k += nt) {
+      int run = base ? base[k] : 0;
+      for (int w = 0; w < nw; ++w) {
+        const int t = wc[(w * ws + k) * S];
+        wc[(w * ws + k) * S] = run;
+        run += t;
+      }
+      if (base) base[k] = run;
+    }
+    return;
+  }
+  const int lg = nw <= 1 ? 0 : 32 - __clz(nw - 1);   // log2 of the group size
+  const int g = 1 << lg, w = lane & (g - 1);
+  for (int k = tid >> lg; k < n; k += nt >> lg) {
+    const int v = w < nw ? wc[(w * ws + k) * S] : 0;
+    int x = v;
+    // inclusive scan inside the group (row shifts; a group never crosses a row)
+    int y;
+    y = (int)dpp_mov<0x111>((uint32_t)x); x += w >= 1 ? y : 0;
+    y = (int)dpp_mov<0x112>((uint32_t)x); x += w >= 2 ? y : 0;
+    y = (int)dpp_mov<0x114>((uint32_t)x); x += w >= 4 ? y : 0;
+    y = (int)dpp_mov<0x118>((uint32_t)x); x += w >= 8 ? y : 0;
+    const int tot = __shfl(x, lane | (g - 1));
+    const int b0 = base ? base[k] : 0;
+    if (w < nw) wc[(w * ws + k) * S] = b0 + x - v;
+    if (base && w == 0) base[k] = b0 + tot;
+  }
+}
+
+// ---------------------------------------------------------------- reroute
+
+// The workgroup holds the chunk of the same histogram block.  An expert's
+// occurrences go to its instances in order, so when the chunk's occurrences
+// of e all lie inside one instance's share they need no rank: one
+// destination, looked up by id.  Only an expert whose occurrences run past a
+// share's end in this chunk ("crossing") has its ids ranked, tile by tile,
+// and there is at most one such (chunk, expert) pair per share end in the
+// whole plan, so most chunks stream with no barrier.
+//
+// td[e]: the destination of e's occurrences in the chunk, or ~j where they
+// start in entry j and run past its end; tx[e] is then the index of e's next
+// occurrence.
+//
+// Bound: HBM (4 B read and 4 B written per id): 80 us for 2^26 ids, 6.7 TB/s.
+// Ranking every id (a ballot per id bit) was issue bound in a long chain of
+// tiles; 256-thread blocks of it, 3641 of them, reached 85 us, but the solver
+// then summed 3641 rows of counts (36 us, now 512 rows, 10).  One contiguous
+// part per wave instead of a tile shared by the waves: 90 us, and 67 against
+// 47 for the histogram (8192 streams of 2 KB pieces).  Plan with inputs that
+// alternate, 2^26 ids, E = 128: 193 -> 131 us.
+//
+// Slots: also the send-buffer slots.  A wave's piece of a tile is then read
+// in 4-byte order (element i of lane l is id i * 64 + l), else 16 bytes per
+// lane (element 4 j + c is id (j * 64 + l) * 4 + c).
+template <int V, bool Slots>
+__global__ __launch_bounds__(1024, 8) void reroute_kernel(Plan p) {
+  extern __shared__ int smem_r[];
+  constexpr int K = 4 * V;   // ids per lane and tile
+  const int tid = threadIdx.x, nt = blockDim.x, nw = nt >> 6, lane = tid & 63, wave = tid >> 6;
+  const int E = p.E, es = E | 1, rs = p.R | 1;
+  int2 *ent = reinterpret_cast<int2 *>(smem_r);   // nent_cap: (cumulative share, rank) per entry
+  int *td = reinterpret_cast<int *>(ent + p.nent_cap);   // E
+  int *tx = td + E;                  // E
+  int *ptr = tx + E;                 // E + 1
+  int *wc = ptr + E + 1;             // nw * es: per wave a crossing expert's count in the tile, then its next occurrence
+  int *wcd = wc + nw * es;           // nw * rs: per wave and rank the count in the tile, then the next slot
+  int *so = wcd + nw * rs;           // R + 1 + nw + 1: next slot per rank, scan scratch
+  int *flag = so + p.R + nw + 2;     // 1: an expert crosses in this chunk
+  const int b = blockIdx.x;
+  const int64_t lo = (int64_t)b * p.chunk;
+  const int64_t hi = lo + p.chunk < p.n ? lo + p.chunk : p.n;
+  const uint32_t fin = p.ctrl[kCtrlFinal];
+  if (fin & (kNoPlan | TOPOEP_ST_SYNC)) {
+    for (int64_t i = lo + tid; i < hi; i += nt) p.dest_out[i] = -1;
+    if (Slots) {
+      for (int64_t i = lo + tid; i < hi; i += nt) p.slot_out[i] = -1;
+    }
+    if (b == 0 && p.offs_out)
+      for (int r = tid; r <= p.R; r += nt) p.offs_out[r] = 0;
+    return;
+  }
+  const bool vec = (reinterpret_cast<uintptr_t>(p.topk) & 15) == 0;
+  const bool vec_out = (reinterpret_cast<uintptr_t>(p.dest_out) & 15) == 0;
+  const int64_t tile = (int64_t)nw * 64 * K, wofs = (int64_t)wave * 64 * K;
+  int nx[K];
+  auto load_piece = [&](int64_t base) {
+    if constexpr (Slots) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) nx[i] = base + i * 64 + lane < hi ? p.topk[base + i * 64 + lane] : -1;
+    } else {
+      load_ids<V>(p.topk, base, hi, vec, nx);
+    }
+  };
+  // the first tile's ids are on their way while the tables are made
+  load_piece(lo + wofs);
+  if (p.offs_out) {
+    for (int r = tid; r < p.R; r += nt) so[r] = p.send_out[r];
+    slot_offsets(p, so, so + p.R + 1, b == 0);
+  }
+  if (tid == 0) *flag = 0;
+  for (int e = tid; e <= E; e += nt) {
+    const int v = p.csr_ptr[e];
+    ptr[e] = v < 0 ? 0 : (v > p.nent_cap ? p.nent_cap : v);
+    if (e < E) {
+      tx[e] = p.offsets[(int64_t)b * E + e];
+      td[e] = p.partials[(int64_t)b * E + e];
+    }
+  }
+  for (int j = tid; j < p.nent_cap; j += nt) ent[j] = make_int2(p.csr_end[j], p.csr_r[j]);
+  __syncthreads();
+  bool any = false;
+  for (int e = tid; e < E; e += nt) {
+    const int start = tx[e], end = start + td[e], j1 = ptr[e + 1];
+    // the entry holding occurrence `start`: the first whose cumulative share
+    // exceeds it (shares ascend)
+    int j = ptr[e];
+    if constexpr (Slots) {
+      // assignments of earlier chunks per rank: entry j holds occurrences
+      // [end(j - 1), end(j))
+      int from = 0;
+      for (int i = j; i < j1 && from < start; ++i) {
+        const int2 en = ent[i];
+        const int c = imin(start, en.x) - from;
+        if (c > 0) atomicAdd(&so[en.y], c);
+        from = en.x;
+      }
+    }
+    for (int top = j1; j < top;) {
+      const int mid = (j + top) >> 1;
+      if (ent[mid].x <= start) j = mid + 1;
+      else top = mid;
+    }
+    const int2 en = j < j1 ? ent[j] : make_int2(INT_MIN, -1);
+    const bool inside = end <= en.x;
+    td[e] = inside ? en.y : ~j;
+    any |= !inside && end > start;
+  }
+  if (__ballot(any) && lane == 0) *flag = 1;
+  __syncthreads();
+  const bool crossing = *flag != 0;
+  int *mywc = wc + wave * es, *mywcd = wcd + wave * rs;
+  for (int64_t tb = lo; tb < hi; tb += tile) {
+    const int64_t base = tb + wofs;
+    int ev[K], dv[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) ev[i] = nx[i];
+    // the next tile's ids load while this one is placed (the barriers below
+    // order LDS only, so they do not wait for these loads)
+    if (tb + tile < hi) load_piece(base + tile);
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      const bool valid = (unsigned)ev[i] < (unsigned)E;   // (-1 past the end)
+      const int d = td[valid ? ev[i] : 0];
+      if (!valid) ev[i] = -1;
+      dv[i] = valid ? d : -1;
+    }
+    if (crossing) {
+      // the wave's crossing experts one at a time: each of their ids' rank in
+      // the wave's piece (into dv, below the sign bit), the wave's count into
+      // its row
+      for (int e = lane; e < E; e += 64) mywc[e] = 0;
+      wave_sync();
+      uint32_t todo = 0;   // this lane's elements not yet ranked
+#pragma unroll
+      for (int i = 0; i < K; ++i) todo |= (ev[i] >= 0 && dv[i] < 0 ? 1u : 0u) << i;
+      uint64_t pend;
+      while ((pend = __ballot(todo != 0u)) != 0) {
+        int e1 = 0;
+#pragma unroll
+        for (int i = K - 1; i >= 0; --i) e1 = (todo >> i) & 1u ? ev[i] : e1;
+        const int ec = readlane_i32(e1, __ffsll((long long)pend) - 1);
+        int seen = 0;
+        if constexpr (Slots) {
+#pragma unroll
+          for (int i = 0; i < K; ++i) {
+            const uint64_t m = __ballot(ev[i] == ec);
+            if (ev[i] == ec) dv[i] = INT_MIN | count_below(m, seen);
+            seen += __popcll(m);
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < V; ++j) {
+            int below = seen;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const uint64_t m = __ballot(ev[4 * j + c] == ec);
+              below = count_below(m, below);
+              seen += __popcll(m);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              if (ev[4 * j + c] == ec) dv[4 * j + c] = INT_MIN | below++;
+          }
+        }
+        if (lane == 0) mywc[ec] = seen;
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+          if (ev[i] == ec) todo &= ~(1u << i);
+      }
+      lds_barrier();
+      // each wave's first occurrence index of a crossing expert
+      for (int e = tid; e < E; e += nt) {
+        if (td[e] >= 0) continue;
+        int r = tx[e];
+        for (int w = 0; w < nw; ++w) {
+          const int t = wc[w * es + e];
+          wc[w * es + e] = r;
+          r += t;
+        }
+        tx[e] = r;
+      }
+      lds_barrier();
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        if (ev[i] < 0 || dv[i] >= 0) continue;
+        const int rho = mywc[ev[i]] + (dv[i] & INT_MAX), j1 = ptr[ev[i] + 1];
+        int j = ~td[ev[i]];
+        while (j < j1 && ent[j].x <= rho) ++j;
+        dv[i] = j < j1 ? ent[j].y : -1;
+      }
+    }
+    if constexpr (Slots) {
+      for (int r = lane; r < p.R; r += 64) mywcd[r] = 0;
+      wave_sync();
+      int lr[K];
+#pragma unroll
+      for (int i = 0; i < K; ++i) lr[i] = wave_rank(dv[i], (unsigned)dv[i] < (unsigned)p.R, p.rbits, mywcd);
+      lds_barrier();
+      scan_wave_columns(wcd, rs, p.R, nw, so);
+      lds_barrier();
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        const int64_t idx = base + i * 64 + lane;
+        if (idx < hi) {
+          const bool valid = (unsigned)dv[i] < (unsigned)p.R;
+          p.dest_out[idx] = dv[i];
+          p.slot_out[idx] = valid ? mywcd[dv[i]] + lr[i] : -1;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        const int64_t idx = base + (int64_t)(j * 64 + lane) * 4;
+        if (vec_out && idx + 4 <= hi) {
+          v4i x;
+          x.x = dv[4 * j];
+          x.y = dv[4 * j + 1];
+          x.z = dv[4 * j + 2];
+          x.w = dv[4 * j + 3];
+          __builtin_nontemporal_store(x, reinterpret_cast<v4i *>(p.dest_out + idx));
+        } else {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            if (idx + c < hi) p.dest_out[idx + c] = dv[4 * j + c];
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------- single-launch plan
+//
+// Workgroup 0 solves; workgroups 1..nb each hold one chunk of ids.  The
+// plan's generation g orders the hand-overs (control words 8..11 above):
+//   chunk -> everyone: chunk b writes its count of every expert to
+//     pub[b][e] and adds it to the histogram ghist[g & 1][e] with an
+//     agent-scope atomic (integer adds commute: the sum does not depend on
+//     their order; word E counts bad ids), then makes one release increment
+//     of the 64-bit arrival counter; the value it moves the counter from,
+//     g nb + c, gives g and tells the last arrival (c = nb - 1).  A chunk
+//     reads g from word 10 to pick the histogram buffer before it arrives;
+//     that read can only be stale when the solver has already given up on
+//     this plan, and the chunk then takes its adds back.
+//   last chunk -> chunks: word 1 of every chunk's flag line = g + 1
+//     (release): every count is written.  Chunk b then sums its first
+//     occurrence index of each expert from the counts of the chunks before
+//     it, or from the histogram less the counts of the chunks from b on,
+//     whichever reads fewer rows (at most nb / 2).
+//   last chunk -> solver: the histogram against row self of Omega, released
+//     as the verdict ((g + 1) << 2) | v.  Only the solver polls that word.
+//   solver -> chunk b: word 0 of chunk b's flag line = g + 1 (release) once
+//     the outputs, this rank's instance list and the final status are
+//     written.  Chunk b polls only its own 128-byte flag line, acquires, and
+//     reads the instance list in one round trip.
+// No word is cleared between plans except the other histogram buffer (by
+// the solver, before any chunk of the next plan can use it): a workspace is
+// zero-filled before its first plan, and a plan whose bounded wait gave up
+// (SYNC) leaves nothing that a later plan's waits could mistake for its own.
 
 // Solver side of a redo: hs[e] = the histogram of local_topk, gh[e] (every
 // chunk's adds, acquired with the last chunk's verdict), BAD_ID from gh[E].
@@ -3206,21 +3199,8 @@ __device__ __forceinline__ void fused_solver(const Plan &p, int *sm) {
     single_init(p, t);
     lds_barrier();
     read_histogram(p, p.ghist + (int64_t)(t.misc[40] & 1) * (E + 1), t.hs, t.misc);
-    bool diff = false;
-    int64_t adj = 0;
-    for (int e = tid; e < E; e += nt) {
-      const int h = t.hs[e], g = t.om[p.self * E + e];
-      diff |= g != h;
-      adj += (int64_t)(h > 0 ? h : 0) - (int64_t)(g > 0 ? g : 0);
-      t.om[p.self * E + e] = h;
-    }
-    adj = (int64_t)wave_sum_u64((uint64_t)adj);
-    const uint64_t any_diff = __ballot(diff);
-    if (lane_id() == 0) {
-      atomicOr(reinterpret_cast<unsigned *>(&t.misc[0]), (any_diff ? TOPOEP_ST_SELF_DIFF : 0u) | neg0);
-      if (adj) atomicAdd(reinterpret_cast<unsigned long long *>(t.misc + 8), (unsigned long long)adj);
-    }
-    lds_barrier();
+    if (tid == 0 && neg0) atomicOr(reinterpret_cast<unsigned *>(&t.misc[0]), neg0);
+    swap_self_row(p, t);
     uint32_t gst = (uint32_t)t.misc[0];
     if (out_of_range(p, total0 + *reinterpret_cast<const unsigned long long *>(t.misc + 8))) gst |= TOPOEP_ST_RANGE;
     single_plan<Form>(p, t, gst, true);
@@ -3709,7 +3689,7 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
 
   Shape s;
   const int ipt_req = lc ? lc->items_per_thread : 0;
-  s.ipt = ipt_req ? ipt_req : (q.n >= ((int64_t)1 << 24) ? 8 : 4);   // 8 ids per thread measured ~3 % faster from 2^24 on
+  s.ipt = ipt_req ? ipt_req : (q.n >= ((int64_t)1 << 24) ? 8 : 4);
   s.bt = lc && lc->block_threads ? lc->block_threads : 256;
   s.st = lc && lc->solve_threads ? lc->solve_threads : 0;
   const int solver = lc ? lc->solver : 0;
@@ -3764,20 +3744,46 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
     }
   }
 
+  int64_t ws_rows = 0;   // rows of the blocks' counts and offsets in the workspace
   if (s.mode != 3) {
+  // instance entries, the chunk's table (destination, next occurrence), ptr,
+  // per-wave counts of crossing experts, per-wave slots, next slots and scan
+  // scratch, a flag
+  // (the largest E and R taken come from the layout with (offset, entry)
+  // pairs per wave and expert that the reroute had room for)
+  const size_t w0 = s.bt / 64;
+  const size_t lds_bound = (2 * ((size_t)q.nent_cap + 1) + 2 * (size_t)E + 2 * (size_t)(E | 1) * w0 + (size_t)E +
+                            (size_t)E + 1 + (size_t)(R | 1) * w0 + (size_t)R + (size_t)R + 1 + w0 + 1) * 4;
+  auto lds_reroute = [&](int bt) {
+    const size_t nw = bt / 64;
+    return (2 * (size_t)q.nent_cap + 2 * (size_t)E + (size_t)E + 1 + (size_t)(E | 1) * nw + (size_t)(R | 1) * nw +
+            (size_t)R + 1 + nw + 1 + 1) * 4;
+  };
+  const bool given = lc && (lc->items_per_thread || lc->block_threads || lc->tiles_per_block > 0);
   const int64_t tile = (int64_t)s.bt * s.ipt;
   const int64_t tiles = (q.n + tile - 1) / tile;
-  // about 16 K ids per block, 2048..8192 blocks: every CU keeps eight
-  // 256-thread blocks resident with work to spare, while the solver's
-  // per-block offset scan (nb words per expert) stays short
+  // about 16 K ids per block of a small-block launch, 2048..8192 blocks
   const int64_t want = q.n / 16384;
-  const int64_t target = want < kMinBlocks ? kMinBlocks : (want > kMaxBlocks ? kMaxBlocks : want);
-  int64_t tpb = lc && lc->tiles_per_block > 0 ? lc->tiles_per_block : (tiles + target - 1) / target;
+  const int64_t small_blocks = want < kMinBlocks ? kMinBlocks : (want > kMaxBlocks ? kMaxBlocks : want);
+  int64_t tpb = lc && lc->tiles_per_block > 0 ? lc->tiles_per_block : (tiles + small_blocks - 1) / small_blocks;
   if (tpb < 1) tpb = 1;
   q.chunk = tpb * tile;
-  const int64_t nb = q.n > 0 ? (q.n + q.chunk - 1) / q.chunk : 1;
-  if (nb > (1 << 24)) return TOPOEP_ELIMIT;
-  q.nb = (int)nb;
+  ws_rows = q.n > 0 ? (q.n + q.chunk - 1) / q.chunk : 1;
+  if (ws_rows > (1 << 24)) return TOPOEP_ELIMIT;
+  if (!given && q.n > kOneTileIds) {
+    // Large blocks of 1024 threads, two per CU: the solver and its helpers
+    // read every block's counts (1.6 M ids, E = 256: 1563 blocks of 256
+    // threads 52 us a plan, 196 of these 28).  The workspace
+    // keeps its rows, more than these blocks need: its size, and with it
+    // which plans the no-allocation array takes, is not the launch's.
+    s.ipt = 8;
+    s.bt = 1024;
+    while (s.bt > 256 && lds_reroute(s.bt) > (size_t)kLdsLimit) s.bt >>= 1;
+    const int64_t big = (int64_t)s.bt * s.ipt;
+    q.chunk = big;
+    if (q.n > big * kLongBlocks) q.chunk = (q.n + (int64_t)kLongBlocks * 64 - 1) / ((int64_t)kLongBlocks * 64) * 64;
+  }
+  q.nb = q.n > 0 ? (int)((q.n + q.chunk - 1) / q.chunk) : 1;
   q.n_helpers = (E + kOffsetExperts - 1) / kOffsetExperts;
   if (general) {
     if (solver == 1) return TOPOEP_EINVAL;
@@ -3802,13 +3808,10 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
                                                      s.st, s.lds_solve))
     return TOPOEP_ELIMIT;
   s.solve_groups = q.n_solvers + q.n_helpers;
-  s.lds_hist = (size_t)E * 4;
-  // instance entries, cursors, per-wave (count, entry) pairs, run, ptr,
-  // per-wave rank counts, counts before the tile, send offsets and scratch
-  s.lds_reroute = (2 * ((size_t)q.nent_cap + 1) + 2 * (size_t)E + 2 * (size_t)(E | 1) * (s.bt / 64) + (size_t)E +
-                   (size_t)E + 1 + (size_t)(R | 1) * (s.bt / 64) + (size_t)R + (size_t)R + 1 + s.bt / 64 + 1) * 4;
+  s.lds_hist = (size_t)E * 4 * (s.bt / 64);
+  s.lds_reroute = lds_reroute(s.bt);
   s.lds_fused = 0;
-  if (s.lds_reroute > (size_t)kLdsLimit) return TOPOEP_ELIMIT;
+  if (lds_bound > (size_t)kLdsLimit) return TOPOEP_ELIMIT;
   }
 
   // routing: the largest divisor c of M with (instances routed at once) * c
@@ -3838,9 +3841,9 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
   const size_t o_flg = take(one ? (size_t)q.nb * kFlagStride * 4 : 0);
   const size_t o_gh = take(one ? (size_t)2 * (E + 1) * 4 : 0);
   s.zero_bytes = off;
-  const size_t o_part = take(three ? (size_t)q.nb * E * 4 : 0);
-  const size_t o_offs = take(three ? (size_t)q.nb * E * 4 : 0);
-  const size_t o_berr = take(three ? (size_t)q.nb * 4 : 0);
+  const size_t o_part = take(three ? (size_t)ws_rows * E * 4 : 0);
+  const size_t o_offs = take(three ? (size_t)ws_rows * E * 4 : 0);
+  const size_t o_berr = take(three ? (size_t)ws_rows * 4 : 0);
   const size_t o_repl = take(s.mode == 2 ? (size_t)q.M * imax(q.cap1, 1) * 4 : 0);
   const size_t o_sege = take(s.mode == 2 ? (size_t)q.M * q.I * 4 : 0);
   const size_t o_segq = take(s.mode == 2 ? (size_t)q.M * q.I * 4 : 0);
@@ -3895,15 +3898,13 @@ void set_attrs() {
   if (g_attrs_set) return;
   allow_lds(hist_kernel<1>);
   allow_lds(hist_kernel<2>);
-  allow_lds(hist_kernel<4>);
-  allow_lds(hist_kernel<8>);
-  allow_lds(reroute_kernel<1>);
-  allow_lds(reroute_kernel<2>);
-  allow_lds(reroute_kernel<4>);
-  allow_lds(reroute_kernel<8>);
+  allow_lds(reroute_kernel<1, false>);
+  allow_lds(reroute_kernel<1, true>);
+  allow_lds(reroute_kernel<2, false>);
   allow_lds(solve_kernel<512>);
   allow_lds(solve_kernel<1024>);
-  allow_lds(solve_single_kernel);
+  allow_lds(solve_single_kernel<kRefineReg>);
+  allow_lds(solve_single_kernel<kRefineLds>);
   allow_lds(plan_fused_kernel<1, kRefineLds>);
   allow_lds(plan_fused_kernel<1, kRefineReg>);
   allow_lds(plan_fused_kernel<1, kRefinePairs>);
@@ -3922,30 +3923,29 @@ void set_attrs() {
   g_attrs_set = true;
 }
 
+// Four ids per lane and load: two loads a tile from 8 ids per thread on.
 void launch_hist(const Plan &p, const Shape &s, hipStream_t st) {
   const dim3 g(p.nb), b(s.bt);
-  switch (s.ipt) {
-    case 1: hipLaunchKernelGGL(hist_kernel<1>, g, b, s.lds_hist, st, p); break;
-    case 2: hipLaunchKernelGGL(hist_kernel<2>, g, b, s.lds_hist, st, p); break;
-    case 4: hipLaunchKernelGGL(hist_kernel<4>, g, b, s.lds_hist, st, p); break;
-    default: hipLaunchKernelGGL(hist_kernel<8>, g, b, s.lds_hist, st, p); break;
-  }
+  if (s.ipt < 8) hipLaunchKernelGGL(hist_kernel<1>, g, b, s.lds_hist, st, p);
+  else hipLaunchKernelGGL(hist_kernel<2>, g, b, s.lds_hist, st, p);
 }
 
+// (with slots four ids a tile: eight spill the 64 registers of two blocks a CU)
 void launch_reroute(const Plan &p, const Shape &s, hipStream_t st) {
   const dim3 g(p.nb), b(s.bt);
-  switch (s.ipt) {
-    case 1: hipLaunchKernelGGL(reroute_kernel<1>, g, b, s.lds_reroute, st, p); break;
-    case 2: hipLaunchKernelGGL(reroute_kernel<2>, g, b, s.lds_reroute, st, p); break;
-    case 4: hipLaunchKernelGGL(reroute_kernel<4>, g, b, s.lds_reroute, st, p); break;
-    default: hipLaunchKernelGGL(reroute_kernel<8>, g, b, s.lds_reroute, st, p); break;
-  }
+  if (p.slot_out) hipLaunchKernelGGL((reroute_kernel<1, true>), g, b, s.lds_reroute, st, p);
+  else if (s.ipt < 8) hipLaunchKernelGGL((reroute_kernel<1, false>), g, b, s.lds_reroute, st, p);
+  else hipLaunchKernelGGL((reroute_kernel<2, false>), g, b, s.lds_reroute, st, p);
 }
 
 void launch_solve(const Plan &p, const Shape &s, hipStream_t st) {
-  if (s.mode == 1) hipLaunchKernelGGL(solve_single_kernel, dim3(s.solve_groups), dim3(s.st), s.lds_solve, st, p);
-  else if (s.st <= 512) hipLaunchKernelGGL(solve_kernel<512>, dim3(s.solve_groups), dim3(s.st), s.lds_solve, st, p);
-  else hipLaunchKernelGGL(solve_kernel<1024>, dim3(s.solve_groups), dim3(s.st), s.lds_solve, st, p);
+  const dim3 g(s.solve_groups), b(s.st);
+  if (s.mode == 1 && refine_form(p.G, p.I, p.PN) != kRefineLds)
+    hipLaunchKernelGGL((solve_single_kernel<kRefineReg>), g, b, s.lds_solve, st, p);
+  else if (s.mode == 1)
+    hipLaunchKernelGGL((solve_single_kernel<kRefineLds>), g, b, s.lds_solve, st, p);
+  else if (s.st <= 512) hipLaunchKernelGGL(solve_kernel<512>, g, b, s.lds_solve, st, p);
+  else hipLaunchKernelGGL(solve_kernel<1024>, g, b, s.lds_solve, st, p);
 }
 
 template <int IPT>

@@ -93,7 +93,11 @@ typedef struct topoep_launch {
 
 /* Launch shape a plan will use (topoep_plan_shape). */
 typedef struct topoep_shape {
-  int32_t kernels;          /* kernels one plan enqueues: 1 (solver 3) or 3     */
+  int32_t kernels;          /* stages of a plan (topoep_plan_stage): 1 (solver 3) */
+                            /* or 3.  Chosen by default (launch NULL or zero     */
+                            /* shape fields), a small plan with the per-domain   */
+                            /* solver enqueues its three stages' work as one     */
+                            /* kernel; each stage still runs alone               */
   int32_t solver;           /* 1, 2 or 3 as in topoep_launch.solver              */
   int32_t items_per_thread; /* ids per thread of the histogram/reroute work      */
   int32_t chunk_blocks;     /* workgroups holding ids                            */
@@ -133,7 +137,9 @@ typedef struct topoep_shape {
 
 /*
  * Bytes of device workspace topoep_plan needs for these sizes (default
- * launch shape).  Returns TOPOEP_OK, TOPOEP_EINVAL for invalid sizes, or
+ * launch shape).  A plan whose stages run as one kernel (topoep_shape) asks
+ * for that kernel's buffers too; with the bytes of launch shape solver 2 it
+ * runs as three kernels.  Returns TOPOEP_OK, TOPOEP_EINVAL for invalid sizes, or
  * TOPOEP_ELIMIT when one domain's solver state cannot fit in LDS.
  */
 int topoep_workspace_bytes(const topoep_topology *topo, int32_t T, int32_t k,

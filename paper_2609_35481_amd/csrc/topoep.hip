@@ -16,6 +16,9 @@
 //              bounded grid barrier that publishes the inter-node placement
 //              of every domain and a last-workgroup step that assembles
 //              this rank's instance list.
+//            (Where that solver is chosen by default and the plan is small
+//            enough, the three kernels' work runs as one launch:
+//            plan_domains_kernel.)
 //            Either way: domain demand D (Eq. 4), inter-node placement by
 //            the benefit b = 2 D S - W (Eq. 9), routing construction q, U, L
 //            (Section 4.3) and intra-node refinement (Eq. 10) with wave64
@@ -82,12 +85,16 @@ constexpr uint32_t kVerdictRedo = 2;
 // words 16..63: phase stamps of the instrumented build (TOPOEP_STAMPS)
 constexpr int kCtrlStamps = 16;
 
+constexpr int kMiscGen = 40;    // LDS word of the solvers' misc array: the plan's generation
 constexpr uint32_t kNoPlan = TOPOEP_ST_BAD_ID | TOPOEP_ST_NEG_LOAD | TOPOEP_ST_RANGE | TOPOEP_ST_COST;
 constexpr int kLdsLimit = 160 * 1024;   // LDS per workgroup on gfx950
 constexpr int kMaxSolveGroups = 128;    // co-resident by a wide margin (256 CUs)
 constexpr int kMinBlocks = 2048;        // histogram/reroute blocks to aim for, at least
 constexpr int kMaxBlocks = 8192;        // and at most
 constexpr int64_t kOneTileIds = 1 << 20;   // above: blocks of 1024 threads
+constexpr size_t kThreeOnly = 0;        // setup's max_ws: no one-launch plan with the per-domain solver
+constexpr int kOneThreads = 512;        // threads of plan_domains_kernel
+constexpr int kMaxOneGroups = 64;       // its workgroups at most (a quarter of 256 CUs)
 constexpr int kLongBlocks = 512;        // and at most this many of them (two per CU)
 constexpr int kOffsetExperts = 32;      // experts per offset workgroup
 // chunk workgroups the single-launch plan aims for: each chunk reads the
@@ -217,11 +224,19 @@ __device__ inline int vgpr(int v) {
 
 // The plan with its divisors in vector registers (see vgpr).
 __device__ inline Plan solver_plan(Plan q) {
-  FastDiv *fds[] = {&q.fE, &q.fG, &q.fGP, &q.fP, &q.fI, &q.fPN, &q.fCap, &q.fN, &q.fMI};
-  for (FastDiv *f : fds) {
-    f->m = (uint32_t)vgpr((int)f->m);
-    f->sh = (uint32_t)vgpr((int)f->sh);
-  }
+  auto keep = [](FastDiv &f) {
+    f.m = (uint32_t)vgpr((int)f.m);
+    f.sh = (uint32_t)vgpr((int)f.sh);
+  };
+  keep(q.fE);
+  keep(q.fG);
+  keep(q.fGP);
+  keep(q.fP);
+  keep(q.fI);
+  keep(q.fPN);
+  keep(q.fCap);
+  keep(q.fN);
+  keep(q.fMI);
   return q;
 }
 
@@ -475,7 +490,7 @@ __device__ void hist_from_partials(const Plan &p, int *hs, int *scratch) {
 // of the blocks, eight loads in flight.  scratch: one word per thread for
 // each expert group of this workgroup (one group when n_helpers covers E, as
 // the host sets it).
-__device__ void block_offsets(const Plan &p, int h, int *scratch) {
+__device__ __forceinline__ void block_offsets(const Plan &p, int h, int *scratch) {
   const int tid = threadIdx.x, nt = blockDim.x, E = p.E, nb = p.nb;
   const int ng = nt / kOffsetExperts;
   const int el = tid % kOffsetExperts, g = tid / kOffsetExperts;
@@ -1527,73 +1542,41 @@ __device__ inline uint64_t cand_key(int D, int e) {
   return ((uint64_t)(uint32_t)(0x7FFFFFFF - D) << 32) | (uint32_t)e;
 }
 
-// Rank of candidate c among the nc keys of its domain (keys are distinct);
-// the first cap ranks name the domain's stage-1 replicas.
-__device__ inline void rank_candidates(int c, int nc, int cap, const uint64_t *keys, int *out) {
-  const uint64_t kc = keys[c];
-  int rank = 0;
-  int c2 = 0;
-  for (; c2 + 8 <= nc; c2 += 8) {
-    uint64_t k[8];
+// Ranks of a domain's nc candidates by the whole workgroup, 64 candidates
+// (one per lane) against 16 keys a wave at a time; rk (nc words) starts at
+// zero.  General: keys are benefits (descending), ties to the lower expert of
+// es (||W_e|| differs per expert, so b does not follow D); else keys ascend
+// (cand_key) and are distinct.  The keys are broadcast reads; one thread per
+// candidate walking all keys took 2.6 us of dependent LDS reads for 96
+// candidates under the general model.
+template <bool General>
+__device__ __forceinline__ void rank_units(int nc, const uint64_t *keys, const int *es, int *rk) {
+  const int lane = lane_id(), wave = uniform_i32(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int blocks = (nc + 63) >> 6, parts = (nc + 15) >> 4;
+  const int lb = blocks <= 1 ? 0 : 32 - __clz(blocks - 1);
+  for (int u = wave; u < (parts << lb); u += nw) {
+    const int blk = u & ((1 << lb) - 1), k0 = (u >> lb) * 16;
+    if (blk >= blocks) continue;
+    const int c = blk * 64 + lane, cc = imin(c, nc - 1);
+    const uint64_t kc = keys[cc];
+    const int ec = General ? es[cc] : 0;
+    int below = 0;
+    uint64_t k[16];
+    int e2[16];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) k[u] = keys[c2 + u];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) rank += k[u] < kc;
-  }
-  for (; c2 < nc; ++c2) rank += keys[c2] < kc;
-  if (rank < cap) out[rank] = (int)(uint32_t)kc;
-}
-
-// Rank of candidate c by (benefit b descending, expert ascending) among nc
-// candidates with benefits bs[] and experts es[] (the general model, where
-// ||W_e|| differs per expert so b does not follow D); the first cap ranks
-// name the domain's stage-1 replicas.
-__device__ inline void rank_candidates_b(int c, int nc, int cap, const uint64_t *bs, const int *es, int *out) {
-  const uint64_t bc = bs[c];
-  const int ec = es[c];
-  int rank = 0;
-  for (int c2 = 0; c2 < nc; ++c2) {
-    const uint64_t b2 = bs[c2];
-    rank += b2 > bc || (b2 == bc && es[c2] < ec);
-  }
-  if (rank < cap) out[rank] = ec;
-}
-
-// Stage 1 (Eq. 9) candidates of domain d, by one wave: the experts whose
-// main is outside d with benefit b = 2 D S - W > 0 (D from om, Omega with
-// row self already the histogram when dom(self) = d), compacted with ballots
-// into keys ck_d; returns their count on every lane.
-__device__ int stage1_candidates_wave(const Plan &p, int d, const int *om, uint64_t *ck_d) {
-  const int lane = lane_id(), E = p.E, G = p.G;
-  int nc = 0;
-  for (int e0 = 0; e0 < E; e0 += 64) {
-    const int e = e0 + lane;
-    bool cand = false;
-    uint64_t key = 0;
-    if (e < E && (int)fdiv((uint32_t)e, p.fGP) != d) {
-      int D = 0;
-#pragma unroll 8
-      for (int j = 0; j < G; ++j) D += om[(d * G + j) * E + e];
-      cand = (int64_t)2 * D * p.S > p.W;
-      key = cand_key(D, e);
+    for (int i = 0; i < 16; ++i) {
+      const int at = imin(k0 + i, nc - 1);
+      k[i] = keys[at];
+      if (General) e2[i] = es[at];
     }
-    const uint64_t m = __ballot(cand);
-    if (cand) ck_d[nc + __popcll(m & lanemask_lt())] = key;
-    nc += __popcll(m);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const bool before = General ? (k[i] > kc || (k[i] == kc && e2[i] < ec)) : k[i] < kc;
+      below += before && k0 + i < nc ? 1 : 0;
+    }
+    if (c < nc && below) atomicAdd(&rk[c], below);
   }
-  wave_sync();
-  return nc;
 }
-
-// Stage 1 of domain d by one wave: candidates, then each ranked by key; the
-// first cap ranks fill repl_d (pre-filled with -1) and ccnt[d] = the count.
-__device__ void stage1_domain_wave(const Plan &p, int d, const int *om, uint64_t *ck_d, int *ccnt, int *repl_d) {
-  const int nc = stage1_candidates_wave(p, d, om, ck_d);
-  if (d == 0) STAMP(p, 22);
-  for (int c = lane_id(); c < nc; c += 64) rank_candidates(c, nc, p.cap1, ck_d, repl_d);
-  if (lane_id() == 0) ccnt[d] = nc;
-}
-
 
 // Stage 1 (Eq. 9) of every domain by the whole workgroup.  Item (d, e):
 // D[d][e] summed over the domain's rows of Omega; an expert whose main lies
@@ -1776,9 +1759,15 @@ __device__ uint32_t general_check(const Plan &p, int *misc, uint64_t *cmax, uint
   } else {
     wm = (uint64_t)p.W;
   }
-  if (bad) misc[16] = 1;
-  atomicMax(reinterpret_cast<unsigned *>(&misc[17]), cm);
-  atomicMax(reinterpret_cast<unsigned long long *>(misc + 18), (unsigned long long)wm);
+  // (one LDS atomic per wave: of every lane they serialise on one word)
+  cm = ~rows_min_u32(~cm, false);
+  wm = ~wave_min_u64(~wm);
+  const uint64_t any_bad = __ballot(bad);
+  if (lane_id() == 0) {
+    if (any_bad) misc[16] = 1;
+    atomicMax(reinterpret_cast<unsigned *>(&misc[17]), cm);
+    atomicMax(reinterpret_cast<unsigned long long *>(misc + 18), (unsigned long long)wm);
+  }
   lds_barrier();
   *cmax = (uint32_t)misc[17];
   *wmax = *reinterpret_cast<const unsigned long long *>(misc + 18);
@@ -1801,17 +1790,25 @@ __device__ GenCost general_tables(const Plan &p, int d, int *sm, const DomainLds
   }
   for (int e = tid; e < p.E; e += nt) wx[e] = p.We ? p.We[e] : p.W;
   lds_barrier();
-  for (int x = tid; x < G * G * R; x += nt) {
-    const int pair = x / R, s = x - pair * R, jb = pair / G, jt = pair - jb * G;
+  // one wave per pair: lane l ranks source s0 + l among all sources, whose
+  // differences come lane by lane from registers
+  const int lane = tid & 63, nw = nt >> 6;
+  for (int pair = uniform_i32(tid >> 6); pair < G * G; pair += nw) {
+    const int jb = pair / G, jt = pair - jb * G;
     if (jb == jt) continue;
     const int *cb = ccol + jb * R, *ct = ccol + jt * R;
-    const int ds = ct[s] - cb[s];
-    int rank = 0;
-    for (int s2 = 0; s2 < R; ++s2) {
-      const int d2 = ct[s2] - cb[s2];
-      rank += d2 < ds || (d2 == ds && s2 < s);
+    for (int s0 = 0; s0 < R; s0 += 64) {
+      const int s = s0 + lane, ds = s < R ? ct[s] - cb[s] : 0;
+      int rank = 0;
+      for (int t0 = 0; t0 < R; t0 += 64) {
+        const int t = t0 + lane, dt = t < R ? ct[t] - cb[t] : 0, nt2 = imin(64, R - t0);
+        for (int l = 0; l < nt2; ++l) {
+          const int d2 = readlane_i32(dt, l);
+          rank += d2 < ds || (d2 == ds && t0 + l < s) ? 1 : 0;
+        }
+      }
+      if (s < R) ord[pair * R + rank] = (uint16_t)s;
     }
-    ord[pair * R + rank] = (uint16_t)s;
   }
   lds_barrier();
   GenCost gc;
@@ -1819,6 +1816,22 @@ __device__ GenCost general_tables(const Plan &p, int d, int *sm, const DomainLds
   gc.ccol = ccol;
   gc.wx = wx;
   return gc;
+}
+
+// Send offsets of the one-launch plan (exclusive prefix of the send counts
+// sendl, total at [R]) by wave 0, for the caller and for the chunks.
+__device__ __forceinline__ void solver_send_offsets(const Plan &p, const int *sendl) {
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x, R = p.R;
+  const int per = (R + 63) / 64, lo = imin(R, lane * per), hi = imin(R, lo + per);
+  int sum = 0;
+  for (int r = lo; r < hi; ++r) sum += sendl[r];
+  int run = wave_incl_scan(sum) - sum;
+  for (int r = lo; r < hi; ++r) {
+    p.offs_out[r] = run;
+    run += sendl[r];
+  }
+  if (lane == 63) p.offs_out[R] = run;
 }
 
 // ---------------------------------------------------------------- solver: one workgroup per domain
@@ -1831,21 +1844,33 @@ __device__ GenCost general_tables(const Plan &p, int d, int *sm, const DomainLds
 // domain's instances, routing (Section 4.3), refinement (Eq. 10) and the
 // domain's outputs follow.  The last solver workgroup to finish (a ticket)
 // lists this rank's instances per expert for the reroute and writes the
-// final status.  NT: the most threads per workgroup (launch bounds): the
-// usual 512-thread launch gets twice the registers a 1024-thread one may use.
-template <int NT>
-__global__ __launch_bounds__(NT) void solve_kernel(Plan p0) {
-  extern __shared__ int64_t smem_s[];
-  int *sm = reinterpret_cast<int *>(smem_s);
-  if ((int)blockIdx.x >= p0.n_solvers) {
-    block_offsets(p0, blockIdx.x - p0.n_solvers, sm);
-    return;
-  }
-  const Plan p = solver_plan(p0);
+// final status.
+//
+// One (plan_domains_kernel, one domain per workgroup): row self and bad ids
+// come from the chunk workgroups of the same launch.  The workgroup of the
+// domain holding self makes its stage 1 from Omega as gathered, then waits
+// for the last chunk's verdict on row self and makes it again when that row
+// differs from the histogram; the grid barrier passes the verdict on.  The
+// last workgroup to finish releases the chunks.
+template <bool One>
+__device__ __forceinline__ void domain_solver(const Plan &p0, int *sm) {
+  const Plan p = solver_plan(role_plan(p0));
   DomainLds lay = domain_lds(p);
-  int *offs[] = {&lay.ck, &lay.fdt, &lay.hs, &lay.rows, &lay.mask, &lay.slots, &lay.used, &lay.L,
-                 &lay.e_of, &lay.U, &lay.misc, &lay.qcol, &lay.ord, &lay.ccol, &lay.wx};
-  for (int *o : offs) *o = vgpr(*o);
+  lay.ck = vgpr(lay.ck);
+  lay.fdt = vgpr(lay.fdt);
+  lay.hs = vgpr(lay.hs);
+  lay.rows = vgpr(lay.rows);
+  lay.mask = vgpr(lay.mask);
+  lay.slots = vgpr(lay.slots);
+  lay.used = vgpr(lay.used);
+  lay.L = vgpr(lay.L);
+  lay.e_of = vgpr(lay.e_of);
+  lay.U = vgpr(lay.U);
+  lay.misc = vgpr(lay.misc);
+  lay.qcol = vgpr(lay.qcol);
+  lay.ord = vgpr(lay.ord);
+  lay.ccol = vgpr(lay.ccol);
+  lay.wx = vgpr(lay.wx);
   uint64_t *ck = reinterpret_cast<uint64_t *>(sm + lay.ck);
   FastDiv *fdt = reinterpret_cast<FastDiv *>(sm + lay.fdt);
   int *hs = sm + lay.hs;
@@ -1865,10 +1890,27 @@ __global__ __launch_bounds__(NT) void solve_kernel(Plan p0) {
 
   if (wg == 0) STAMP(p, 0);
   if (tid < 16) misc[tid] = 0;
+  if constexpr (One) {
+    // the plan's generation (the last workgroup to finish advances it), the
+    // next plan's histogram buffer cleared (see fused_solver), row self as
+    // gathered
+    if (tid < 64) {
+      const uint32_t g = __hip_atomic_load(&p.ctrl[kCtrlGen], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (tid == 0) misc[kMiscGen] = (int)g;
+      if (wg == 0) {
+        uint32_t *other = p.ghist + ((g + 1u) & 1u) * (E + 1);
+        for (int e = tid; e <= E; e += 64)
+          __hip_atomic_store(other + e, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) p.status_out[0] = 0;   // chunks may OR SYNC into it
+      }
+    }
+    for (int e = tid; e < E; e += nt) hs[e] = p.gl[(int64_t)p.self * E + e];
+  }
   build_divisors(M, fdt);
   uint64_t cmax = (uint64_t)imax(p.cI, p.cX), wmax = (uint64_t)p.W;
+  uint32_t cst = 0;
   if (p.general) {
-    const uint32_t cst = general_check(p, misc, &cmax, &wmax);
+    cst = general_check(p, misc, &cmax, &wmax);
     if (tid == 0 && cst) atomicOr(reinterpret_cast<unsigned *>(&misc[0]), cst);
   }
   // ---- row self of Omega: the histogram of local_topk, from the offset
@@ -1877,54 +1919,98 @@ __global__ __launch_bounds__(NT) void solve_kernel(Plan p0) {
   // after the grid barrier (by then the helpers are done)
   const int dself = (int)fdiv((uint32_t)p.self, p.fG);
   const bool has_self = dself < M && dself % nwg == wg;
-  if (wg == 0)
+  if (!One && wg == 0)
     for (int b = tid; b < p.nb; b += nt)
       if (p.blk_err[b]) atomicOr(reinterpret_cast<unsigned *>(&misc[0]), TOPOEP_ST_BAD_ID);
+  bool waited = true;   // One: the wait for the verdict did not give up
+  // domains hosting each expert: the main's here, the stage-1 replicas' after
+  // the grid barrier (the words are this workgroup's own until then)
+  for (int e = tid; e < E; e += nt) {
+    const int dm = (int)fdiv((uint32_t)e, p.fGP);
+    for (int w = 0; w < p.MW; ++w) mask[e * p.MW + w] = w == (dm >> 5) ? 1u << (dm & 31) : 0u;
+  }
 
   // ---- inter-node placement (Eq. 9), each domain independently
   for (int d = wg; d < M; d += nwg) {
     const Plan p = solver_plan(role_plan(p0));   // (reloaded: see the domain loop below)
     copy_to_lds(rows, p.gl + (int64_t)d * G * E, G * E);
     if (wg == 0) STAMP(p, 14);
-    if (d == dself) row_self(p, hs, qcol, &misc[10]);
+    if (!One && d == dself) row_self(p, hs, qcol, &misc[10]);
     if (wg == 0) STAMP(p, 15);
-    if (tid == 0) misc[1] = 0;
-    lds_barrier();
-    scan_rows(p, d * G, (d + 1) * G, rows, hs, misc);
-    for (int e = tid; e < E; e += nt) {
-      if ((int)fdiv((uint32_t)e, p.fGP) == d) continue;   // main inside the domain
-      int D = 0;
+    for (int pass = 0;; ++pass) {
+      if (tid == 0) misc[1] = 0;
+      for (int c = tid; c < E; c += nt) qcol[E + c] = 0;   // the candidates' ranks
+      lds_barrier();
+      scan_rows(p, d * G, (d + 1) * G, rows, hs, misc);
+      for (int e = tid; e < E; e += nt) {
+        if ((int)fdiv((uint32_t)e, p.fGP) == d) continue;   // main inside the domain
+        int D = 0;
 #pragma unroll 8
-      for (int j = 0; j < G; ++j) {
-        const int s = d * G + j;
-        D += s == p.self ? hs[e] : rows[j * E + e];
-      }
-      const int64_t we = p.general && p.We ? p.We[e] : p.W;
-      if ((int64_t)2 * D * p.S > we) {
-        const int pos = atomicAdd(&misc[1], 1);
-        if (p.general) {
-          // sizes differ per expert: rank by the benefit itself (qcol is
-          // free until the routing and holds the experts)
-          ck[pos] = (uint64_t)((int64_t)2 * D * p.S - we);
-          qcol[pos] = e;
-        } else {
-          ck[pos] = cand_key(D, e);
+        for (int j = 0; j < G; ++j) {
+          const int s = d * G + j;
+          D += s == p.self ? hs[e] : rows[j * E + e];
+        }
+        const int64_t we = p.general && p.We ? p.We[e] : p.W;
+        if ((int64_t)2 * D * p.S > we) {
+          const int pos = atomicAdd(&misc[1], 1);
+          if (p.general) {
+            // sizes differ per expert: rank by the benefit itself (qcol is
+            // free until the routing and holds the experts)
+            ck[pos] = (uint64_t)((int64_t)2 * D * p.S - we);
+            qcol[pos] = e;
+          } else {
+            ck[pos] = cand_key(D, e);
+          }
         }
       }
+      lds_barrier();
+      if (wg == 0) STAMP(p, 16);
+      const int nc = misc[1];
+      if (wg == 0 && tid == 0) stamp_nc(nc);
+      if (p.general) rank_units<true>(nc, ck, qcol, qcol + E);
+      else rank_units<false>(nc, ck, nullptr, qcol + E);
+      lds_barrier();
+      // the first cap ranks name the domain's stage-1 replicas
+      for (int c = tid; c < nc; c += nt) {
+        const int rank = qcol[E + c];
+        if (rank < cap) p.repl1[(int64_t)d * cap + rank] = p.general ? qcol[c] : (int)(uint32_t)ck[c];
+      }
+      for (int i = imin(nc, cap) + tid; i < cap; i += nt) p.repl1[(int64_t)d * cap + i] = -1;
+      lds_barrier();
+      if (!One || d != dself || pass > 0) break;
+      if (tid == 0) {
+        const uint32_t want = ((uint32_t)misc[kMiscGen] + 1u) & 0x3FFFFFFFu;
+        uint32_t v = 0;
+        int ok = 0;
+        for (uint32_t it = 0; it < p.spin_limit; ++it) {
+          if (it > 0) __builtin_amdgcn_s_sleep(1);
+          v = __hip_atomic_load(&p.ctrl[kCtrlVerdict], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if ((v >> 2) == want) {
+            ok = 1;
+            break;
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        misc[2] = ok;
+        misc[3] = (int)(v & 3u);
+      }
+      __syncthreads();
+      waited = misc[2] != 0;
+      if (!waited || (uint32_t)misc[3] == kVerdictSame) break;
+      // row self := the histogram, and the stage again (its replicas' stores
+      // above complete before they are stored again)
+      drain_then_barrier();
+      const uint32_t *gh = p.ghist + (misc[kMiscGen] & 1) * (E + 1);
+      for (int e = tid; e < E; e += nt) hs[e] = (int)gh[e];
+      if (tid == 0) {
+        misc[0] = (int)(cst | (gh[E] ? TOPOEP_ST_BAD_ID : 0u));
+        misc[8] = misc[9] = 0;
+      }
     }
-    lds_barrier();
-    if (wg == 0) STAMP(p, 16);
-    const int nc = misc[1];
-    if (wg == 0 && tid == 0) stamp_nc(nc);
-    for (int c = tid; c < nc; c += nt) {
-      if (p.general) rank_candidates_b(c, nc, cap, ck, qcol, p.repl1 + (int64_t)d * cap);
-      else rank_candidates(c, nc, cap, ck, p.repl1 + (int64_t)d * cap);
-    }
-    for (int i = imin(nc, cap) + tid; i < cap; i += nt) p.repl1[(int64_t)d * cap + i] = -1;
-    lds_barrier();
   }
   if (tid == 0) {
-    if (misc[0]) atomicOr(&p.ctrl[kCtrlStatus], (uint32_t)misc[0]);
+    const uint32_t st = (uint32_t)misc[0] | (waited ? 0u : TOPOEP_ST_SYNC);
+    if (st) atomicOr(&p.ctrl[kCtrlStatus], st);
     const unsigned long long t = *reinterpret_cast<unsigned long long *>(misc + 8);
     if (t) atomicAdd(reinterpret_cast<unsigned long long *>(p.ctrl + kCtrlTotal), t);
   }
@@ -1933,38 +2019,124 @@ __global__ __launch_bounds__(NT) void solve_kernel(Plan p0) {
   if (wg == 0) STAMP(p, 1);
   const bool synced = grid_barrier(&p.ctrl[kCtrlBar], (uint32_t)nwg, p.spin_limit, &misc[2]);
   if (wg == 0) STAMP(p, 2);
+  // every domain's replicas on their way with the status words
+  int rv[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) rv[u] = tid + u * nt < M * cap ? p.repl1[tid + u * nt] : 0;
   uint32_t gst = __hip_atomic_load(&p.ctrl[kCtrlStatus], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint64_t total = __hip_atomic_load(reinterpret_cast<unsigned long long *>(p.ctrl + kCtrlTotal),
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (out_of_range_cw(p, total, cmax, wmax)) gst |= TOPOEP_ST_RANGE;
   if (!synced) gst |= TOPOEP_ST_SYNC;
-  const bool noplan = (gst & kNoPlan) != 0 || !synced;
+  const bool noplan = (gst & (kNoPlan | TOPOEP_ST_SYNC)) != 0;
 
-  if (!has_self && !noplan) row_self(p, hs, qcol, &misc[10]);
+  if constexpr (One) {
+    const uint32_t v = __hip_atomic_load(&p.ctrl[kCtrlVerdict], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!has_self && !noplan && (v & 3u) == kVerdictRedo) {
+      const uint32_t *gh = p.ghist + (misc[kMiscGen] & 1) * (E + 1);
+      for (int e = tid; e < E; e += nt) hs[e] = (int)gh[e];   // (a barrier follows before any is read)
+    }
+  } else {
+    if (!has_self && !noplan) row_self(p, hs, qcol, &misc[10]);
+  }
 
   // ---- domains hosting each expert: the main's domain plus stage-1 replicas
   const bool one_domain = M <= nwg;
+  bool empty = false;   // an empty entry: a rank of that domain has a free slot
   if (!noplan) {
-    for (int i = tid; i < E * p.MW; i += nt) mask[i] = 0;
-    __syncthreads();
-    for (int e = tid; e < E; e += nt) {
-      const int dm = (int)fdiv((uint32_t)e, p.fGP);
-      atomicOr(&mask[e * p.MW + (dm >> 5)], 1u << (dm & 31));
-    }
-    for (int i = tid; i < M * cap; i += nt) {
-      const int e = p.repl1[i];
+    auto host = [&](int i, int e) {
       const int dd = (int)fdiv((uint32_t)i, p.fCap);
       // a workgroup of one domain keeps that domain's list (rows is free
       // after stage 1: cap = G Neff <= G E words)
       if (one_domain && dd == wg) rows[i - dd * cap] = e;
       if ((unsigned)e < (unsigned)E) atomicOr(&mask[e * p.MW + (dd >> 5)], 1u << (dd & 31));
-    }
+      else empty = true;
+    };
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (tid + u * nt < M * cap) host(tid + u * nt, rv[u]);
+    for (int i = tid + 2 * nt; i < M * cap; i += nt) host(i, p.repl1[i]);
   }
-  __syncthreads();
+  // No domain can refine (every slot taken by stage 1, or one rank per
+  // domain): the routing rule alone gives this rank's shares (see
+  // fast_finish), and every workgroup writes its own domains' part of the
+  // instance list, which otherwise waits for the last one.
+  // (One only: the three-kernel solver has no registers left for it.)
+  bool lean = false;
+  if constexpr (One) lean = __syncthreads_or(empty) == 0 || G < 2;
+  else __syncthreads();
   if (wg == 0) STAMP(p, 3);
 
   uint32_t flags = 0;
-  for (int d = wg; d < M; d += nwg) {
+  if (lean && !noplan) {
+    const int ds = dself;
+    int *first = qcol;   // E + 1: each expert's first entry
+    for (int e = tid; e < E; e += nt) {
+      const uint32_t *me = mask + e * p.MW;
+      const int w = hs[e];
+      int n = 0;
+      for (int wd = 0; wd < p.MW; ++wd) n += __popc(me[wd]);
+      first[e] = w <= 0 ? 0 : (((me[ds >> 5] >> (ds & 31)) & 1u) ? 1 : imin(n, w));
+    }
+    lds_barrier();
+    const int all = block_excl_scan(first, E, qcol + E + 2);
+    if (wg == 0) {
+      for (int e = tid; e < E; e += nt) p.csr_ptr[e] = first[e];
+      if (tid == 0) p.csr_ptr[E] = all;
+    }
+    for (int d = wg; d < M; d += nwg) {
+      for (int j = tid; j < G; j += nt) Lr[j] = 0;   // the ranks' send counts
+      lds_barrier();
+      for (int a = tid; a < I; a += nt) {
+        const int j = (int)fdiv((uint32_t)a, p.fPN), pos = a - j * PN, r = d * G + j;
+        int e = r * P + pos;
+        if (pos >= P) {
+          // stage-1 entry t G + j sits in slot t of local rank j
+          const int c = (pos - P) * G + j;
+          e = one_domain ? rows[c] : p.repl1[(int64_t)d * cap + c];
+          p.slots_out[(int64_t)r * p.N + pos - P] = e;
+        }
+        e_of[a] = e;
+        const int w = e >= 0 ? hs[e] : 0;
+        if (w <= 0) continue;
+        const uint32_t *me = mask + e * p.MW;
+        int i = 0, q = w, end = w;
+        if ((me[ds >> 5] >> (ds & 31)) & 1u) {
+          if (d != ds) continue;   // all of w to the instance in dom(self)
+        } else {
+          int n = 0;
+          for (int wd = 0; wd < p.MW; ++wd) {
+            const uint32_t bits = me[wd];
+            n += __popc(bits);
+            const int lo = wd * 32;
+            if (d >= lo + 32) i += __popc(bits);
+            else if (d > lo) i += __popc(bits & ((1u << (d - lo)) - 1u));
+          }
+          const FastDiv fn = fdt[n];
+          const int qq = (int)fdiv_hi((uint32_t)w, fn), rem = w - qq * n;
+          q = qq + (i < rem ? 1 : 0);
+          if (q <= 0) continue;
+          end = (i + 1) * qq + imin(i + 1, rem);
+        }
+        p.csr_r[first[e] + i] = r;
+        p.csr_end[first[e] + i] = end;
+        atomicAdd(&Lr[j], q);
+      }
+      // slots beyond the experts a rank does not hold stay empty
+      for (int i = tid; i < G * (p.N - Neff); i += nt) {
+        const int j = i % G, t = Neff + i / G;
+        p.slots_out[(int64_t)(d * G + j) * p.N + t] = -1;
+      }
+      lds_barrier();
+      for (int j = tid; j < G; j += nt) p.send_out[d * G + j] = Lr[j];
+      if (p.recv_out && d == ds)
+        write_recv_counts(p, (p.self - d * G) * PN, e_of, nullptr, false, mask, fdt,
+                          [&](int s, int e) { return s == p.self ? hs[e] : p.gl[(int64_t)s * E + e]; },
+                          reinterpret_cast<int *>(ck));
+      lds_barrier();
+    }
+  }
+  for (int d = wg; d < M && !(lean && !noplan); d += nwg) {
     // the plan's fields load again in every iteration (see role_plan): the
     // loop usually runs once, and invariants hoisted out of it would only
     // crowd the scalar registers
@@ -2100,6 +2272,7 @@ __global__ __launch_bounds__(NT) void solve_kernel(Plan p0) {
   __syncthreads();
   if (!misc[4]) return;
   STAMP(p, 10);
+  if (!lean || noplan) {
   int *cnt = qcol;                                            // E + 1
   uint32_t *bm = reinterpret_cast<uint32_t *>(qcol + E + 2);  // E * RW
   int *tmp = qcol + E + 2 + E * p.RW;                         // scan scratch (64)
@@ -2160,13 +2333,15 @@ __global__ __launch_bounds__(NT) void solve_kernel(Plan p0) {
   STAMP(p, 12);
   for (int j = tid; j < cnt[E]; j += nt) p.csr_end[j] = cv[j];
   __syncthreads();
+  }
   STAMP(p, 13);
   STAMP_FLUSH(p, 10, 14);
   if (tid == 0) {
     uint32_t fin = __hip_atomic_load(&p.ctrl[kCtrlStatus], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     fin |= gst & TOPOEP_ST_RANGE;
     p.ctrl[kCtrlFinal] = fin;
-    p.status_out[0] = (int32_t)fin;
+    if (One) atomicOr(reinterpret_cast<unsigned *>(p.status_out), fin);
+    else p.status_out[0] = (int32_t)fin;
     p.status_out[1] = (fin & (kNoPlan | TOPOEP_ST_SYNC))
                           ? 0
                           : (int32_t)__hip_atomic_load(&p.ctrl[kCtrlMoves], __ATOMIC_RELAXED,
@@ -2180,8 +2355,39 @@ __global__ __launch_bounds__(NT) void solve_kernel(Plan p0) {
     p.ctrl[kCtrlStatus] = 0;
     p.ctrl[kCtrlMoves] = 0;
     *reinterpret_cast<unsigned long long *>(p.ctrl + kCtrlTotal) = 0ull;
-    __hip_atomic_fetch_sub(&p.ctrl[kCtrlHelpers], (uint32_t)p.n_helpers, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!One)
+      __hip_atomic_fetch_sub(&p.ctrl[kCtrlHelpers], (uint32_t)p.n_helpers, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
   }
+  if constexpr (One) {
+    if (p.offs_out && !noplan) {
+      for (int r = tid; r < R; r += nt) hs[r] = p.send_out[r];   // (hs: E >= R words, no longer needed)
+      lds_barrier();
+      solver_send_offsets(p, hs);
+    }
+    // the instance list, the final status and the send offsets, then the
+    // chunks' flags and the next generation
+    drain_then_barrier();
+    if (tid < 64) {
+      const uint32_t next = (uint32_t)misc[kMiscGen] + 1u;
+      for (int b = tid; b < p.nb; b += 64)
+        __hip_atomic_store(p.flags + (int64_t)b * kFlagStride, next, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      if (tid == 0) __hip_atomic_store(&p.ctrl[kCtrlGen], next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
+// NT: the most threads per workgroup (launch bounds): the usual 512-thread
+// launch gets twice the registers a 1024-thread one may use.
+template <int NT>
+__global__ __launch_bounds__(NT) void solve_kernel(Plan p0) {
+  extern __shared__ int64_t smem_s[];
+  int *sm = reinterpret_cast<int *>(smem_s);
+  if ((int)blockIdx.x >= p0.n_solvers) {
+    block_offsets(p0, blockIdx.x - p0.n_solvers, sm);
+    return;
+  }
+  domain_solver<false>(p0, sm);
 }
 
 // ---------------------------------------------------------------- solver: one workgroup for every domain
@@ -2619,22 +2825,6 @@ __device__ __forceinline__ void single_recv_counts(const Plan &p, const SingleSt
   // (hs, the histogram, is no longer needed: it is the scratch)
   write_recv_counts(p, ds * p.I + (p.self - ds * p.G) * p.PN, t.e_of, t.qcol, t.dfree[ds] != 0, t.mask, t.fdt,
                     [&](int s, int e) { return om[s * E + e]; }, t.hs);
-}
-
-// Send offsets of the one-launch plan (exclusive prefix of the send counts
-// sendl, total at [R]) by wave 0, for the caller and for the chunks.
-__device__ __forceinline__ void solver_send_offsets(const Plan &p, const int *sendl) {
-  if (threadIdx.x >= 64) return;
-  const int lane = threadIdx.x, R = p.R;
-  const int per = (R + 63) / 64, lo = imin(R, lane * per), hi = imin(R, lo + per);
-  int sum = 0;
-  for (int r = lo; r < hi; ++r) sum += sendl[r];
-  int run = wave_incl_scan(sum) - sum;
-  for (int r = lo; r < hi; ++r) {
-    p.offs_out[r] = run;
-    run += sendl[r];
-  }
-  if (lane == 63) p.offs_out[R] = run;
 }
 
 // Omega to LDS with its status bits and total load (row self included as
@@ -3405,7 +3595,7 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
     const bool inr = idx < hi;
     const bool valid = (unsigned)ev[i] < (unsigned)E;   // (ev is -1 past the end)
     bad |= (inr && !valid) ? 1 : 0;
-    lr[i] = wave_rank(ev[i], valid, p.nbits, mywc);
+    if (valid) atomicAdd(&mywc[ev[i]], 1);
   }
   bad = __syncthreads_or(bad);
   // publish the chunk's counts; wc becomes each wave's offset in the chunk
@@ -3451,18 +3641,22 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
     STAMP_FLUSH(p, 13, 14);
     STAMP_FLUSH(p, 19, 20);
   }
+  // the ids' occurrence indices in the chunk (each wave counts on from its
+  // offset, in its own row), while the other chunks arrive
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) lr[i] = wave_rank(ev[i], (unsigned)ev[i] < (unsigned)E, p.nbits, mywc);
   // every count is written: this chunk's first occurrence index per expert
   bool ok = wait_flag(p, b, 1, gen + 1u, flag);
   if (ok) chunk_offsets(p, b, p.ghist + (gen & 1u) * (E + 1), run, gs);
   if (b == 0) STAMP(p, 16);
-  // each id's occurrence index rho = chunk offset + wave offset + rank in
-  // the wave, while the plan is still being made
+  // each id's occurrence index rho = chunk offset + index in the chunk,
+  // while the plan is still being made
   __syncthreads();
   int rho[IPT];
 #pragma unroll
   for (int i = 0; i < IPT; ++i) {
     const int e = (unsigned)ev[i] < (unsigned)E ? ev[i] : 0;
-    rho[i] = run[e] + wc[wave * E + e] + lr[i];
+    rho[i] = run[e] + lr[i];
   }
   // the plan is ready
   ok = ok && wait_flag(p, b, 0, gen + 1u, flag);
@@ -3512,7 +3706,18 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
     if (idx < hi) {
       if ((unsigned)ev[i] < (unsigned)E) {
         const int j1 = ptr[ev[i] + 1];
-        for (int j = ptr[ev[i]]; j < j1; ++j) {
+        int j = ptr[ev[i]];
+        // (shares ascend: halve a long list down to four entries first)
+        for (int len = j1 - j; len > 4;) {
+          const int half = len >> 1;
+          if (ent[j + half - 1].x <= rho[i]) {
+            j += half;
+            len -= half;
+          } else {
+            len = half;
+          }
+        }
+        for (; j < j1; ++j) {
           const int2 en = ent[j];
           if (rho[i] < en.x) {
             dest = en.y;
@@ -3552,6 +3757,24 @@ __global__ __launch_bounds__(1024) void plan_fused_kernel(Plan p) {
   }
 }
 
+// The per-domain solver and the chunks in one launch: workgroups 0 ..
+// n_solvers - 1 solve one domain each, the nb after them hold the ids.  All
+// are resident at once (kMaxOneGroups) and every wait is bounded.  Bound:
+// latency.  A Stress-like layer (R = 256, E = 512, 131 072 ids) takes 21 us,
+// three kernels 32 (4.8 + 19.3 + 8.2 and their boundaries); a Qwen3-like one
+// under a general cost model 23, three kernels 33.
+template <int IPT>
+__global__ __launch_bounds__(512) void plan_domains_kernel(Plan p) {
+  extern __shared__ int64_t smem_d[];
+  int *sm = reinterpret_cast<int *>(smem_d);
+  if ((int)blockIdx.x < p.n_solvers) {
+    domain_solver<true>(p, sm);
+  } else {
+    const Plan q = role_plan(p);
+    fused_chunk<IPT>(q, blockIdx.x - q.n_solvers, sm);
+  }
+}
+
 // Same launch shape, empty body: the launch floor of a plan's kernel.
 __global__ __launch_bounds__(1024) void empty_kernel(Plan p) { (void)p; }
 
@@ -3563,6 +3786,11 @@ struct Shape {
   int mode;       // 1 single-workgroup solver, 2 per-domain solver (three kernels each), 3 one launch
   size_t lds_hist, lds_solve, lds_reroute, lds_fused;
   int solve_groups;
+  // a plan with the per-domain solver that runs as one launch
+  // (plan_domains_kernel): chunk workgroups (0: three kernels), ids per
+  // thread, LDS
+  int one_nb, one_ipt;
+  size_t lds_one;
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -3621,11 +3849,12 @@ int resident_capacity(const void *fn, int threads, size_t lds) {
 }
 
 const void *fused_fn(int ipt, int form);
+const void *domains_fn(int ipt);
 
 // Validate the arguments and fill the plan's sizes, launch shape and
 // workspace layout (pointers are offsets when ws == nullptr).
 int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoep_launch *lc, Plan *p,
-          Shape *sh, size_t *ws_bytes, char *ws, bool general = false) {
+          Shape *sh, size_t *ws_bytes, char *ws, bool general = false, size_t max_ws = SIZE_MAX) {
   if (!t) return TOPOEP_EINVAL;
   const int R = t->num_ranks, G = t->ranks_per_node, E = t->num_experts;
   if (R <= 0 || G <= 0 || E <= 0 || R % G != 0 || E % R != 0) return TOPOEP_EINVAL;
@@ -3688,6 +3917,8 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
   q.fMI = make_fastdiv((uint32_t)(q.M * q.I));
 
   Shape s;
+  s.one_nb = s.one_ipt = 0;
+  s.lds_one = 0;
   const int ipt_req = lc ? lc->items_per_thread : 0;
   s.ipt = ipt_req ? ipt_req : (q.n >= ((int64_t)1 << 24) ? 8 : 4);
   s.bt = lc && lc->block_threads ? lc->block_threads : 256;
@@ -3808,6 +4039,25 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
                                                      s.st, s.lds_solve))
     return TOPOEP_ELIMIT;
   s.solve_groups = q.n_solvers + q.n_helpers;
+  // The whole plan in one launch when one workgroup per domain and the
+  // chunks' workgroups together fill at most a quarter of the device: they
+  // wait on each other, and so up to four such plans on four hardware queues
+  // are resident together.  Two ids per thread while that keeps to 32
+  // chunks, else eight.
+  if (max_ws != kThreeOnly && s.mode == 2 && solver == 0 && !given && !(lc && lc->solve_threads) && q.n_solvers == q.M) {
+    for (int ipt = 2; ipt <= 8 && s.one_nb == 0; ipt *= 4) {
+      const int64_t per = (int64_t)kOneThreads * ipt;
+      const int64_t nbo = q.n > 0 ? (q.n + per - 1) / per : 1;
+      const int64_t chunk_words = (int64_t)chunk_lds(q, kOneThreads).words;
+      const int64_t words = multi_words > chunk_words ? multi_words : chunk_words;
+      if (nbo > kFusedBlocks && ipt < 8) continue;
+      if (words * 4 + 1024 > kLdsLimit || q.n_solvers + nbo > kMaxOneGroups) continue;
+      if (4 * (q.n_solvers + nbo) > resident_capacity(domains_fn(ipt), kOneThreads, (size_t)words * 4)) continue;
+      s.one_nb = (int)nbo;
+      s.one_ipt = ipt;
+      s.lds_one = (size_t)words * 4;
+    }
+  }
   s.lds_hist = (size_t)E * 4 * (s.bt / 64);
   s.lds_reroute = lds_reroute(s.bt);
   s.lds_fused = 0;
@@ -3833,14 +4083,20 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
     off = align256(off + bytes);
     return o;
   };
-  // every word a plan needs zero before its first use sits in the prefix
-  // [0, zero_bytes): the control words, then (one launch) the ready flags
+  // Every word a plan needs zero before its first use sits in the prefix
+  // [0, zero_bytes): the control words, then (one launch) the ready flags and
+  // the histogram buffers.  A plan with the per-domain solver that runs as
+  // one launch also keeps the three-kernel plan's buffers (its stages run
+  // alone too), and runs as three kernels in a workspace without room for
+  // both (max_ws).
   const bool one = s.mode == 3;
   const bool three = !one;
+  const int chunks = one ? q.nb : s.one_nb;   // one launch: chunk workgroups
   const size_t o_ctrl = take(kCtrlBytes);
-  const size_t o_flg = take(one ? (size_t)q.nb * kFlagStride * 4 : 0);
-  const size_t o_gh = take(one ? (size_t)2 * (E + 1) * 4 : 0);
+  const size_t o_flg = take((size_t)chunks * kFlagStride * 4);
+  const size_t o_gh = take(chunks ? (size_t)2 * (E + 1) * 4 : 0);
   s.zero_bytes = off;
+  const size_t o_pub = take((size_t)chunks * E * 2);
   const size_t o_part = take(three ? (size_t)ws_rows * E * 4 : 0);
   const size_t o_offs = take(three ? (size_t)ws_rows * E * 4 : 0);
   const size_t o_berr = take(three ? (size_t)ws_rows * 4 : 0);
@@ -3851,7 +4107,8 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
   const size_t o_cr = take((size_t)q.nent_cap * 4);
   const size_t o_ce = take((size_t)q.nent_cap * 4);
   const size_t o_ht = take(three ? (size_t)E * 4 : 0);
-  const size_t o_pub = take(one ? (size_t)q.nb * E * 2 : 0);
+  if (s.one_nb > 0 && off > max_ws)   // no room for one launch: three kernels
+    return setup(t, T, k, N, lc, p, sh, ws_bytes, ws, general, kThreeOnly);
   *ws_bytes = off;
   if (ws) {
     auto at = [&](size_t o, bool have) { return have ? reinterpret_cast<int32_t *>(ws + o) : nullptr; };
@@ -3867,9 +4124,9 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
     q.csr_r = at(o_cr, true);
     q.csr_end = at(o_ce, true);
     q.htot = at(o_ht, three);
-    q.flags = atu(o_flg, one);
-    q.pub = one ? reinterpret_cast<uint16_t *>(ws + o_pub) : nullptr;
-    q.ghist = atu(o_gh, one);
+    q.flags = atu(o_flg, chunks > 0);
+    q.pub = chunks > 0 ? reinterpret_cast<uint16_t *>(ws + o_pub) : nullptr;
+    q.ghist = atu(o_gh, chunks > 0);
   }
   *p = q;
   *sh = s;
@@ -3894,8 +4151,15 @@ const void *fused_fn(int ipt, int form) {
   }
 }
 
+const void *domains_fn(int ipt) {
+  return ipt == 2 ? reinterpret_cast<const void *>(plan_domains_kernel<2>)
+                  : reinterpret_cast<const void *>(plan_domains_kernel<8>);
+}
+
 void set_attrs() {
   if (g_attrs_set) return;
+  allow_lds(plan_domains_kernel<2>);
+  allow_lds(plan_domains_kernel<8>);
   allow_lds(hist_kernel<1>);
   allow_lds(hist_kernel<2>);
   allow_lds(reroute_kernel<1, false>);
@@ -3966,7 +4230,18 @@ void launch_fused(const Plan &p, const Shape &s, hipStream_t st) {
   }
 }
 
-// Kernels of one plan in launch order: grid, threads, dynamic LDS.
+// The one-launch plan with the per-domain solver: p's chunks are this
+// launch's.
+void launch_domains(Plan p, const Shape &s, hipStream_t st) {
+  p.nb = s.one_nb;
+  p.chunk = (int64_t)kOneThreads * s.one_ipt;
+  const dim3 g(p.n_solvers + p.nb), b(kOneThreads);
+  if (s.one_ipt == 2) hipLaunchKernelGGL(plan_domains_kernel<2>, g, b, s.lds_one, st, p);
+  else hipLaunchKernelGGL(plan_domains_kernel<8>, g, b, s.lds_one, st, p);
+}
+
+// Kernels of one plan in launch order: grid, threads, dynamic LDS (with the
+// per-domain solver its three stages', also where the plan is one launch).
 int plan_kernels(const Plan &p, const Shape &s, int grid[3], int block[3], size_t lds[3]) {
   if (s.mode == 3) {
     grid[0] = p.nb + 1;
@@ -3998,13 +4273,13 @@ int enqueue(int stage_mask, const topoep_topology *topo, const int32_t *global_l
   Shape s;
   size_t need = 0;
   const bool general = costs != nullptr;
-  int rc = setup(topo, T, k, N, launch, &p, &s, &need, nullptr, general);
+  int rc = setup(topo, T, k, N, launch, &p, &s, &need, nullptr, general, workspace_bytes);
   if (rc != TOPOEP_OK) return rc;
   if (!global_load || !send_counts || !status || !workspace) return TOPOEP_EINVAL;
   if ((int64_t)topo->num_ranks * N > 0 && !replica_slots) return TOPOEP_EINVAL;
   if (T > 0 && (!local_topk || !token_dest)) return TOPOEP_EINVAL;
   if (workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255)) return TOPOEP_EWORKSPACE;
-  rc = setup(topo, T, k, N, launch, &p, &s, &need, static_cast<char *>(workspace), general);
+  rc = setup(topo, T, k, N, launch, &p, &s, &need, static_cast<char *>(workspace), general, workspace_bytes);
   if (rc != TOPOEP_OK) return rc;
   p.Cm = general ? costs->cost : nullptr;
   p.We = general ? costs->expert_bytes : nullptr;
@@ -4028,6 +4303,8 @@ int enqueue(int stage_mask, const topoep_topology *topo, const int32_t *global_l
   } else if (s.mode == 3) {
     if (stage_mask != 7 && stage_mask != 1) return TOPOEP_EINVAL;   // one kernel: the plan, or stage 0
     launch_fused(p, s, st);
+  } else if (s.one_nb > 0 && stage_mask == 7) {
+    launch_domains(p, s, st);
   } else {
     if (stage_mask & 1) launch_hist(p, s, st);
     if (stage_mask & 2) launch_solve(p, s, st);
@@ -4088,7 +4365,7 @@ int topoep_plan_noalloc(const topoep_topology *topo, const int32_t *global_load,
   Plan p;
   Shape s;
   size_t need = 0;
-  int rc = setup(topo, T, k, replica_budget, nullptr, &p, &s, &need, nullptr);
+  int rc = setup(topo, T, k, replica_budget, nullptr, &p, &s, &need, nullptr, false, kScratchBytes);
   if (rc != TOPOEP_OK) return rc;
   // the argument checks of topoep_plan, before anything is enqueued
   if (!global_load || !send_counts || !status) return TOPOEP_EINVAL;

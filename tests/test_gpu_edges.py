@@ -75,3 +75,130 @@ def test_large_batch_unaligned(offset):
     assert_same(got, ref_plan(*args), "unaligned by %d" % offset)
     rest = torch.cat([dest[:offset], dest[offset + tk.size:]])
     assert bool((rest == -9).all())
+
+
+def _domain_case(name, seed=3):
+    """Plans that run the per-domain solver and the chunks as one launch by
+    default: a large group (Stress-like) and many experts over a few nodes."""
+    if name == "stress":
+        return _zipf_case(256, 8, 512, 4, 131072, 8, seed)
+    if name == "experts":
+        return _zipf_case(32, 8, 1024, 2, 20000, 4, seed)
+    if name == "refine":
+        return _zipf_case(64, 8, 512, 4, 3001, 1, seed, W=1 << 20)
+    if name == "empty":
+        R, G, E, s, cI, cX, S, W, N, omega, _ = _zipf_case(256, 8, 512, 4, 64, 8, seed)
+        omega[s] = 0
+        return R, G, E, s, cI, cX, S, W, N, omega, np.zeros((0, 8), np.int32)
+    return _zipf_case(256, 8, 512, 4, int(name), 1, seed)
+
+
+DOMAIN_CASES = ["stress", "experts", "refine", "empty", "1", "1023", "1024", "1025", "32768", "32769", "131073"]
+
+
+@pytest.mark.parametrize("name", DOMAIN_CASES)
+def test_per_domain_one_launch(name):
+    """The default launch against the oracle and against the three kernels of
+    solver 2, at the edges of the chunks (2 and 8 ids per thread) and just
+    beyond the most ids that one launch takes; then with a row self that is
+    not the histogram (stage 1 again), a bad id and a refused Omega."""
+    args = _domain_case(name)
+    got, _ = both(*args, what="per-domain one launch %s" % name)
+    three, _ = both(*args, launch=SOLVERS["perdomain"], what="three kernels %s" % name)
+    for k in got:
+        assert np.array_equal(got[k], three[k]), k
+    R, G, E, s, cI, cX, S, W, N, omega, tk = args
+    other = omega.copy()
+    other[s] = np.roll(omega[s], 7) * 2 + 1
+    both(R, G, E, s, cI, cX, S, W, N, other, tk, what="row self differs %s" % name)
+    other = omega.copy()
+    other[s, 1] = -3
+    both(R, G, E, s, cI, cX, S, W, N, other, tk, what="negative in row self %s" % name)
+    other = omega.copy()
+    other[(s + 1) % R, 1] = -3
+    both(R, G, E, s, cI, cX, S, W, N, other, tk, what="negative elsewhere %s" % name)
+    if tk.size:
+        bad = tk.copy()
+        bad[-1, -1] = E
+        both(R, G, E, s, cI, cX, S, W, N, omega, bad, what="bad id %s" % name)
+
+
+@pytest.mark.parametrize("name", ["stress", "refine"])
+def test_per_domain_one_launch_reuse(name):
+    """One workspace, plan after plan: other inputs, a plan whose every wait
+    gives up (SYNC), the stages run alone in between, HIP graph replays."""
+    from test_gpu_parity import DEV, assert_same, ref_plan, topoep
+    a, b = _domain_case(name, 3), _domain_case(name, 4)
+    R, G, E, s, cI, cX, S, W, N, _, tk = a
+    b = (R, G, E, s) + b[4:9] + (b[9].copy(), b[10])
+    b[9][s] = np.bincount(b[10].ravel(), minlength=E)
+    other = b[9].copy()
+    other[s] = np.roll(other[s], 5)
+    c = b[:9] + (other, b[10])
+    p = topoep.Planner(topoep.topology(R, G, E, s, cI, cX, S, W), tk.shape[0], tk.shape[1], N, device=DEV)
+    dev = [(torch.from_numpy(x[9]).to(DEV), torch.from_numpy(x[10]).to(DEV)) for x in (a, b, c)]
+    refs = [ref_plan(*x) for x in (a, b, c)]
+
+    def check(i, what):
+        torch.cuda.synchronize()
+        assert_same(dict(replica_slots=p.replica_slots.cpu().numpy(), token_dest=p.token_dest.cpu().numpy(),
+                         send_counts=p.send_counts.cpu().numpy(), status=int(p.status[0]),
+                         move_count=int(p.status[1])), refs[i], what)
+
+    for rnd in range(3):
+        for i in (0, 1, 2, 1):
+            p.token_dest.fill_(-9)
+            p.plan(*dev[i])
+            check(i, "%s round %d input %d" % (name, rnd, i))
+        p.plan(*dev[2], launch=(0, 0, 0, 0, 0, -1, 0))
+        torch.cuda.synchronize()
+        assert int(p.status[0]) & topoep.ST_SYNC and bool((p.token_dest == -1).all())
+        p.plan(*dev[0])
+        check(0, "%s after SYNC, round %d" % (name, rnd))
+        for stage in range(3):
+            p.stage(stage, *dev[1])
+        check(1, "%s stages, round %d" % (name, rnd))
+        p.plan(*dev[2])
+        check(2, "%s after stages, round %d" % (name, rnd))
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        with torch.cuda.graph(graph, stream=stream):
+            p.plan(*dev[0])
+    torch.cuda.current_stream().wait_stream(stream)
+    for i in range(4):
+        p.token_dest.fill_(-9)
+        graph.replay()
+        check(0, "%s replay %d" % (name, i))
+        p.plan(*dev[1 + i % 2])
+        check(1 + i % 2, "%s eager after replay %d" % (name, i))
+
+
+def test_per_domain_three_kernel_workspace():
+    """A workspace of the three-kernel plan's size: the same plan, as three
+    kernels."""
+    from test_gpu_parity import DEV, assert_same, ref_plan, topoep
+    args = _domain_case("refine")
+    R, G, E, s, cI, cX, S, W, N, omega, tk = args
+    topo = topoep.topology(R, G, E, s, cI, cX, S, W)
+    p = topoep.Planner(topo, tk.shape[0], tk.shape[1], N, device=DEV)
+    three = topoep.workspace_bytes(topo, tk.shape[0], tk.shape[1], N, launch=SOLVERS["perdomain"])
+    assert three < p.ws_bytes
+    p.ws_bytes = three
+    p.workspace_view().zero_()
+    p.plan(torch.from_numpy(omega).to(DEV), torch.from_numpy(tk).to(DEV))
+    torch.cuda.synchronize()
+    assert_same(dict(replica_slots=p.replica_slots.cpu().numpy(), token_dest=p.token_dest.cpu().numpy(),
+                     send_counts=p.send_counts.cpu().numpy(), status=int(p.status[0]), move_count=int(p.status[1])),
+                ref_plan(*args), "three-kernel workspace")
+    p.ws_bytes = three - 256
+    with pytest.raises(topoep.TopoepError):
+        p.plan(torch.from_numpy(omega).to(DEV), torch.from_numpy(tk).to(DEV))
+
+
+@pytest.mark.parametrize("name", ["stress", "experts", "refine", "empty", "1025"])
+def test_per_domain_one_launch_dispatch(name):
+    """Receive counts, send offsets and slots of the one-launch plan."""
+    from test_gpu_dispatch import check
+    check(_domain_case(name), "per-domain one launch %s" % name)

@@ -129,6 +129,7 @@ struct Plan {
   const int32_t *Cm;   // general cost matrix [R, R] (with general), else null
   const int64_t *We;   // ||W_e|| per expert [E] (with general), else null
   int general;         // the full model of Section 4.1 (per-domain solver only)
+  int lanes;           // the refinement's lane forms: LDS holds position words
   int32_t *slot_out;   // send-buffer slot of every assignment [n], or null
   int32_t *offs_out;   // send offsets [R + 1] (given with slot_out)
   uint32_t *ctrl;
@@ -277,7 +278,8 @@ struct GenCost {
 __host__ __device__ inline DomainLds domain_lds(const Plan &p) {
   DomainLds l;
   int o = 0;
-  l.ck = o;    o += 2 * p.E;                 // uint64 stage-1 candidate keys
+  l.ck = o;    // uint64 stage-1 candidate keys, then the refinement's words per expert or (lane forms) instance
+  o += 2 * (p.lanes ? imax(p.E, p.I) : p.E);
   l.fdt = o;   o += 2 * (p.M + 1);           // divisors 1..M
   l.hs = o;    o += p.E;                     // row self of Omega (histogram)
   l.rows = o;  o += p.G * p.E;               // Omega rows of the domain's sources
@@ -311,7 +313,9 @@ __host__ __device__ inline SingleLds single_lds(const Plan &p) {
   SingleLds l;
   int o = 0;
   l.ck = o;    o += 2 * p.M * ((p.E + 15) & ~15);   // uint64 stage-1 candidate keys per domain (stride E rounded to 16)
-  l.em = o;    o += 2 * p.M * p.E;            // uint64 per domain and expert: local ranks hosting it
+  l.em = o;    // uint64 per domain and expert: local ranks hosting it (LDS form), or per instance its
+               // expert's positions (lane forms)
+  o += 2 * p.M * (p.lanes ? imax(p.E, p.I) : p.E);
   l.fdt = o;   o += 2 * (p.M + 1);            // divisors 1..M
   l.hs = o;    o += p.E;                      // histogram of local_topk
   l.cnt = o;   o += p.M;                      // candidates per domain
@@ -359,7 +363,7 @@ __host__ __device__ inline ChunkLds chunk_lds(const Plan &p, int nt) {
 
 // Global -> LDS copy by the whole workgroup, four 16-byte loads in flight
 // per thread when source, destination and length allow.
-__device__ void copy_to_lds(int *dst, const int *src, int n) {
+__device__ __forceinline__ void copy_to_lds(int *dst, const int *src, int n) {
   const int tid = threadIdx.x, nt = blockDim.x;
   if (((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0 && (n & 3) == 0) {
     const int n4 = n >> 2;
@@ -421,7 +425,7 @@ __device__ inline uint32_t fdiv_hi(uint32_t x, FastDiv f) {
 // blocks' partials: thread (e, g) sums its share of the blocks with eight
 // loads in flight; scratch needs hist_scratch_words(p) = max(E, 4 * blockDim)
 // words (the int4 path keeps blockDim int4 partial sums).
-__device__ void hist_from_partials(const Plan &p, int *hs, int *scratch) {
+__device__ __forceinline__ void hist_from_partials(const Plan &p, int *hs, int *scratch) {
   const int tid = threadIdx.x, nt = blockDim.x, E = p.E, nb = p.nb;
   if ((E & 3) == 0) {
     // thread (e4, g): four experts, a share of the blocks, 16-byte loads
@@ -554,7 +558,7 @@ __device__ __forceinline__ void block_offsets(const Plan &p, int h, int *scratch
 // a few microseconds beside the solver workgroups; the wait is bounded by
 // kHelperSpin polls (~0.2 ms), not by the hang guard, so a dispatch whose
 // helpers start late costs little.  flag: one LDS word.
-__device__ void row_self(const Plan &p, int *hs, int *scratch, int *flag) {
+__device__ __forceinline__ void row_self(const Plan &p, int *hs, int *scratch, int *flag) {
   if (threadIdx.x == 0) {
     uint32_t it = 0;
     int ok = 1;
@@ -604,7 +608,7 @@ __device__ inline bool out_of_range(const Plan &p, uint64_t total) {
 // Grid barrier of the per-domain solver workgroups: all of them are
 // resident (at most kMaxSolveGroups), and the wait is bounded so the kernel
 // always exits.
-__device__ bool grid_barrier(uint32_t *count, uint32_t groups, uint32_t spin_limit, int *flag) {
+__device__ __forceinline__ bool grid_barrier(uint32_t *count, uint32_t groups, uint32_t spin_limit, int *flag) {
   drain_then_barrier();
   if (threadIdx.x == 0) {
     __hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
@@ -758,7 +762,7 @@ __device__ inline int route_self_q(const Plan &p, int d, int e, int w, const uin
 // from omega(s, e).
 // One thread per (source, instance); acc: R words of LDS scratch.
 template <class OmegaOf>
-__device__ void write_recv_counts(const Plan &p, int i0, const int *e_of, const int *qcol, bool full,
+__device__ __forceinline__ void write_recv_counts(const Plan &p, int i0, const int *e_of, const int *qcol, bool full,
                                   const uint32_t *mask, const FastDiv *fdt, OmegaOf omega_of, int *acc) {
   const int tid = threadIdx.x, nt = blockDim.x, R = p.R, PN = p.PN;
   const int ds = (int)fdiv((uint32_t)p.self, p.fG);
@@ -782,7 +786,7 @@ __device__ void write_recv_counts(const Plan &p, int i0, const int *e_of, const 
 // writes that one value, then calls on_self(i, d, e, q); the other sources
 // of the column are left unset.
 template <class SrcOf, class DomOf, class Full, class OnSelf>
-__device__ void route_instances(const Plan &p, int NI, FastDiv fNI, int chunks, const int *e_of,
+__device__ __forceinline__ void route_instances(const Plan &p, int NI, FastDiv fNI, int chunks, const int *e_of,
                                 const uint32_t *mask, const FastDiv *fdt, int *qcol, int *U, SrcOf src_of,
                                 int stride, DomOf dom_of, Full full, OnSelf on_self) {
   const int tid = threadIdx.x, nt = blockDim.x, G = p.G;
@@ -853,303 +857,302 @@ __device__ inline int instance_of(const Plan &p, int d, int j, int e, const int 
   return -1;
 }
 
-// Forms of the refinement loop: the register form where the domain fits it
-// (refine_in_registers), scoring (instance, target) pairs when a rank has
-// at most four instances (refine_in_pairs; one-launch kernel only), else
-// the LDS form; a kernel that knows its form carries only that one's code.
-constexpr int kRefineAny = 0, kRefineReg = 1, kRefineLds = 2, kRefinePairs = 3;
-__host__ __device__ inline bool refine_in_registers(int G, int I, int PN) { return G <= 16 && I <= 128 && PN <= 64; }
-// the register form scoring (instance, target) pairs: at most four instances
-// per rank (a row of 16 lanes each)
-__host__ __device__ inline bool refine_in_pairs(int G, int I, int PN) { return refine_in_registers(G, I, PN) && PN <= 4; }
-__host__ __device__ inline int refine_form(int G, int I, int PN) {
-  return refine_in_pairs(G, I, PN) ? kRefinePairs : (refine_in_registers(G, I, PN) ? kRefineReg : kRefineLds);
+// Forms of the refinement loop: the lane forms where an expert's positions
+// in the domain fit one 64-bit word (refine_in_lanes), scoring (instance,
+// target) pairs (kRefinePairs) or instances (kRefineLanes); else the LDS
+// form.  A kernel carries one form's code.
+constexpr int kRefinePairs = 1, kRefineLds = 2, kRefineLanes = 3;
+__host__ __device__ inline bool refine_in_lanes(int G, int PN) {
+  return G >= 2 && ((G <= 8 && PN <= 254) || (G <= 16 && PN <= 14));
+}
+__host__ __device__ inline bool refine_in_pairs(int G, int PN) { return G <= 8 && PN <= 16; }
+// bits of one rank's field in an expert's position word
+__host__ __device__ inline int position_bits(int G) { return G <= 8 ? 8 : 4; }
+
+// Maximum / minimum over groups of GM = 8 or 16 lanes, left in every lane of
+// the group (DPP: lane pairs, quads, mirrored halves of a row).
+template <int GM>
+__device__ inline int group_max_i32(int v) {
+  v = imax(v, (int)dpp_mov<0xB1>((uint32_t)v));
+  v = imax(v, (int)dpp_mov<0x4E>((uint32_t)v));
+  v = imax(v, (int)dpp_mov<0x141>((uint32_t)v));
+  if (GM == 16) v = imax(v, (int)dpp_mov<0x140>((uint32_t)v));
+  return v;
+}
+template <int GM>
+__device__ inline int group_min_i32(int v) {
+  v = imin(v, (int)dpp_mov<0xB1>((uint32_t)v));
+  v = imin(v, (int)dpp_mov<0x4E>((uint32_t)v));
+  v = imin(v, (int)dpp_mov<0x141>((uint32_t)v));
+  if (GM == 16) v = imin(v, (int)dpp_mov<0x140>((uint32_t)v));
+  return v;
+}
+// Wave-wide maximum / minimum as a scalar: a row's, then across the rows by
+// broadcasts of lanes 15 and 31, read from lane 63.
+__device__ inline int wave_max_i32(int v) {
+  v = group_max_i32<16>(v);
+  v = imax(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x142, 0xA, 0xF, false));
+  v = imax(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x143, 0xC, 0xF, false));
+  return readlane_i32(v, 63);
+}
+__device__ inline uint32_t wave_min_u32(uint32_t v) {
+  return ~(uint32_t)0 ^ ((uint32_t)wave_max_i32((int)(~v ^ 0x80000000u)) ^ 0x80000000u);
 }
 
-// Minimum over each row of 16 lanes, left in every lane of the row.
-__device__ inline uint32_t row_min_all_u32(uint32_t v) {
-  uint32_t o;
-  o = dpp_mov<0x128>(v); v = o < v ? o : v;
-  o = dpp_mov<0x124>(v); v = o < v ? o : v;
-  o = dpp_mov<0x122>(v); v = o < v ? o : v;
-  o = dpp_mov<0x121>(v); v = o < v ? o : v;
-  return v;
-}
-__device__ inline uint64_t row_min_all_u64(uint64_t v) {
-  uint64_t o;
-  o = dpp_mov64<0x128>(v); v = o < v ? o : v;
-  o = dpp_mov64<0x124>(v); v = o < v ? o : v;
-  o = dpp_mov64<0x122>(v); v = o < v ? o : v;
-  o = dpp_mov64<0x121>(v); v = o < v ? o : v;
-  return v;
-}
-// Lane l's value in a vector register (the same in every lane), and a lane
-// predicate as 0 or 1 in a vector register.  A single wave pays about 20
-// cycles each time the scalar unit consumes a vector result (a lane mask
-// combined with s_and, a branch on a compare, arithmetic on a readlane), and
-// plain bool logic lives in scalar lane masks; values passed through these
-// keep such logic in vector instructions (selects, ands) instead.
-__device__ inline int vlane(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
-__device__ inline uint64_t vlane64(uint64_t v, int l) {
-  return ((uint64_t)(uint32_t)vlane((int)(v >> 32), l) << 32) | (uint32_t)vlane((int)v, l);
-}
-__device__ inline int vb(bool b) { return b ? 1 : 0; }
-__device__ inline int row_max_all_i32(int v) {
-  int o;
-  o = (int)dpp_mov<0x128>((uint32_t)v); v = o > v ? o : v;
-  o = (int)dpp_mov<0x124>((uint32_t)v); v = o > v ? o : v;
-  o = (int)dpp_mov<0x122>((uint32_t)v); v = o > v ? o : v;
-  o = (int)dpp_mov<0x121>((uint32_t)v); v = o > v ? o : v;
-  return v;
-}
-
-// Register form of the refinement loop below (two-level cost, G <= GM <= 16
-// ranks, I <= 128 instances, PN <= 64): lane l keeps instances l and l + 64
-// (expert, load, the domain ranks hosting that expert) and lane j < G rank
-// j's load and used slots; only the q columns stay in LDS.  It makes the
-// same moves in the same order as the LDS form (the busiest rank rb, lowest
-// index on ties; one lane per instance of rb scoring its lightest
-// receivers, or with at most four instances per rank one row of 16 lanes
-// per instance, a lane per target rank; the minimum of (delta descending,
-// L[rt], cost change, e, rt);
-// the transfer from rt's own assignments, then the other sources
-// ascending, rb's own last), as straight-line vector code with few scalar
-// hand-overs (see vlane and vb).  e_of, U, Lr, used, slots, em and the q
-// columns hold the final state on return.
-template <int GM, bool Pairs>
-__device__ uint32_t refine_domain_reg(const Plan &p, int d, int *e_of, int *U, int *qcol, int *slots, int *used,
-                                      int *Lr, uint64_t *em, uint32_t *flags) {
+// Lane forms of the refinement loop below (two-level cost, refine_in_lanes).
+// Lane l keeps the load and used slots of local rank l mod GM (GM = 8 or 16);
+// the instances' experts, loads and q columns stay in LDS.  pi[a] (instance
+// a of expert e) holds for each local rank a field of position_bits(G) bits:
+// e's position on that rank + 1, 0 where the rank does not hold e, so a
+// target's instance needs no search.  At the start every expert has one
+// instance in the domain at most; the caller sets pi for that.  Same moves in
+// the same order as the LDS form.  A move's candidates are scored
+//   - Pairs = 1 or 2 (at most 8 or 16 instances per rank, GM = 8): one lane
+//     per (instance of the busiest rank, target rank), one or two each;
+//   - else one lane per instance, against its lightest receivers only (its
+//     other targets cannot win, see refine_domain): the lightest ranks with
+//     a free slot, the same for every instance (usually one), and the ranks
+//     hosting its expert that are no heavier.
+// Plain: the usual shape, R <= 64 with an intra-domain cost; its move is
+// straight-line code.
+//
+// Bound: one wave's dependent chain.  The next busiest rank is found while
+// the q columns are on their way; scores take vector registers only, and the
+// scalar unit sees a move's two or more wave-wide minima.  Layers of Mixtral's
+// shape (18 moves on one wave) 32.4 -> 23.8 us, DeepSeek-V3's with 4 slots
+// (75 over 4 waves) 58.4 -> 45.0, E = 640 on one node (35 moves, 82 instances
+// a rank: one lane per instance; pairs took 90 us there, and lanes 62.6 on
+// the 12 instances a rank of DeepSeek-V3's) 59.4 -> 45.9.
+template <int GM, int Pairs, bool Plain>
+__device__ __forceinline__ uint32_t refine_domain_lanes(const Plan &p, int d, int *e_of, int *U, uint64_t *pi,
+                                                        int *qcol, int *slots, int *used, int *Lr, uint32_t *flags) {
+  static_assert(Pairs == 0 || GM == 8, "eight targets per instance");
+  constexpr int BW = GM == 8 ? 8 : 4;
+  constexpr uint32_t FM = (1u << BW) - 1u;
   const int lane = lane_id();
-  const int G = p.G, PN = p.PN, R = p.R, P = p.P, Neff = p.Neff, QS = p.QS, I = p.I;
+  const int G = p.G, PN = p.PN, R = p.R, P = p.P, Neff = p.Neff, QS = p.QS;
+  {
+    const bool free_slot = lane < G && used[lane] < Neff;
+    if (__ballot(free_slot) == 0) return 0;   // (no candidate ever: see refine_domain)
+  }
   const int r0 = d * G;
-  const bool two_level = p.cI > 0;
+  const bool two_level = Plain || p.cI > 0;
   const int64_t tokc = 2 * p.S * (int64_t)p.cI;
   const int64_t repI = (int64_t)p.cI * p.W, repX = (int64_t)p.cX * p.W;
-  // rb's instances one per lane, or (at most four of them, pairs) one per
-  // row of 16 lanes, a lane per target rank
-  constexpr bool pairs = Pairs;
-  const bool one_row = pairs ? PN <= 1 : PN <= 16;
-  const int vl = vgpr(lane);
-  const int rank_lane = vb(vl < G), rb_lane = vb(vl < PN), src_lane = vb(vl < R);
-  // instance registers: lane l holds instances l and l + 64
-  int ie0 = vl < I ? e_of[vl] : -1, ie1 = vl + 64 < I ? e_of[vl + 64] : -1;
-  int iu0 = vl < I ? U[vl] : 0, iu1 = vl + 64 < I ? U[vl + 64] : 0;
-  uint32_t ih0 = ie0 >= 0 ? (uint32_t)em[ie0] : 0u, ih1 = ie1 >= 0 ? (uint32_t)em[ie1] : 0u;
-  // rank registers (lanes >= G: never the busiest, never a receiver)
-  int lj = rank_lane ? Lr[vl] : -1;
-  int uj = rank_lane ? used[vl] : Neff;
+  const int e_lo = d * G * P, e_n = G * P;   // experts whose main lies in the domain
+  const int j = vgpr(lane & (GM - 1)), c = vgpr(lane / GM);
+  const bool in_rank = j < G;
+  const int jq = in_rank ? j : 0;
+  const int fsh = (j & (GM / 2 - 1)) * BW;   // this lane's rank's field in its half of a position word
+  const bool fhi = j >= GM / 2;
+  // rank loads: each group of lanes sums its share of a rank's instances
+  int lj = 0;
+  if (in_rank)
+    for (int pos = c; pos < PN; pos += 64 / GM) lj += U[j * PN + pos];
+#pragma unroll
+  for (int o = GM; o < 64; o *= 2) lj += __shfl_xor(lj, o);
+  if (!in_rank) lj = -1;   // never the busiest, never a receiver
+  int uj = in_rank ? used[j] : Neff;
+  // the busiest rank: the largest L, lowest index on ties
+  int Lrb = group_max_i32<GM>(lj);
+  int rbj = group_min_i32<GM>(lj == Lrb ? j : GM);
+  auto cost_of = [&](int mx, int pos, int e) {
+    const int64_t rep = (unsigned)(e - e_lo) < (unsigned)e_n ? repI : repX;
+    return tokc * (int64_t)mx + (pos ? 0 : rep);
+  };
+  // moved from the busiest rank's own sources less moved from the target's
+  // own, of dl assignments (the cost change follows from it)
+  auto own_moves = [&](int dl, int u, int qt, int qrb) {
+    const int m_rt = imin(dl, qt), rest = dl - m_rt;
+    return two_level ? rest - imin(rest, u - qt - qrb) - m_rt : 0;
+  };
   uint32_t it = 0;
   RSECT_DECL(d);
   for (;; ++it) {
-    // ---- busiest rank rb: the largest L, lowest index on ties
-    const int Lrb = vlane(row_max_all_i32(lj), 0);
-    const int rbj_s = __ffsll((long long)__ballot(rank_lane && lj == Lrb)) - 1;
-    const int rbj = vgpr(rbj_s);
-    const int rb = r0 + rbj;
-    // ---- receivers: L[rt] <= L[rb] - 2; the lightest with a free slot form
-    // one level (lf, tfm); hosting receivers matter up to that level (lightm)
-    const int low = rank_lane & vb(vl != rbj) & vb(Lrb - lj >= 2);
-    const int fr = low & vb(uj < Neff);
-    const uint32_t lf = (uint32_t)vlane((int)row_min_all_u32(fr ? (uint32_t)lj : ~0u), 0);
-    const uint32_t tfm = (uint32_t)vgpr((int)(uint32_t)__ballot(fr & vb((uint32_t)lj == lf)));
-    const uint32_t lightm = (uint32_t)vgpr((int)(uint32_t)__ballot(low & vb((uint32_t)lj <= lf)));
-    RSECT(0);
-    // ---- the candidates: a scored lane's instance of rb (expert e, load u,
-    // hosting mask hm), its lightest receiver level lm, delta, and its best
-    // target bj with that target's cost change bc and q column word bq
-    int e, u, valid, delta, bj, bq;
-    uint32_t hm, lm;
-    int64_t bc;
-    if constexpr (pairs) {
-      // lane 16 c + j: rb's instance c (a = rbj PN + c) against local rank
-      // j; the row of 16 lanes of instance c keeps its lightest receivers
-      // (low ranks with a free slot or already hosting e), which are its
-      // targets, each scored by one lane
-      const uint32_t lowm = (uint32_t)vgpr((int)(uint32_t)__ballot(low)), frm = (uint32_t)vgpr((int)(uint32_t)__ballot(fr));
-      const int c = vl >> 4, jj = vl & 15;
-      const int a = rbj * PN + c;
-      const int src = (a & 63) << 2;
-      const int e0 = __builtin_amdgcn_ds_bpermute(src, ie0), e1 = __builtin_amdgcn_ds_bpermute(src, ie1);
-      const int u0 = __builtin_amdgcn_ds_bpermute(src, iu0), u1 = __builtin_amdgcn_ds_bpermute(src, iu1);
-      const int h0 = __builtin_amdgcn_ds_bpermute(src, (int)ih0), h1 = __builtin_amdgcn_ds_bpermute(src, (int)ih1);
-      const int Lq = __builtin_amdgcn_ds_bpermute(jj << 2, lj);   // rank jj's load (-1 from G on)
-      const int *qa = qcol + (c < PN ? a : 0) * QS;
-      const int qrb = two_level ? qa[rb] : 0;
-      const int qt = two_level ? qa[r0 + (jj < G ? jj : 0)] : 0;
-      const int hi = vb(a >= 64);
-      e = hi ? e1 : e0;
-      u = hi ? u1 : u0;
-      hm = (uint32_t)(hi ? h1 : h0);
-      const int cand = vb(c < PN) & vb(e >= 0) & vb(u > 0);
-      const int hostj = (int)((hm >> jj) & 1u);
-      const int ok = cand & (int)((lowm >> jj) & 1u) & ((int)((frm >> jj) & 1u) | hostj);
-      lm = row_min_all_u32(ok ? (uint32_t)Lq : ~0u);
-      valid = ok & vb((uint32_t)Lq == lm);
-      delta = imin(u, (Lrb - (int)lm) >> 1);
-      int64_t dc = 0;
-      if (two_level) {
-        const int m_rt = imin(delta, qt);
-        const int rest = delta - m_rt;
-        const int m_rb = rest - imin(rest, u - qt - qrb);
-        dc = tokc * (int64_t)(m_rb - m_rt);
-      }
-      bc = hostj ? dc : dc + (((int)fdiv((uint32_t)e, p.fGP) == d) ? repI : repX);
-      bj = jj;
-      bq = qt;
-    } else {
-      // ---- lane c < PN: rb's instance a = rbj PN + c, its fields from the lane
-      // holding it
-      const int a = rbj * PN + vl;
-      const int src = (a & 63) << 2;
-      const int e0 = __builtin_amdgcn_ds_bpermute(src, ie0), e1 = __builtin_amdgcn_ds_bpermute(src, ie1);
-      const int u0 = __builtin_amdgcn_ds_bpermute(src, iu0), u1 = __builtin_amdgcn_ds_bpermute(src, iu1);
-      const int h0 = __builtin_amdgcn_ds_bpermute(src, (int)ih0), h1 = __builtin_amdgcn_ds_bpermute(src, (int)ih1);
-      const int *qa = qcol + (rb_lane ? a : 0) * QS;
-      const int qrb = two_level ? qa[rb] : 0;
-      const int hi = vb(a >= 64);
-      e = hi ? e1 : e0;
-      u = hi ? u1 : u0;
-      hm = (uint32_t)(hi ? h1 : h0);
-      const int cand = rb_lane & vb(e >= 0) & vb(u > 0);
-      // the lightest receivers hosting e, no heavier than the free level
-      const uint32_t hl = cand ? hm & lightm : 0u;
-      uint32_t lh = ~0u, th = 0u;
-      if (__ballot(hl != 0u)) {
+    const int gap = Lrb - lj;
+    const bool low = gap >= 2 && j != rbj, room = uj < Neff;
+    const int rbs = readlane_i32(rbj, 0);
+    const int a0 = rbs * PN;
+    // ---- this lane's best candidate: delta (0: none), target load, what its
+    // cost change follows from (own_moves, position on the target, expert);
+    // !Pairs: target, instance
+    int bd = 0, bl = lj, bx = 0, be = 0, bpos = 0, bt = 0, ba = 0;
+    if constexpr (Pairs > 0) {
+      // (the words of both instances of a lane are on their way together)
+      int es[Pairs], us[Pairs], qb[Pairs], qt[Pairs];
+      uint64_t ws[Pairs];
 #pragma unroll
-        for (int j = 0; j < GM; ++j) {
-          const uint32_t Lj = (uint32_t)__builtin_amdgcn_readlane(lj, j);
-          const uint32_t c = (hl >> j) & 1u ? Lj : ~0u;
-          th = c < lh ? 1u << j : (c == lh ? th | (1u << j) : th);
-          lh = c < lh ? c : lh;
-        }
+      for (int i = 0; i < Pairs; ++i) {
+        const int a = a0 + (c + 8 * i < PN ? c + 8 * i : 0);
+        const int *qa = qcol + a * QS + r0;
+        es[i] = e_of[a];
+        us[i] = U[a];
+        ws[i] = pi[a];
+        qb[i] = qa[rbs];
+        qt[i] = qa[jq];
       }
-      lm = lf < lh ? lf : lh;
-      valid = cand & vb(lm != ~0u);
-      const uint32_t tset = valid ? ((lf == lm ? tfm : 0u) | (lh == lm ? th : 0u)) : 0u;
-      delta = imin(u, (Lrb - (int)lm) >> 1);
-      // ---- cost change at each target of tset, lowest (cost, rt) kept
-      auto cost_at = [&](int jt, int &qt) {
-        int64_t dc = 0;
-        qt = 0;
-        if (two_level) {
-          qt = qa[r0 + jt];
-          const int m_rt = imin(delta, qt);
-          const int rest = delta - m_rt;
-          const int m_rb = rest - imin(rest, u - qt - qrb);
-          dc = tokc * (int64_t)(m_rb - m_rt);
-        }
-        const int64_t rep = ((int)fdiv((uint32_t)e, p.fGP) == d) ? repI : repX;
-        return ((hm >> jt) & 1u) ? dc : dc + rep;
-      };
-      bj = valid ? __ffs(tset) - 1 : 0;
-      bc = cost_at(bj, bq);
-      const uint32_t more = tset & (tset - 1u);
-      if (__ballot(more != 0u)) {
-        for (uint32_t t = more; t; t &= t - 1u) {
-          const int jt = __ffs(t) - 1;
-          int qt;
-          const int64_t dc = cost_at(jt, qt);
-          if (dc < bc) {
-            bc = dc;
-            bj = jt;
-            bq = qt;
+#pragma unroll
+      for (int i = 0; i < Pairs; ++i) {
+        const int pos = (int)(((fhi ? (uint32_t)(ws[i] >> 32) : (uint32_t)ws[i]) >> fsh) & FM);
+        const bool on = c + 8 * i < PN && us[i] > 0 && low && (room || pos != 0);
+        const int sd = on ? imin(us[i], gap >> 1) : 0;
+        const int sx = own_moves(sd, us[i], qt[i], qb[i]);
+        bool lt = i == 0 || sd > bd;
+        if (i > 0) {
+          // equal delta (and the same target): the lower cost change, then expert
+          const bool tie = sd == bd && sd > 0;
+          if (__ballot(tie)) {
+            const int64_t cn = cost_of(sx, pos, es[i]), cb = cost_of(bx, bpos, be);
+            lt = lt || (tie && (cn < cb || (cn == cb && es[i] < be)));
           }
         }
+        bd = lt ? sd : bd;
+        bx = lt ? sx : bx;
+        be = lt ? es[i] : be;
+        bpos = lt ? pos : bpos;
+        ba = lt ? i : ba;   // (its round)
+      }
+    } else {
+      const int Lb = readlane_i32(Lrb, 0);
+      const int lfv = group_min_i32<GM>(low && room ? lj : INT_MAX);
+      const int lf = readlane_i32(lfv, 0);
+      constexpr uint32_t ranks = (1u << GM) - 1u;
+      const uint32_t tf = (uint32_t)__ballot(low && room && lj == lfv) & ranks;   // lightest with a free slot
+      const uint32_t th = (uint32_t)__ballot(low && lj <= lfv) & ranks & ~tf;     // others no heavier
+      const int t1 = tf ? __ffs(tf) - 1 : 0, dfree = tf ? (Lb - lf) >> 1 : 0;
+      auto field = [&](uint64_t w, int t) { return (int)(w >> (BW * t)) & (int)FM; };
+      // instance a: expert e, load u, position word w, q[rb], q[t1]
+      auto score = [&](int a, int e, int u, uint64_t w, int qrb, int q1, bool on) {
+        on = on && u > 0;
+        int sd = on ? imin(u, dfree) : 0, sl = lf, st = t1, sp = field(w, t1);
+        int sx = own_moves(sd, u, q1, qrb);
+        const int *qa = qcol + a * QS + r0;
+        for (uint32_t m = tf & (tf - 1u); m; m &= m - 1u) {
+          // another rank of the same load: the lower cost change, then index
+          const int t = __ffs(m) - 1, qt = qa[t], pos = field(w, t);
+          const int mx = own_moves(sd, u, qt, qrb);
+          if (cost_of(mx, pos, e) < cost_of(sx, sp, e)) {
+            st = t;
+            sp = pos;
+            sx = mx;
+          }
+        }
+        for (uint32_t m = th; m; m &= m - 1u) {
+          const int t = __ffs(m) - 1, pos = field(w, t);
+          if (__ballot(on && pos != 0) == 0) continue;
+          const int Lt = readlane_i32(lj, t), qt = qa[t];
+          const int dl = on && pos ? imin(u, (Lb - Lt) >> 1) : 0;
+          const int mx = own_moves(dl, u, qt, qrb);
+          const int64_t cn = cost_of(mx, pos, e), cb = cost_of(sx, sp, e);
+          const bool lt = dl > sd || (dl == sd && dl > 0 &&
+                                      (Lt < sl || (Lt == sl && (cn < cb || (cn == cb && t < st)))));
+          sd = lt ? dl : sd;
+          sl = lt ? Lt : sl;
+          st = lt ? t : st;
+          sp = lt ? pos : sp;
+          sx = lt ? mx : sx;
+        }
+        // against this lane's earlier instance: delta, load, cost, expert
+        bool lt = sd > bd;
+        const bool tie = sd == bd && sd > 0;
+        if (__ballot(tie)) {
+          const int64_t cn = cost_of(sx, sp, e), cb = cost_of(bx, bpos, be);
+          lt = lt || (tie && (sl < bl || (sl == bl && (cn < cb || (cn == cb && e < be)))));
+        }
+        bd = lt ? sd : bd;
+        bl = lt ? sl : bl;
+        bx = lt ? sx : bx;
+        be = lt ? e : be;
+        bpos = lt ? sp : bpos;
+        bt = lt ? st : bt;
+        ba = lt ? a : ba;
+      };
+      for (int p0 = 0; p0 < PN; p0 += 64) {
+        const bool on = p0 + lane < PN;
+        const int a = a0 + (on ? p0 + lane : 0);
+        const int *qa = qcol + a * QS + r0;
+        score(a, e_of[a], U[a], pi[a], qa[rbs], qa[t1], on);
+      }
+    }
+    RSECT(0);
+    // ---- the wave's best: delta descending, L[rt], cost change, e, rt
+    const int dw = wave_max_i32(bd);
+    if (dw == 0 || it >= p.iter_limit) {
+      if (dw != 0 && lane == 0) *flags |= TOPOEP_ST_ITER;
+      break;
+    }
+    const uint32_t Lrt = wave_min_u32(bd == dw ? (uint32_t)bl : ~0u);
+    const bool in2 = bd == dw && (uint32_t)bl == Lrt;
+    uint64_t win = __ballot(in2);
+    if (__popcll(win) != 1) {
+      const uint64_t kc = (uint64_t)cost_of(bx, bpos, be) ^ (1ull << 63);
+      const uint32_t ch = wave_min_u32(in2 ? (uint32_t)(kc >> 32) : ~0u);
+      const bool in3 = in2 && (uint32_t)(kc >> 32) == ch;
+      const uint32_t cl = wave_min_u32(in3 ? (uint32_t)kc : ~0u);
+      const bool in4 = in3 && (uint32_t)kc == cl;
+      win = __ballot(in4);
+      if (__popcll(win) != 1) {
+        // one expert: its lanes (Pairs: one instance against several ranks,
+        // ascending) start with the lowest rt
+        const uint32_t ew = wave_min_u32(in4 ? (uint32_t)be : ~0u);
+        win = __ballot(in4 && (uint32_t)be == ew);
       }
     }
     RSECT(1);
-    // ---- minimum key: (delta descending, L[rt]) first, then cost, e, rt
-    const uint64_t k1 = valid ? ((uint64_t)(uint32_t)(0x7FFFFFFF - delta) << 32) | lm : ~0ull;
-    uint64_t m1 = row_min_all_u64(k1);
-    if (!one_row) {
-      const uint64_t x1 = vlane64(m1, 16), x2 = vlane64(m1, 32), x3 = vlane64(m1, 48);
-      m1 = vlane64(m1, 0);
-      m1 = x1 < m1 ? x1 : m1;
-      m1 = x2 < m1 ? x2 : m1;
-      m1 = x3 < m1 ? x3 : m1;
-    } else {
-      m1 = vlane64(m1, 0);
-    }
-    if (m1 == ~0ull) break;
-    if (it >= p.iter_limit) {
-      if (lane == 0) *flags |= TOPOEP_ST_ITER;
-      break;
-    }
-    uint64_t win = __ballot(k1 == m1);
-    if (__popcll(win) != 1) {
-      const bool in2 = k1 == m1;
-      const uint64_t kc = in2 ? (uint64_t)bc ^ (1ull << 63) : ~0ull;
-      const uint64_t m3 = wave_min_u64(kc);
-      win &= __ballot(kc == m3);
-      if (__popcll(win) != 1) {
-        const bool in3 = ((win >> lane) & 1ull) != 0;
-        const uint64_t ke = in3 ? ((uint64_t)(uint32_t)e << 32) | (uint32_t)(r0 + bj) : ~0ull;
-        const uint64_t m4 = wave_min_u64(ke);
-        win &= __ballot(ke == m4);
-      }
-    }
     const int wl = __ffsll((long long)win) - 1;
-    const int dw = vlane(delta, wl);
-    const int Lrt = vlane((int)lm, wl);
-    const int ew = vlane(e, wl);
-    const int rtj_s = __builtin_amdgcn_readlane(bj, wl);
-    const int rtj = vgpr(rtj_s);
-    const int rt = r0 + rtj;
-    const int uw = vlane(u, wl);
-    const int qrt = vlane(bq, wl);
-    const uint32_t hw = (uint32_t)vlane((int)hm, wl);
-    const int aw_s = rbj_s * PN + (pairs ? wl >> 4 : wl);
-    const int aw = vgpr(aw_s);
-    const int fresh = vb(((hw >> rtj) & 1u) == 0u);
+    const int rtj = Pairs ? wl & (GM - 1) : readlane_i32(bt, wl);
+    const int aw = Pairs == 0 ? readlane_i32(ba, wl) : a0 + wl / GM + (Pairs > 1 ? 8 * readlane_i32(ba, wl) : 0);
+    const int pos = readlane_i32(bpos, wl), ew = readlane_i32(be, wl);
+    const uint64_t ww = pi[aw];   // (with the column's words below: one round trip)
+    const int at = pos ? pos - 1 : P + readlane_i32(uj, rtj);   // the target's instance: held, or its first free slot
+    const int a2 = rtj * PN + at;
+    int *qw = qcol + aw * QS, *qb = qcol + a2 * QS;
+    const int rt = r0 + rtj, rb = r0 + rbs;
+    // ---- the transfer of dw assignments from aw's column to a2's: rt's own
+    // first, the other sources ascending, rb's own last (ascending alone
+    // when the intra-domain cost is zero); one pass up to 64 sources, lanes
+    // >= R on the spare word after them (QS > R)
+    const bool one_pass = Plain || R <= 64;
+    const int sv = lane < R ? lane : R;
+    int av = 0;
+    if (one_pass) av = qw[sv];
+    const int uw = U[aw];
+    // ---- the ranks, and the next busiest one
+    lj = j == rbs ? Lrb - dw : (j == rtj ? (int)Lrt + dw : lj);
+    uj += j == rtj && pos == 0 ? 1 : 0;
+    Lrb = group_max_i32<GM>(lj);
+    rbj = group_min_i32<GM>(lj == Lrb ? j : GM);
     RSECT(2);
-    // ---- rt's instance of e: the one it holds (rt's instances are rtj PN ..
-    // rtj PN + PN - 1), or its first free slot
-    const int base = rtj * PN;
-    const uint64_t f0 = __ballot(vb(ie0 == ew) & vb((uint32_t)(vl - base) < (uint32_t)PN));
-    const uint64_t f1 = __ballot(vb(ie1 == ew) & vb((uint32_t)(vl + 64 - base) < (uint32_t)PN));
-    const int held = f0 ? __ffsll((long long)f0) - 1 : 64 + __ffsll((long long)f1) - 1;
-    const int a2 = fresh ? base + P + vlane(uj, rtj_s) : vgpr(held);
-    RSECT(3);
-    // ---- the transfer of dw assignments from aw's column to a2's
-    int *qw = qcol + aw_s * QS;
-    int *qb = qcol + a2 * QS;
-    if (R <= 64) {
-      // one pass: rt's own first, the other sources ascending, rb's own last;
-      // lanes >= R take the spare word after the sources (QS > R)
-      const int sv = src_lane ? vl : R;
-      const int av = src_lane ? qw[sv] : 0;
+    if (one_pass) {
+      if (lane >= R) av = 0;
       int excl;
       if (two_level) {
-        const int is_rt = vb(vl == rt), is_rb = vb(vl == rb);
-        const int other = (is_rt | is_rb) ? 0 : av;
+        const bool is_rt = lane == rt, is_rb = lane == rb;
+        const int other = is_rt || is_rb ? 0 : av, qrt = readlane_i32(av, rt);
         const int incl = wave_incl_scan(other);
-        const int tot = vlane(incl, 63);
-        excl = is_rt ? 0 : (is_rb ? qrt + tot : qrt + incl - other);
+        excl = is_rt ? 0 : (is_rb ? qrt + readlane_i32(incl, 63) : qrt + incl - other);
       } else {
         excl = wave_incl_scan(av) - av;
       }
-      int m = dw - excl;
-      m = m < 0 ? 0 : (m > av ? av : m);
+      const int m = imin(imax(dw - excl, 0), av);
       qw[sv] = av - m;
       atomicAdd(&qb[sv], m);
     } else {
       int rest = dw;
       int m_rt = 0;
       if (two_level) {
-        m_rt = imin(rest, qrt);
+        m_rt = imin(rest, uniform_i32(qw[rt]));
         rest -= m_rt;
       }
       for (int s0 = 0; s0 < R && rest > 0; s0 += 64) {
-        const int sv = s0 + lane;
-        int av = 0;
-        if (sv < R && (!two_level || (sv != rt && sv != rb))) av = qw[sv];
-        const int incl = wave_incl_scan(av);
-        const int excl = incl - av;
-        int m = rest - excl;
-        m = m < 0 ? 0 : (m > av ? av : m);
+        const int s = s0 + lane;
+        int v = 0;
+        if (s < R && (!two_level || (s != rt && s != rb))) v = qw[s];
+        const int incl = wave_incl_scan(v);
+        const int m = imin(imax(rest - (incl - v), 0), v);
         if (m) {
-          qw[sv] = av - m;
-          atomicAdd(&qb[sv], m);
+          qw[s] = v - m;
+          atomicAdd(&qb[s], m);
         }
         const int total = readlane_i32(incl, 63);
         rest -= total < rest ? total : rest;
@@ -1165,42 +1168,48 @@ __device__ uint32_t refine_domain_reg(const Plan &p, int d, int *e_of, int *U, i
         }
       }
     }
+    RSECT(3);
+    // ---- the instances: loads; the target's expert and slot (already these
+    // where it held the expert), and its position in the words of every
+    // instance of that expert
+    const uint64_t word = ww | (uint64_t)(uint32_t)(at + 1) << (BW * rtj);
+    const int held = (int)(((fhi ? (uint32_t)(word >> 32) : (uint32_t)word) >> fsh) & FM);
+    if (lane < GM && held) pi[lane * PN + held - 1] = word;
+    if (lane == 0) {
+      U[aw] = uw - dw;
+      atomicAdd(&U[a2], dw);
+      e_of[a2] = ew;
+      if (at >= P) slots[rtj * Neff + at - P] = ew;
+    }
+    wave_sync();
     RSECT(4);
-    // ---- registers: the two instances' loads, a new replica's expert and the
-    // hosting mask of its expert, the two ranks
-    const uint32_t hn = hw | (1u << rtj);
-    const int at0 = vb(vl == a2), at1 = vb(vl + 64 == a2);
-    iu0 = vl == aw ? uw - dw : iu0;
-    iu1 = vl + 64 == aw ? uw - dw : iu1;
-    iu0 = at0 ? iu0 + dw : iu0;
-    iu1 = at1 ? iu1 + dw : iu1;
-    ie0 = (fresh & at0) ? ew : ie0;
-    ie1 = (fresh & at1) ? ew : ie1;
-    ih0 = (fresh & vb(ie0 == ew)) ? hn : ih0;
-    ih1 = (fresh & vb(ie1 == ew)) ? hn : ih1;
-    lj = vl == rbj ? Lrb - dw : (vl == rtj ? Lrt + dw : lj);
-    uj = (fresh & vb(vl == rtj)) ? uj + 1 : uj;
-    RSECT(5);
   }
   RSECT_END(it);
-  // final state: instances, their slots, the hosting masks, the ranks
-  auto put = [&](int a, int ex, int ux, uint32_t hx) {
-    if (a < I) {
-      e_of[a] = ex;
-      U[a] = ux;
-      const int j = (int)fdiv((uint32_t)a, p.fPN), pos = a - j * PN;
-      if (pos >= P) slots[j * Neff + pos - P] = ex;
-      if (ex >= 0) em[ex] = (uint64_t)hx;
-    }
-  };
-  put(vl, ie0, iu0, ih0);
-  put(vl + 64, ie1, iu1, ih1);
-  if (rank_lane) {
-    Lr[vl] = lj;
-    used[vl] = uj;
+  if (lane < G) {
+    Lr[lane] = lj;
+    used[lane] = uj;
   }
   wave_sync();
   return it;
+}
+
+// The lane form for the plan's shape (Form: kRefinePairs or kRefineLanes).
+template <int Form>
+__device__ __forceinline__ uint32_t refine_domain_in_lanes(const Plan &p, int d, int *e_of, int *U, uint64_t *pi,
+                                                           int *qcol, int *slots, int *used, int *Lr,
+                                                           uint32_t *flags) {
+  const bool plain = p.R <= 64 && p.cI > 0;
+  if constexpr (Form == kRefinePairs) {
+    if (p.PN <= 8)
+      return plain ? refine_domain_lanes<8, 1, true>(p, d, e_of, U, pi, qcol, slots, used, Lr, flags)
+                   : refine_domain_lanes<8, 1, false>(p, d, e_of, U, pi, qcol, slots, used, Lr, flags);
+    return plain ? refine_domain_lanes<8, 2, true>(p, d, e_of, U, pi, qcol, slots, used, Lr, flags)
+                 : refine_domain_lanes<8, 2, false>(p, d, e_of, U, pi, qcol, slots, used, Lr, flags);
+  }
+  if (p.G <= 8)
+    return plain ? refine_domain_lanes<8, 0, true>(p, d, e_of, U, pi, qcol, slots, used, Lr, flags)
+                 : refine_domain_lanes<8, 0, false>(p, d, e_of, U, pi, qcol, slots, used, Lr, flags);
+  return refine_domain_lanes<16, 0, false>(p, d, e_of, U, pi, qcol, slots, used, Lr, flags);
 }
 
 // Intra-node refinement of domain d (Section 4.3, Eq. 10), by one wave.
@@ -1210,9 +1219,8 @@ __device__ uint32_t refine_domain_reg(const Plan &p, int d, int *e_of, int *U, i
 // lowest rank), takes the best (instance of rb, other rank of the domain)
 // candidate by key (delta desc, L[rt] asc, cost change asc, e asc, rt asc)
 // and commits it: each lane takes an instance of rb and scores only its
-// lightest receivers (the others cannot win).  Domains that fit it run the
-// register form (refine_domain_reg); Form pins one form at compile time.
-// The moved assignments come from sources in ascending (c(s,rt) - c(s,rb),
+// lightest receivers (the others cannot win).  (refine_domain_lanes makes the
+// same moves for the domains that fit it.)  The moved assignments come from sources in ascending (c(s,rt) - c(s,rb),
 // s) order: with the two-level cost that is rt
 // itself, then the other sources ascending, then rb (or plain ascending when
 // the intra-domain cost is zero).  The loop ends when no candidate has
@@ -1223,11 +1231,9 @@ __device__ uint32_t refine_domain_reg(const Plan &p, int d, int *e_of, int *U, i
 // moved assignments come from the sources in the precomputed (c(s,rt) -
 // c(s,rb), s) order of gc, and the cost change uses the cost matrix and
 // ||W_e||.
-template <bool General = false, int Form = kRefineAny>
-__device__ uint32_t refine_domain(const Plan &p, int d, int *e_of, int *U, int *qcol, int *slots, int *used,
+template <bool General = false>
+__device__ __forceinline__ uint32_t refine_domain(const Plan &p, int d, int *e_of, int *U, int *qcol, int *slots, int *used,
                                   int *Lr, uint64_t *em, uint32_t *flags, bool prepared, GenCost gc = GenCost{}) {
-  static_assert(!(General && (Form == kRefineReg || Form == kRefinePairs)),
-                "the register form scores the two-level cost only");
   const int lane = lane_id();
   const int G = p.G, PN = p.PN, R = p.R, P = p.P, Neff = p.Neff, QS = p.QS, E = p.E, I = p.I;
   if (G < 2) return 0;
@@ -1257,21 +1263,6 @@ __device__ uint32_t refine_domain(const Plan &p, int d, int *e_of, int *U, int *
     }
   }
   wave_sync();
-  // (the pairs variant only where the kernel was built for it: the
-  // one-launch plan's; the three-kernel solvers keep one register variant)
-  if constexpr (!General && Form == kRefinePairs) {
-    return G <= 8 ? refine_domain_reg<8, true>(p, d, e_of, U, qcol, slots, used, Lr, em, flags)
-                  : refine_domain_reg<16, true>(p, d, e_of, U, qcol, slots, used, Lr, em, flags);
-  }
-  if constexpr (!General && (Form == kRefineReg || Form == kRefineAny)) {
-    if (Form == kRefineReg || refine_in_registers(G, I, PN)) {
-      return G <= 8 ? refine_domain_reg<8, false>(p, d, e_of, U, qcol, slots, used, Lr, em, flags)
-                    : refine_domain_reg<16, false>(p, d, e_of, U, qcol, slots, used, Lr, em, flags);
-    }
-  }
-  if constexpr (Form == kRefineReg || Form == kRefinePairs) {
-    return 0;   // (not reached: the host picks the register form only where it applies)
-  } else {
   // One lane per instance of rb.  Among the targets an instance may move to
   // (the domain's other ranks with L[rt] <= L[rb] - 2 that host its expert
   // or have a free slot) delta = min(u, (L[rb] - L[rt]) / 2) only grows as
@@ -1532,7 +1523,6 @@ __device__ uint32_t refine_domain(const Plan &p, int d, int *e_of, int *U, int *
   }
   RSECT_END(it);
   return it;   // one move per completed iteration
-  }
 }
 
 // Stage-1 candidate key: (D descending, e ascending) as one unsigned
@@ -1698,7 +1688,7 @@ __device__ void emit_instance_list(const Plan &p, const int *qcol, const int *sl
 // the histogram hs) over rows [r0, r1) held at rows[(s - r0) * E + e];
 // wave-reduced, then one LDS atomic per wave into misc[0] (bits) and
 // misc[8..9] (total).  Called by every thread of the workgroup.
-__device__ void scan_rows(const Plan &p, int r0, int r1, const int *rows, const int *hs, int *misc) {
+__device__ __forceinline__ void scan_rows(const Plan &p, int r0, int r1, const int *rows, const int *hs, int *misc) {
   const int tid = threadIdx.x, nt = blockDim.x, E = p.E;
   bool neg = false, diff = false;
   uint64_t tot = 0;
@@ -1733,7 +1723,7 @@ __device__ void scan_rows(const Plan &p, int r0, int r1, const int *rows, const 
 // cost (symmetric, nonnegative, zero diagonal) and every size nonnegative,
 // and the largest entry and size for the exact-range bound.  misc[16..23]
 // are scratch; returns the COST bit or 0 (the same on every thread).
-__device__ uint32_t general_check(const Plan &p, int *misc, uint64_t *cmax, uint64_t *wmax) {
+__device__ __forceinline__ uint32_t general_check(const Plan &p, int *misc, uint64_t *cmax, uint64_t *wmax) {
   const int tid = threadIdx.x, nt = blockDim.x, R = p.R;
   if (tid < 8) misc[16 + tid] = 0;
   lds_barrier();
@@ -1779,7 +1769,7 @@ __device__ uint32_t general_check(const Plan &p, int *misc, uint64_t *cmax, uint
 // Cost tables of domain d for its refinement: ccol[j][s] = c(s, dG + j),
 // ||W_e|| and, per ordered pair (jb, jt) of the domain's ranks, the sources
 // in ascending (c(s,rt) - c(s,rb), s) order.
-__device__ GenCost general_tables(const Plan &p, int d, int *sm, const DomainLds &lay) {
+__device__ __forceinline__ GenCost general_tables(const Plan &p, int d, int *sm, const DomainLds &lay) {
   const int tid = threadIdx.x, nt = blockDim.x, R = p.R, G = p.G;
   uint16_t *ord = reinterpret_cast<uint16_t *>(sm + lay.ord);
   int *ccol = sm + lay.ccol;
@@ -2188,6 +2178,7 @@ __device__ __forceinline__ void domain_solver(const Plan &p0, int *sm) {
       else e = (pos - P) < used[j] ? slots[j * Neff + pos - P] : -1;
       e_of[a] = e;
       U[a] = 0;
+      if (p.lanes) ck[a] = e >= 0 ? (uint64_t)(uint32_t)(pos + 1) << (position_bits(G) * j) : 0;
     }
     lds_barrier();
     if (wg == 0) STAMP(p, 4);
@@ -2232,7 +2223,10 @@ __device__ __forceinline__ void domain_solver(const Plan &p0, int *sm) {
         if (tid == 0 && mv) atomicAdd(&p.ctrl[kCtrlMoves], mv);
       }
     } else if (tid < 64) {
-      const uint32_t mv = refine_domain(p, d, e_of, U, qcol, slots, used, Lr, ck, &flags, false);
+      const uint32_t mv = p.lanes && refine_in_pairs(G, PN)
+                              ? refine_domain_in_lanes<kRefinePairs>(p, d, e_of, U, ck, qcol, slots, used, Lr, &flags)
+                          : p.lanes ? refine_domain_in_lanes<kRefineLanes>(p, d, e_of, U, ck, qcol, slots, used, Lr, &flags)
+                                 : refine_domain<>(p, d, e_of, U, qcol, slots, used, Lr, ck, &flags, false);
       if (tid == 0 && mv) atomicAdd(&p.ctrl[kCtrlMoves], mv);
     }
     lds_barrier();
@@ -2460,7 +2454,8 @@ __device__ inline void single_init(const Plan &p, const SingleState &t) {
   for (int i = tid; i < p.E * p.RW; i += nt) t.bm[i] = 0;
   for (int i = tid; i < p.R; i += nt) t.sendl[i] = 0;
   for (int i = tid; i < p.M * p.cap1; i += nt) t.repl[i] = -1;
-  for (int i = tid; i < p.M * p.E; i += nt) t.em[i] = 0;
+  if (!p.lanes)
+    for (int i = tid; i < p.M * p.E; i += nt) t.em[i] = 0;
   // candidate keys: ~0 sorts after every candidate (stage1_ranks reads
   // whole parts of 16)
   for (int i = tid; i < p.M * ((p.E + 15) & ~15); i += nt) t.ck[i] = ~0ull;
@@ -2609,7 +2604,7 @@ struct NoHook {
 template <class H> struct IsNoHook { static constexpr bool value = false; };
 template <> struct IsNoHook<NoHook> { static constexpr bool value = true; };
 
-template <int Form = kRefineAny, class Published = NoHook>
+template <int Form, class Published = NoHook>
 __device__ __forceinline__ void single_plan(const Plan &p, const SingleState &t, uint32_t gst, bool or_status,
                                             Published published = NoHook{}) {
   uint64_t *ck = t.ck, *em = t.em;
@@ -2692,7 +2687,11 @@ __device__ __forceinline__ void single_plan(const Plan &p, const SingleState &t,
         }
         e_of[idx] = e;
         U[idx] = 0;
-        if (e >= 0) atomicOr(reinterpret_cast<unsigned long long *>(&em[d * E + e]), 1ull << (uint32_t)j);
+        if constexpr (Form != kRefineLds) {
+          em[idx] = e >= 0 ? (uint64_t)(uint32_t)(pos + 1) << (position_bits(G) * j) : 0;
+        } else {
+          if (e >= 0) atomicOr(reinterpret_cast<unsigned long long *>(&em[d * E + e]), 1ull << (uint32_t)j);
+        }
       } else if (v < n2) {
         const int e = v - n1;
         const int dm = (int)fdiv((uint32_t)e, p.fGP);
@@ -2743,19 +2742,33 @@ __device__ __forceinline__ void single_plan(const Plan &p, const SingleState &t,
     // ---- intra-node refinement (Eq. 10): one wave per domain (it sums its
     // ranks' loads first; a domain without a free slot returns at once)
     uint32_t flags = 0, moves = 0;
-    for (int d = wave; d < M; d += nw)
-      moves += refine_domain<false, Form>(p, d, e_of + d * I, U + d * I, qcol + d * I * p.QS, slots + d * G * Neff,
-                             used + d * G, Lr + d * G, em + (int64_t)d * E, &flags, true);
+    for (int d = wave; d < M; d += nw) {
+      if constexpr (Form != kRefineLds)
+        moves += refine_domain_in_lanes<Form>(p, d, e_of + d * I, U + d * I, em + d * I, qcol + d * I * p.QS,
+                                       slots + d * G * Neff, used + d * G, Lr + d * G, &flags);
+      else
+        moves += refine_domain<>(p, d, e_of + d * I, U + d * I, qcol + d * I * p.QS, slots + d * G * Neff,
+                                 used + d * G, Lr + d * G, em + (int64_t)d * E, &flags, true);
+    }
     if (lane_id() == 0) {
       if (flags) atomicOr(reinterpret_cast<unsigned *>(&misc[0]), flags);
       if (moves) atomicAdd(reinterpret_cast<unsigned *>(&misc[12]), moves);
     }
     lds_barrier();
+  }
+  // (the plan's fields load again: kept across the refinement they would take
+  // the registers of its loop)
+  const Plan pr = solver_plan(role_plan(p));
+  if (misc[14]) {
     // ---- the refined domains' instances enter the bitmaps and send counts
     for (int idx = tid; idx < M * I; idx += nt) {
-      const int d = (int)fdiv((uint32_t)idx, p.fI);
-      const int e = e_of[idx];
-      if (dfree[d] && e >= 0) mark(idx, d, e, qcol[idx * p.QS + p.self]);
+      const int d = (int)fdiv((uint32_t)idx, pr.fI);
+      const int e = e_of[idx], q = qcol[idx * pr.QS + pr.self];
+      if (dfree[d] && e >= 0 && q > 0) {
+        const int r = d * G + (int)fdiv((uint32_t)(idx - d * I), pr.fPN);
+        atomicOr(&bm[e * pr.RW + (r >> 5)], 1u << (r & 31));
+        atomicAdd(&sendl[r], q);
+      }
     }
     lds_barrier();
   }
@@ -2767,36 +2780,36 @@ __device__ __forceinline__ void single_plan(const Plan &p, const SingleState &t,
   // until the hook has released the chunks.
   constexpr bool defer = !IsNoHook<Published>::value;
   auto caller_outputs = [&]() {
-    for (int i = tid; i < R * p.N; i += nt) {
-      const int r = (int)fdiv((uint32_t)i, p.fN), t2 = i - r * p.N;
-      p.slots_out[i] = t2 < used[r] ? slots[r * Neff + t2] : -1;
+    for (int i = tid; i < R * pr.N; i += nt) {
+      const int r = (int)fdiv((uint32_t)i, pr.fN), t2 = i - r * pr.N;
+      pr.slots_out[i] = t2 < used[r] ? slots[r * Neff + t2] : -1;
     }
-    for (int r = tid; r < R; r += nt) p.send_out[r] = sendl[r];
+    for (int r = tid; r < R; r += nt) pr.send_out[r] = sendl[r];
     if (tid == 0) {
       const uint32_t fin = (uint32_t)misc[45];
-      if (or_status) atomicOr(reinterpret_cast<unsigned *>(p.status_out), fin);
-      else p.status_out[0] = (int32_t)fin;
-      p.status_out[1] = misc[12];
+      if (or_status) atomicOr(reinterpret_cast<unsigned *>(pr.status_out), fin);
+      else pr.status_out[0] = (int32_t)fin;
+      pr.status_out[1] = misc[12];
     }
   };
   if constexpr (!defer) {
-    for (int i = tid; i < R * p.N; i += nt) {
-      const int r = (int)fdiv((uint32_t)i, p.fN), t2 = i - r * p.N;
-      p.slots_out[i] = t2 < used[r] ? slots[r * Neff + t2] : -1;
+    for (int i = tid; i < R * pr.N; i += nt) {
+      const int r = (int)fdiv((uint32_t)i, pr.fN), t2 = i - r * pr.N;
+      pr.slots_out[i] = t2 < used[r] ? slots[r * Neff + t2] : -1;
     }
-    for (int r = tid; r < R; r += nt) p.send_out[r] = sendl[r];
+    for (int r = tid; r < R; r += nt) pr.send_out[r] = sendl[r];
   }
   STAMP(p, 6);
-  emit_instance_list(p, qcol, slots, used, bm, t.wt);
+  emit_instance_list(pr, qcol, slots, used, bm, t.wt);
   STAMP(p, 7);
   if (tid == 0) {
     const uint32_t fin = (uint32_t)misc[0] | (gst & TOPOEP_ST_RANGE);
-    p.ctrl[kCtrlFinal] = fin;
+    pr.ctrl[kCtrlFinal] = fin;
     misc[45] = (int)fin;   // (kept in LDS past the hook)
     if constexpr (!defer) {
-      if (or_status) atomicOr(reinterpret_cast<unsigned *>(p.status_out), fin);
-      else p.status_out[0] = (int32_t)fin;
-      p.status_out[1] = misc[12];
+      if (or_status) atomicOr(reinterpret_cast<unsigned *>(pr.status_out), fin);
+      else pr.status_out[0] = (int32_t)fin;
+      pr.status_out[1] = misc[12];
     }
   }
   published();
@@ -2901,7 +2914,7 @@ __device__ __forceinline__ void swap_self_row(const Plan &p, const SingleState &
 // The same steps with every domain's state in the LDS of one CU; each
 // domain's refinement runs on its own wave.  Used when Omega and all q
 // columns fit in LDS.  Workgroups beyond the first compute the histogram
-// blocks' offsets for the reroute.  Form: kRefineReg or kRefineLds, whichever
+// blocks' offsets for the reroute.  Form: kRefinePairs or kRefineLds, whichever
 // the shape takes (both in one kernel spilled registers).
 template <int Form>
 __global__ __launch_bounds__(1024) void solve_single_kernel(Plan p0) {
@@ -3379,24 +3392,23 @@ __device__ __forceinline__ void fused_solver(const Plan &p, int *sm) {
   bool planned = stands;
   // a plan that does not stand: its status bits go (a chunk's SYNC stays)
   if (spec && !stands && tid == 0) atomicAnd(reinterpret_cast<unsigned *>(p.status_out), TOPOEP_ST_SYNC);
-  if (stands) {
-    // the speculative plan stands (Omega' = Omega) with its status
-  } else if (synced && verdict == kVerdictSame) {
-    single_plan<Form>(p, t, gst0, true);   // Omega itself refused: blank outputs
-  } else if (synced) {
-    // row self differs from the histogram, or a bad id: plan again from
-    // Omega' (row self = the histogram) on fresh state
-    single_init(p, t);
-    lds_barrier();
-    read_histogram(p, p.ghist + (int64_t)(t.misc[40] & 1) * (E + 1), t.hs, t.misc);
-    if (tid == 0 && neg0) atomicOr(reinterpret_cast<unsigned *>(&t.misc[0]), neg0);
-    swap_self_row(p, t);
-    uint32_t gst = (uint32_t)t.misc[0];
-    if (out_of_range(p, total0 + *reinterpret_cast<const unsigned long long *>(t.misc + 8))) gst |= TOPOEP_ST_RANGE;
+  // the speculative plan stands (Omega' = Omega) with its status, or: Omega
+  // itself refused or a wait given up (blank outputs); or row self differs
+  // from the histogram, or a bad id: plan again from Omega' (row self = the
+  // histogram) on fresh state
+  if (!stands) {
+    uint32_t gst = synced ? gst0 : TOPOEP_ST_SYNC;
+    if (synced && verdict != kVerdictSame) {
+      single_init(p, t);
+      lds_barrier();
+      read_histogram(p, p.ghist + (int64_t)(t.misc[40] & 1) * (E + 1), t.hs, t.misc);
+      if (tid == 0 && neg0) atomicOr(reinterpret_cast<unsigned *>(&t.misc[0]), neg0);
+      swap_self_row(p, t);
+      gst = (uint32_t)t.misc[0];
+      if (out_of_range(p, total0 + *reinterpret_cast<const unsigned long long *>(t.misc + 8))) gst |= TOPOEP_ST_RANGE;
+      planned = !(gst & kNoPlan);
+    }
     single_plan<Form>(p, t, gst, true);
-    planned = !(gst & kNoPlan);
-  } else {
-    single_plan<Form>(p, t, TOPOEP_ST_SYNC, true);
   }
   if (!early) {
     if (planned && p.offs_out) solver_send_offsets(p, t.sendl);
@@ -3849,6 +3861,10 @@ int resident_capacity(const void *fn, int threads, size_t lds) {
 }
 
 const void *fused_fn(int ipt, int form);
+
+int refine_form(const Plan &p) {
+  return !p.lanes ? kRefineLds : (refine_in_pairs(p.G, p.PN) ? kRefinePairs : kRefineLanes);
+}
 const void *domains_fn(int ipt);
 
 // Validate the arguments and fill the plan's sizes, launch shape and
@@ -3935,6 +3951,22 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
   const int64_t multi_words = (int64_t)domain_lds(q).words;
   const bool single_fits = single_words * 4 <= kLdsLimit;
   const bool multi_fits = multi_words * 4 <= kLdsLimit;
+  // the lane forms where LDS has room for its words (they take the place of
+  // the other form's unless a domain has more instances than experts) beside
+  // all that decides which solver runs (1 KiB for the one-launch kernel's
+  // static LDS)
+  int64_t single_lds_words = single_words, multi_lds_words = multi_words;
+  bool single_lanes = false, multi_lanes = false;
+  if (refine_in_lanes(q.G, q.PN) && !general) {
+    q.lanes = 1;
+    const int64_t sw = (int64_t)single_lds(q).words, mw = (int64_t)domain_lds(q).words;
+    q.lanes = 0;
+    single_lanes = sw * 4 + 1024 <= kLdsLimit;
+    multi_lanes = mw * 4 + 1024 <= kLdsLimit;
+    if (single_lanes) single_lds_words = sw;
+    if (multi_lanes) multi_lds_words = mw;
+  }
+  q.lanes = single_lanes ? 1 : 0;   // (of the single-workgroup solver until the per-domain one is chosen)
 
   // one launch: the single-workgroup solver plus at most kMaxFusedBlocks
   // chunk workgroups of st threads holding ipt ids per thread
@@ -3952,11 +3984,11 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
     }
     const int64_t chunk_words = (int64_t)chunk_lds(q, st).words;
     // (1 KiB left for the kernel's static LDS, which __syncthreads_or uses)
-    const int64_t fused_words = single_words > chunk_words ? single_words : chunk_words;
+    const int64_t fused_words = single_lds_words > chunk_words ? single_lds_words : chunk_words;
     bool fused_ok = single_fits && ipt > 0 && fused_words * 4 + 1024 <= kLdsLimit;
     // every workgroup of the launch resident at once (they wait on each other)
     if (fused_ok)
-      fused_ok = nbf + 1 <= resident_capacity(fused_fn(ipt, refine_form(q.G, q.I, q.PN)), st, (size_t)fused_words * 4);
+      fused_ok = nbf + 1 <= resident_capacity(fused_fn(ipt, refine_form(q)), st, (size_t)fused_words * 4);
     if (solver == 3 && !fused_ok) return TOPOEP_ELIMIT;
     if (general && solver == 3) return TOPOEP_EINVAL;   // the general model runs the per-domain solver
     if (fused_ok && !general && (solver == 3 || solver == 0)) {
@@ -4031,7 +4063,8 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
     s.mode = single_fits ? 1 : 2;
   }
   if (s.st == 0) s.st = s.mode == 1 ? 1024 : 512;
-  s.lds_solve = (size_t)(s.mode == 1 ? single_words : multi_words) * 4;
+  if (s.mode == 2) q.lanes = multi_lanes ? 1 : 0;
+  s.lds_solve = (size_t)(s.mode == 1 ? single_lds_words : multi_lds_words) * 4;
   q.n_solvers = s.mode == 1 ? 1 : imin(q.M, kMaxSolveGroups);
   // the per-domain solver's workgroups meet at a grid barrier: all resident
   if (s.mode == 2 && q.n_solvers > resident_capacity(s.st <= 512 ? reinterpret_cast<const void *>(solve_kernel<512>)
@@ -4049,7 +4082,7 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
       const int64_t per = (int64_t)kOneThreads * ipt;
       const int64_t nbo = q.n > 0 ? (q.n + per - 1) / per : 1;
       const int64_t chunk_words = (int64_t)chunk_lds(q, kOneThreads).words;
-      const int64_t words = multi_words > chunk_words ? multi_words : chunk_words;
+      const int64_t words = multi_lds_words > chunk_words ? multi_lds_words : chunk_words;
       if (nbo > kFusedBlocks && ipt < 8) continue;
       if (words * 4 + 1024 > kLdsLimit || q.n_solvers + nbo > kMaxOneGroups) continue;
       if (4 * (q.n_solvers + nbo) > resident_capacity(domains_fn(ipt), kOneThreads, (size_t)words * 4)) continue;
@@ -4137,8 +4170,8 @@ std::atomic<bool> g_attrs_set{false};
 
 template <int IPT>
 const void *fused_fn_ipt(int form) {
-  return form == kRefinePairs ? reinterpret_cast<const void *>(plan_fused_kernel<IPT, kRefinePairs>)
-         : form == kRefineReg ? reinterpret_cast<const void *>(plan_fused_kernel<IPT, kRefineReg>)
+  return form == kRefineLanes ? reinterpret_cast<const void *>(plan_fused_kernel<IPT, kRefineLanes>)
+         : form == kRefinePairs ? reinterpret_cast<const void *>(plan_fused_kernel<IPT, kRefinePairs>)
                               : reinterpret_cast<const void *>(plan_fused_kernel<IPT, kRefineLds>);
 }
 
@@ -4167,20 +4200,21 @@ void set_attrs() {
   allow_lds(reroute_kernel<2, false>);
   allow_lds(solve_kernel<512>);
   allow_lds(solve_kernel<1024>);
-  allow_lds(solve_single_kernel<kRefineReg>);
+  allow_lds(solve_single_kernel<kRefineLanes>);
+  allow_lds(solve_single_kernel<kRefinePairs>);
   allow_lds(solve_single_kernel<kRefineLds>);
   allow_lds(plan_fused_kernel<1, kRefineLds>);
-  allow_lds(plan_fused_kernel<1, kRefineReg>);
   allow_lds(plan_fused_kernel<1, kRefinePairs>);
+  allow_lds(plan_fused_kernel<1, kRefineLanes>);
   allow_lds(plan_fused_kernel<2, kRefineLds>);
-  allow_lds(plan_fused_kernel<2, kRefineReg>);
   allow_lds(plan_fused_kernel<2, kRefinePairs>);
+  allow_lds(plan_fused_kernel<2, kRefineLanes>);
   allow_lds(plan_fused_kernel<4, kRefineLds>);
-  allow_lds(plan_fused_kernel<4, kRefineReg>);
   allow_lds(plan_fused_kernel<4, kRefinePairs>);
+  allow_lds(plan_fused_kernel<4, kRefineLanes>);
   allow_lds(plan_fused_kernel<8, kRefineLds>);
-  allow_lds(plan_fused_kernel<8, kRefineReg>);
   allow_lds(plan_fused_kernel<8, kRefinePairs>);
+  allow_lds(plan_fused_kernel<8, kRefineLanes>);
   allow_lds(empty_kernel);
   // (an attribute a kernel refuses must not linger as the caller's error)
   (void)hipGetLastError();
@@ -4204,8 +4238,11 @@ void launch_reroute(const Plan &p, const Shape &s, hipStream_t st) {
 
 void launch_solve(const Plan &p, const Shape &s, hipStream_t st) {
   const dim3 g(s.solve_groups), b(s.st);
-  if (s.mode == 1 && refine_form(p.G, p.I, p.PN) != kRefineLds)
-    hipLaunchKernelGGL((solve_single_kernel<kRefineReg>), g, b, s.lds_solve, st, p);
+  const int form = refine_form(p);
+  if (s.mode == 1 && form == kRefineLanes)
+    hipLaunchKernelGGL((solve_single_kernel<kRefineLanes>), g, b, s.lds_solve, st, p);
+  else if (s.mode == 1 && form == kRefinePairs)
+    hipLaunchKernelGGL((solve_single_kernel<kRefinePairs>), g, b, s.lds_solve, st, p);
   else if (s.mode == 1)
     hipLaunchKernelGGL((solve_single_kernel<kRefineLds>), g, b, s.lds_solve, st, p);
   else if (s.st <= 512) hipLaunchKernelGGL(solve_kernel<512>, g, b, s.lds_solve, st, p);
@@ -4214,14 +4251,14 @@ void launch_solve(const Plan &p, const Shape &s, hipStream_t st) {
 
 template <int IPT>
 void launch_fused_ipt(int form, dim3 g, dim3 b, size_t lds, hipStream_t st, const Plan &p) {
-  if (form == kRefinePairs) hipLaunchKernelGGL((plan_fused_kernel<IPT, kRefinePairs>), g, b, lds, st, p);
-  else if (form == kRefineReg) hipLaunchKernelGGL((plan_fused_kernel<IPT, kRefineReg>), g, b, lds, st, p);
+  if (form == kRefineLanes) hipLaunchKernelGGL((plan_fused_kernel<IPT, kRefineLanes>), g, b, lds, st, p);
+  else if (form == kRefinePairs) hipLaunchKernelGGL((plan_fused_kernel<IPT, kRefinePairs>), g, b, lds, st, p);
   else hipLaunchKernelGGL((plan_fused_kernel<IPT, kRefineLds>), g, b, lds, st, p);
 }
 
 void launch_fused(const Plan &p, const Shape &s, hipStream_t st) {
   const dim3 g(p.nb + 1), b(s.st);
-  const int form = refine_form(p.G, p.I, p.PN);
+  const int form = refine_form(p);
   switch (s.ipt) {
     case 1: launch_fused_ipt<1>(form, g, b, s.lds_fused, st, p); break;
     case 2: launch_fused_ipt<2>(form, g, b, s.lds_fused, st, p); break;

@@ -202,3 +202,36 @@ def test_per_domain_one_launch_dispatch(name):
     """Receive counts, send offsets and slots of the one-launch plan."""
     from test_gpu_dispatch import check
     check(_domain_case(name), "per-domain one launch %s" % name)
+
+
+@pytest.mark.parametrize("solver", sorted(SOLVERS))
+@pytest.mark.parametrize("R,G,P,N,cI", [
+    (8, 8, 7, 1, 1), (8, 8, 8, 1, 1),       # 8 and 9 instances per rank: one and two pairs a lane
+    (16, 8, 13, 3, 1), (16, 8, 13, 4, 1),   # 16 and 17: pairs, one lane per instance
+    (4, 2, 62, 2, 1), (4, 4, 63, 2, 0),     # 64 and 65: one and two rounds of instances
+    (10, 5, 3, 3, 2), (72, 8, 2, 3, 1),     # ranks that fill no group of lanes; more than 64 sources
+    (24, 12, 10, 4, 1), (24, 12, 10, 5, 1),  # 14 and 15 instances on more than 8 ranks: lanes, LDS form
+])
+def test_refinement_forms(R, G, P, N, cI, solver):
+    """Moves at the edges of the refinement's forms, with hot experts on one
+    rank of each node, equal loads in half of the cases."""
+    from test_gpu_parity import topoep
+    E = R * P
+    for seed in range(4):
+        rng = np.random.default_rng(1000 * R + 10 * P + seed)
+        omega = rng.integers(0, 30, size=(R, E)).astype(np.int32)
+        hot = rng.integers(0, R // G, size=3) * G * P + rng.integers(0, P, size=3)
+        omega[:, hot] += rng.integers(100, 900, size=(R, 3)).astype(np.int32)
+        if seed % 2:
+            omega = omega // 16 * 16
+        s = int(rng.integers(R))
+        tk = np.repeat(np.arange(E, dtype=np.int32), omega[s]).reshape(-1, 1)
+        W = int(omega.sum()) * 2   # few stage-1 replicas: slots stay free
+        try:
+            got, _ = both(R, G, E, s, cI, 8, 64, W, N, omega, np.ascontiguousarray(tk), launch=SOLVERS[solver],
+                          what="forms R=%d G=%d P=%d N=%d seed %d %s" % (R, G, P, N, seed, solver))
+        except topoep.TopoepError as ex:
+            if ex.rc != topoep.ELIMIT:
+                raise
+            pytest.skip("the %s solver's state does not fit one workgroup's LDS here" % solver)
+        assert got["move_count"] > 0

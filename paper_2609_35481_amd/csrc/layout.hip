@@ -5,28 +5,32 @@
 // is (the per-destination counts the dispatch consumes, Section 4.3).
 //
 // One launch; one pass over token_dest for a chunk of one tile per
-// workgroup, two passes for longer chunks (at most 256 workgroups):
+// workgroup, two passes for longer chunks (at most 512 workgroups):
 //   - a one-tile workgroup holds its assignments in registers and ranks
 //     them among equal destinations inside each wave (ballots over the
 //     destination bits give each lane its peers), then scans the per-wave
 //     counts across waves in LDS; a longer chunk is cut into one contiguous
 //     part per wave, each wave only counts its part's destinations here
-//     (LDS atomics), and after the look-back ranks its part step by step
+//     (LDS atomics), and once the earlier counts are in ranks its part step by step
 //     from its own running base, reading the assignments again, with no
 //     workgroup barrier;
-//   - it publishes its per-destination counts (flag 1), then looks back
-//     over up to 64 predecessors at a time: wave 0 waits for their flags in
-//     parallel and stops at the nearest one whose inclusive prefix is
-//     published (flag 2), the whole workgroup sums their counts per
-//     destination, and (when the grid is longer than one window plus
-//     workgroup 0) the workgroup publishes its own inclusive prefix (flag
-//     2).  Workgroup 0 publishes its counts as its inclusive prefix;
+//   - it publishes its per-destination counts; workgroups form groups of
+//     kLayoutGroup, and the last of a group publishes the group's total in
+//     their place.  A workgroup then sums the counts of the earlier ones of
+//     its group and the totals of the earlier groups, at most
+//     kLayoutGroup - 1 rows of each;
 //   - slot = send_offsets[dest] + (earlier workgroups) + (earlier waves, or
 //     their parts) + (earlier steps of the wave's part) + (rank in the
 //     wave).
-// The waits are bounded and only on lower workgroup indices, which are
-// dispatched first.  The last workgroup to finish its look-back (a ticket)
-// clears every flag, so the workspace is zero again for the next call.
+// A published count is one word, the count + 1, stored and polled with relaxed
+// agent-scope atomics: it is valid by itself, so no fence writes back or
+// invalidates an L2 under the other workgroups.  (Flags with release and
+// acquire cost more than the counting and ranking: R = 64, 4.2 M ids 29.2 us,
+// 20.4 now; 0.5 M ids 16.0, 9.3 now.  Every workgroup summing all earlier
+// rows: 45 us.)  The waits are bounded and only on lower workgroup indices,
+// which are dispatched first.  The last workgroup of a group to finish (a
+// ticket) clears the group's counts, the last of all the totals, so the
+// workspace is zero again for the next call.
 // All arithmetic is integer and no atomic decides an order.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -40,8 +44,8 @@ using namespace topoep_dev;
 
 constexpr int kLayoutThreads = 1024;
 constexpr int kLayoutMaxRanks = 1024;   // per-wave counts of 16 waves fit 64 KB of LDS
-constexpr int kLayoutWindow = 64;       // predecessors examined per look-back step
-constexpr int kLayoutBlocks = 256;      // workgroups at most (longer chunks take several tiles)
+constexpr int kLayoutGroup = 16;        // workgroups whose counts one total stands for
+constexpr int kLayoutBlocks = 512;      // workgroups at most (longer chunks take several tiles)
 constexpr uint32_t kLayoutSpin = 1u << 24;
 constexpr int kLayoutCtrlBytes = 256;
 
@@ -53,10 +57,8 @@ struct Layout {
   int32_t *offs_out;   // [R + 1]
   int32_t *slot_out;   // [n]
   int32_t *status;     // [1] or null: TOPOEP_ST_SYNC when a wait gave up
-  uint32_t *agg;       // [nb][R] counts of each workgroup
-  uint32_t *incl;      // [nb][R] inclusive prefixes over workgroups
-  uint32_t *flags;     // [nb] 0, 1 counts published, 2 inclusive prefix published
-  uint32_t *ctrl;      // [0] finish ticket
+  uint32_t *rows;      // [nb][R] a workgroup's counts + 1, or its group's total + 1
+  uint32_t *ctrl;      // finish tickets: [0] of all workgroups, [1 + g] of group g
   uint32_t spin_limit;
 };
 
@@ -126,8 +128,8 @@ __global__ __launch_bounds__(kLayoutThreads) void layout_kernel(Layout L) {
   const int64_t hi = lo + L.chunk < L.n ? lo + L.chunk : L.n;
   const int64_t tile = (int64_t)nt * IPT;
   // a chunk of one tile keeps its ids and ranks in registers across the
-  // look-back; a longer chunk counts its tiles first (pass 1) and ranks them
-  // after the look-back (pass 2), reading the ids twice
+  // wait for the earlier workgroups; a longer chunk counts its tiles first (pass 1) and ranks them
+  // after it (pass 2), reading the ids twice
   const bool multi = L.chunk > tile;
   const int64_t wofs = (int64_t)wave * 64 * IPT + lane;
   // a longer chunk: wave w owns the w-th of nw equal contiguous parts, in
@@ -141,9 +143,10 @@ __global__ __launch_bounds__(kLayoutThreads) void layout_kernel(Layout L) {
       v[i] = idx < whi ? L.dest[idx] : -1;
     }
   };
-  // workgroups whose look-back window reaches workgroup 0 never need the
-  // inclusive prefix of another one
-  const bool publish_incl = L.nb > kLayoutWindow + 1;
+  const int gi = b % kLayoutGroup, grp = b / kLayoutGroup;
+  auto publish = [&](int r, int count) {
+    __hip_atomic_store(L.rows + (int64_t)b * R + r, (uint32_t)count + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
   int *mywc = wc + wave * R;
 
   int dv[IPT], lr[IPT];
@@ -216,10 +219,8 @@ __global__ __launch_bounds__(kLayoutThreads) void layout_kernel(Layout L) {
   lds_barrier();
   scan_waves(R, nw, wc, agg);
   lds_barrier();
-  for (int r = tid; r < R; r += nt) {
-    L.agg[(int64_t)b * R + r] = (uint32_t)agg[r];
-    if (b == 0) L.incl[r] = (uint32_t)agg[r];
-  }
+  if (gi != kLayoutGroup - 1)
+    for (int r = tid; r < R; r += nt) publish(r, agg[r]);
   // send offsets (exclusive prefix of the send counts) by wave 0
   if (wave == 0) {
     const int per = (R + 63) / 64, a0 = imin(R, lane * per), a1 = imin(R, a0 + per);
@@ -233,68 +234,46 @@ __global__ __launch_bounds__(kLayoutThreads) void layout_kernel(Layout L) {
     }
     if (lane == 63) offs[R] = acc;
   }
-  drain_then_barrier();
-  if (tid == 0)
-    __hip_atomic_store(L.flags + b, b == 0 ? 2u : 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  lds_barrier();
   if (b == 0 && L.offs_out)
     for (int r = tid; r <= R; r += nt) L.offs_out[r] = offs[r];
 
-  // look-back over the workgroups before b
-  bool ok = true;
-  int jhi = b - 1;
-  while (jhi >= 0) {
-    if (wave == 0) {
-      const int cnt = imin(kLayoutWindow, jhi + 1);
-      const int j = jhi - lane;
-      uint32_t f = 0;
-      bool gave_up = false;
-      if (lane < cnt) {
-        uint32_t it = 0;
-        while ((f = __hip_atomic_load(L.flags + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0u) {
-          if (++it > L.spin_limit) {
+  // the earlier workgroups' counts: thread (g0, r0) sums every tr-th row of
+  // destination r0, four words in flight
+  const int tr = nt / R, g0 = tid / R, r0 = tid - g0 * R;   // (R <= nt)
+  bool gave_up = false;
+  auto add_rows = [&](int cnt, int first, int stride) {
+    int sum = 0;
+    for (int q = g0; q < cnt && g0 < tr; q += 4 * tr) {
+      uint32_t v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        v[u] = __hip_atomic_load(L.rows + (int64_t)(first + imin(q + u * tr, cnt - 1) * stride) * R + r0,
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (q + u * tr >= cnt) continue;
+        for (uint32_t it = 0; v[u] == 0u; ++it) {
+          if (it >= L.spin_limit) {
             gave_up = true;
             break;
           }
           __builtin_amdgcn_s_sleep(1);
+          v[u] = __hip_atomic_load(L.rows + (int64_t)(first + (q + u * tr) * stride) * R + r0, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
         }
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      const uint64_t done = __ballot(lane < cnt && f == 2u);
-      const bool bad = __ballot(gave_up) != 0;
-      // the nearest predecessor with an inclusive prefix, else the window's end
-      const int stop = done ? jhi - (__ffsll((long long)done) - 1) : jhi - cnt + 1;
-      if (lane == 0) {
-        misc[0] = stop;
-        misc[1] = done != 0;
-        misc[2] = bad;
+        sum += v[u] ? (int)(v[u] - 1u) : 0;
       }
     }
-    __syncthreads();
-    const int stop = misc[0];
-    const bool found = misc[1] != 0;
-    if (misc[2]) {
-      ok = false;
-      break;
-    }
-    // excl[r] += counts of stop+1 .. jhi, plus the inclusive prefix (or the
-    // counts) of stop
-    const int span = jhi - stop + 1;
-    for (int x = tid; x < span * R; x += nt) {
-      const int jj = x / R, r = x - jj * R;
-      const int j = stop + jj;
-      const uint32_t v = (j == stop && found) ? L.incl[(int64_t)j * R + r] : L.agg[(int64_t)j * R + r];
-      if (v) atomicAdd(&excl[r], (int)v);
-    }
-    lds_barrier();
-    if (found) break;
-    jhi = stop - 1;
-  }
-  if (b > 0 && publish_incl) {
-    for (int r = tid; r < R; r += nt) L.incl[(int64_t)b * R + r] = (uint32_t)(excl[r] + agg[r]);
-    drain_then_barrier();
-    if (tid == 0)
-      __hip_atomic_store(L.flags + b, 2u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-  }
+    if (sum) atomicAdd(&excl[r0], sum);
+  };
+  add_rows(gi, grp * kLayoutGroup, 1);
+  lds_barrier();
+  if (gi == kLayoutGroup - 1)   // (a total short of a word that never came is the waiters' SYNC too)
+    for (int r = tid; r < R; r += nt) publish(r, excl[r] + agg[r]);
+  lds_barrier();
+  add_rows(grp, kLayoutGroup - 1, kLayoutGroup);
+  const bool ok = __syncthreads_or(gave_up) == 0;
   if (!multi) {
 #pragma unroll
     for (int i = 0; i < IPT; ++i) {
@@ -328,19 +307,29 @@ __global__ __launch_bounds__(kLayoutThreads) void layout_kernel(Layout L) {
       }
     }
   }
-  // this workgroup has read every flag it needs: the last one to get here
-  // clears them all for the next call
+  // this workgroup has read every word it needs: the last one of its group to
+  // get here clears the group's counts, the last one of all the totals
+  const int gsize = imin(kLayoutGroup, L.nb - grp * kLayoutGroup);
   if (tid == 0) {
-    const uint32_t t = __hip_atomic_fetch_add(L.ctrl, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-    misc[3] = t + 1u == (uint32_t)L.nb;
     if (!ok && L.status) atomicOr(reinterpret_cast<unsigned *>(L.status), TOPOEP_ST_SYNC);
+    misc[4] = __hip_atomic_fetch_add(L.ctrl + 1 + grp, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+              (uint32_t)gsize;
+    misc[5] = __hip_atomic_fetch_add(L.ctrl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (uint32_t)L.nb;
+    if (misc[4]) __hip_atomic_store(L.ctrl + 1 + grp, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (misc[5]) __hip_atomic_store(L.ctrl, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
-  if (misc[3]) {
-    for (int j = tid; j < L.nb; j += nt)
-      __hip_atomic_store(L.flags + j, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (tid == 0) __hip_atomic_store(L.ctrl, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  auto clear = [&](int64_t word) {
+    __hip_atomic_store(L.rows + word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  if (misc[4]) {
+    const int64_t base = (int64_t)grp * kLayoutGroup * R;
+    const int n = imin(gsize, kLayoutGroup - 1) * R;
+    for (int i = tid; i < n; i += nt) clear(base + i);
   }
+  if (misc[5])
+    for (int g = 0; g < L.nb / kLayoutGroup; ++g)
+      for (int r = tid; r < R; r += nt) clear((int64_t)(g * kLayoutGroup + kLayoutGroup - 1) * R + r);
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -358,7 +347,7 @@ struct LayoutShape {
 
 // Sizes, launch shape and workspace layout (pointers stay null when ws is).
 int layout_setup(const topoep_topology *t, int32_t T, int32_t k, Layout *out, LayoutShape *sh,
-                 size_t *ws_bytes, char *ws) {
+                 size_t *ws_bytes, char *ws, size_t max_ws = SIZE_MAX) {
   if (!t) return TOPOEP_EINVAL;
   const int R = t->num_ranks;
   if (R <= 0 || T < 0 || k < 1 || (int64_t)T * k > 0x7FFFFFFF) return TOPOEP_EINVAL;
@@ -368,12 +357,20 @@ int layout_setup(const topoep_topology *t, int32_t T, int32_t k, Layout *out, La
   L.nbits = ceil_log2(R);
   L.n = (int64_t)T * k;
   // ids per thread, then whole tiles per workgroup so that the grid stays
-  // within kLayoutBlocks workgroups, half that up to 2^21 ids (the look-back
-  // chain grows with the grid; on MI355X these bounds measured fastest)
-  const int ipt = L.n <= (int64_t)kLayoutThreads * 16 ? 1 : (L.n <= (int64_t)1 << 20 ? 4 : 8);
+  // within max_blocks: one id while 64 workgroups hold them, two up to 256 (R
+  // = 64, 32 K ids: 6.5 us, four ids 7.3; 131 K: 7.4, 8.0), more ids in one
+  // tile of each of 256 workgroups up to 2^21 (two tiles of 128: 2.1 M ids
+  // 16.8 us, 13.8); 512 workgroups beyond, where two fit a CU (34 M ids 105
+  // us, 94; R = 256, one per CU: 117, 123).  A workspace without room for so
+  // many workgroups' counts gets four ids per thread.
+  const size_t lds = (size_t)layout_lds(R, kLayoutThreads).words * 4;
+  int ipt = L.n <= (int64_t)kLayoutThreads * 64 ? 1 : (L.n <= (int64_t)kLayoutThreads * 256 ? 2 : 4);
+  if (L.n > (int64_t)1 << 20) ipt = 8;
+  if (ipt < 4 && max_ws < kLayoutCtrlBytes + align256((size_t)((L.n + kLayoutThreads * ipt - 1) / (kLayoutThreads * ipt)) * R * 4))
+    ipt = L.n <= (int64_t)kLayoutThreads * 16 ? 1 : 4;
   const int64_t tile = (int64_t)kLayoutThreads * ipt;
   const int64_t tiles = L.n > 0 ? (L.n + tile - 1) / tile : 1;
-  const int64_t max_blocks = L.n <= ((int64_t)1 << 21) ? kLayoutBlocks / 2 : kLayoutBlocks;
+  const int64_t max_blocks = L.n > ((int64_t)1 << 21) && lds <= 80 * 1024 ? kLayoutBlocks : kLayoutBlocks / 2;
   L.chunk = tile * ((tiles + max_blocks - 1) / max_blocks);
   const int64_t nb = L.n > 0 ? (L.n + L.chunk - 1) / L.chunk : 1;
   if (nb > (1 << 20)) return TOPOEP_ELIMIT;
@@ -386,18 +383,14 @@ int layout_setup(const topoep_topology *t, int32_t T, int32_t k, Layout *out, La
     return o;
   };
   const size_t o_ctrl = take(kLayoutCtrlBytes);
-  const size_t o_flag = take((size_t)L.nb * 4);
-  const size_t o_agg = take((size_t)L.nb * R * 4);
-  const size_t o_incl = take((size_t)L.nb * R * 4);
+  const size_t o_rows = take((size_t)L.nb * R * 4);
   *ws_bytes = off;
   if (ws) {
     L.ctrl = reinterpret_cast<uint32_t *>(ws + o_ctrl);
-    L.flags = reinterpret_cast<uint32_t *>(ws + o_flag);
-    L.agg = reinterpret_cast<uint32_t *>(ws + o_agg);
-    L.incl = reinterpret_cast<uint32_t *>(ws + o_incl);
+    L.rows = reinterpret_cast<uint32_t *>(ws + o_rows);
   }
   sh->ipt = ipt;
-  sh->lds = (size_t)layout_lds(R, kLayoutThreads).words * 4;
+  sh->lds = lds;
   *out = L;
   return TOPOEP_OK;
 }
@@ -432,13 +425,11 @@ int topoep_dispatch_layout(const topoep_topology *topo, const int32_t *token_des
   Layout L;
   LayoutShape sh;
   size_t need = 0;
-  int rc = layout_setup(topo, T, k, &L, &sh, &need, nullptr);
+  const int rc = layout_setup(topo, T, k, &L, &sh, &need, static_cast<char *>(workspace), workspace_bytes);
   if (rc != TOPOEP_OK) return rc;
   if (!send_counts || !send_offsets || !workspace || (T > 0 && (!token_dest || !token_slot)))
     return TOPOEP_EINVAL;
   if (workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255)) return TOPOEP_EWORKSPACE;
-  rc = layout_setup(topo, T, k, &L, &sh, &need, static_cast<char *>(workspace));
-  if (rc != TOPOEP_OK) return rc;
   L.dest = token_dest;
   L.send = send_counts;
   L.offs_out = send_offsets;

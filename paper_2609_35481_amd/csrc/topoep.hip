@@ -3597,6 +3597,11 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
   }
   // the generation as the solver left it: the histogram buffer to add to
   const uint32_t gread = __hip_atomic_load(&p.ctrl[kCtrlGen], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // Counting by LDS atomics lets the chunk arrive before its ids are ranked
+  // (Stress-like, eight ids per thread: 2.6 us after the start, 5.1 ranked
+  // first); up to 32 experts they meet on too few words, and the short ranks
+  // come first (R = 16, E = 16, 75 K ids: 10.8 us counted first, 10.3).
+  const bool rank_first = p.nbits <= 5;
   int *mywc = wc + wave * E;
   for (int e = lane; e < E; e += 64) mywc[e] = 0;
   wave_sync();
@@ -3607,7 +3612,8 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
     const bool inr = idx < hi;
     const bool valid = (unsigned)ev[i] < (unsigned)E;   // (ev is -1 past the end)
     bad |= (inr && !valid) ? 1 : 0;
-    if (valid) atomicAdd(&mywc[ev[i]], 1);
+    if (rank_first) lr[i] = wave_rank(ev[i], valid, p.nbits, mywc);
+    else if (valid) atomicAdd(&mywc[ev[i]], 1);
   }
   bad = __syncthreads_or(bad);
   // publish the chunk's counts; wc becomes each wave's offset in the chunk
@@ -3656,7 +3662,11 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
   // the ids' occurrence indices in the chunk (each wave counts on from its
   // offset, in its own row), while the other chunks arrive
 #pragma unroll
-  for (int i = 0; i < IPT; ++i) lr[i] = wave_rank(ev[i], (unsigned)ev[i] < (unsigned)E, p.nbits, mywc);
+  for (int i = 0; i < IPT; ++i) {
+    const bool valid = (unsigned)ev[i] < (unsigned)E;
+    if (rank_first) lr[i] += mywc[valid ? ev[i] : 0];
+    else lr[i] = wave_rank(ev[i], valid, p.nbits, mywc);
+  }
   // every count is written: this chunk's first occurrence index per expert
   bool ok = wait_flag(p, b, 1, gen + 1u, flag);
   if (ok) chunk_offsets(p, b, p.ghist + (gen & 1u) * (E + 1), run, gs);
@@ -4310,14 +4320,12 @@ int enqueue(int stage_mask, const topoep_topology *topo, const int32_t *global_l
   Shape s;
   size_t need = 0;
   const bool general = costs != nullptr;
-  int rc = setup(topo, T, k, N, launch, &p, &s, &need, nullptr, general, workspace_bytes);
+  const int rc = setup(topo, T, k, N, launch, &p, &s, &need, static_cast<char *>(workspace), general, workspace_bytes);
   if (rc != TOPOEP_OK) return rc;
   if (!global_load || !send_counts || !status || !workspace) return TOPOEP_EINVAL;
   if ((int64_t)topo->num_ranks * N > 0 && !replica_slots) return TOPOEP_EINVAL;
   if (T > 0 && (!local_topk || !token_dest)) return TOPOEP_EINVAL;
   if (workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255)) return TOPOEP_EWORKSPACE;
-  rc = setup(topo, T, k, N, launch, &p, &s, &need, static_cast<char *>(workspace), general, workspace_bytes);
-  if (rc != TOPOEP_OK) return rc;
   p.Cm = general ? costs->cost : nullptr;
   p.We = general ? costs->expert_bytes : nullptr;
   p.gl = global_load;

@@ -235,3 +235,57 @@ def test_refinement_forms(R, G, P, N, cI, solver):
                 raise
             pytest.skip("the %s solver's state does not fit one workgroup's LDS here" % solver)
         assert got["move_count"] > 0
+
+
+LAYOUT_SIZES = [1, 1024, 1025, 16 * 1024 + 1, 65536, 65537, 262144, 262145, 1 << 20, (1 << 20) + 1, 1 << 21,
+                (1 << 21) + 1, 4 * (1 << 20) + 3]
+
+
+def _layout(planner, R, n, seed, skew):
+    import oracle
+    from test_gpu_dispatch import layout_case
+    dest, send = layout_case(R, n, np.random.default_rng(seed), skew=skew)
+    d, s = torch.from_numpy(dest).cuda(), torch.from_numpy(send).cuda()
+    offs, slot = planner.layout(d, s)
+    torch.cuda.synchronize()
+    ref_offs, ref_slot = oracle.layout_ref(R, dest, send)
+    assert int(planner.status[0]) == 0
+    assert np.array_equal(offs.cpu().numpy(), ref_offs) and np.array_equal(slot.cpu().numpy(), ref_slot), (R, n)
+    return dest.shape
+
+
+@pytest.mark.parametrize("R", [1, 3, 64, 128, 160, 1024])
+def test_layout_edges(R):
+    """One, two, four and eight ids per thread, groups of 16 workgroups and
+    one more, 256 and 512 workgroups; twice on each workspace, which is zero
+    again after every call."""
+    from test_gpu_parity import DEV, topoep
+    for n in LAYOUT_SIZES:
+        p = None
+        for seed, skew in ((n, 0.0), (n + 1, 1.5)):
+            from test_gpu_dispatch import layout_case
+            T, k = layout_case(R, n, np.random.default_rng(seed), skew=skew)[0].shape
+            if p is None:
+                p = topoep.LayoutPlanner(topoep.topology(R, 1, R, 0, 1, 1, 1, 0), T, k, device=DEV)
+            _layout(p, R, n, seed, skew)
+        assert not bool(p._ws.any()), (R, n)
+
+
+def test_layout_one_workspace_many_sizes():
+    """A workspace of the largest size serves every smaller one in turn, and
+    one of a grid of four ids per thread is still enough for that grid."""
+    from test_gpu_parity import DEV, topoep
+    R = 48
+    topo = topoep.topology(R, 1, R, 0, 1, 1, 1, 0)
+    from test_gpu_dispatch import layout_case
+    shape = lambda n: layout_case(R, n, np.random.default_rng(1), skew=0.0)[0].shape  # noqa: E731
+    big = topoep.LayoutPlanner(topo, *shape(4 * (1 << 20) + 3), device=DEV)
+    for i, n in enumerate(LAYOUT_SIZES + LAYOUT_SIZES[::-1]):
+        p = topoep.LayoutPlanner(topo, *shape(n), device=DEV)
+        assert p.ws_bytes <= big.ws_bytes
+        p.ws_ptr, p.ws_bytes = big.ws_ptr, big.ws_bytes
+        _layout(p, R, n, i, 1.0)
+    n = 65536
+    p = topoep.LayoutPlanner(topo, *shape(n), device=DEV)
+    p.ws_bytes = 256 + 256 + 2 * (n // 4096 * R * 4)
+    _layout(p, R, n, 5, 1.0)

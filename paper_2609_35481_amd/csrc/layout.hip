@@ -26,8 +26,8 @@
 // agent-scope atomics: it is valid by itself, so no fence writes back or
 // invalidates an L2 under the other workgroups.  (Flags with release and
 // acquire cost more than the counting and ranking: R = 64, 4.2 M ids 29.2 us,
-// 20.4 now; 0.5 M ids 16.0, 9.3 now.  Every workgroup summing all earlier
-// rows: 45 us.)  The waits are bounded and only on lower workgroup indices,
+// 22.6 now; 0.5 M ids 16.3, 10.2 now.  Every workgroup summing all earlier
+// rows behind one acquire a wave: 45 us.)  The waits are bounded and only on lower workgroup indices,
 // which are dispatched first.  The last workgroup of a group to finish (a
 // ticket) clears the group's counts, the last of all the totals, so the
 // workspace is zero again for the next call.
@@ -48,6 +48,7 @@ constexpr int kLayoutGroup = 16;        // workgroups whose counts one total sta
 constexpr int kLayoutBlocks = 512;      // workgroups at most (longer chunks take several tiles)
 constexpr uint32_t kLayoutSpin = 1u << 24;
 constexpr int kLayoutCtrlBytes = 256;
+constexpr int kLayoutGroupTickets = 32;   // control words: [0] groups done, [32 + g] workgroups of group g done
 
 struct Layout {
   int R, nbits, nb;
@@ -58,7 +59,7 @@ struct Layout {
   int32_t *slot_out;   // [n]
   int32_t *status;     // [1] or null: TOPOEP_ST_SYNC when a wait gave up
   uint32_t *rows;      // [nb][R] a workgroup's counts + 1, or its group's total + 1
-  uint32_t *ctrl;      // finish tickets: [0] of all workgroups, [1 + g] of group g
+  uint32_t *ctrl;      // finish tickets (kLayoutGroupTickets)
   uint32_t spin_limit;
 };
 
@@ -274,6 +275,11 @@ __global__ __launch_bounds__(kLayoutThreads) void layout_kernel(Layout L) {
   lds_barrier();
   add_rows(grp, kLayoutGroup - 1, kLayoutGroup);
   const bool ok = __syncthreads_or(gave_up) == 0;
+  // this workgroup has read every word it needs: its ticket is on its way
+  // while it writes its slots
+  uint32_t *gticket = L.ctrl + kLayoutGroupTickets + grp;
+  uint32_t ticket = 0;
+  if (tid == 0) ticket = __hip_atomic_fetch_add(gticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (!multi) {
 #pragma unroll
     for (int i = 0; i < IPT; ++i) {
@@ -307,29 +313,37 @@ __global__ __launch_bounds__(kLayoutThreads) void layout_kernel(Layout L) {
       }
     }
   }
-  // this workgroup has read every word it needs: the last one of its group to
-  // get here clears the group's counts, the last one of all the totals
+  // the last one of its group to take a ticket clears the group's counts and
+  // takes the group's; the last group's clears the totals (atomics on one
+  // line take turns: one a workgroup, not two)
   const int gsize = imin(kLayoutGroup, L.nb - grp * kLayoutGroup);
   if (tid == 0) {
     if (!ok && L.status) atomicOr(reinterpret_cast<unsigned *>(L.status), TOPOEP_ST_SYNC);
-    misc[4] = __hip_atomic_fetch_add(L.ctrl + 1 + grp, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
-              (uint32_t)gsize;
-    misc[5] = __hip_atomic_fetch_add(L.ctrl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (uint32_t)L.nb;
-    if (misc[4]) __hip_atomic_store(L.ctrl + 1 + grp, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (misc[5]) __hip_atomic_store(L.ctrl, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    misc[4] = ticket + 1u == (uint32_t)gsize;
   }
-  __syncthreads();
+  lds_barrier();
+  if (!misc[4]) return;
+  const int groups = (L.nb + kLayoutGroup - 1) / kLayoutGroup;
+  if (tid == 0) {
+    __hip_atomic_store(gticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    misc[5] = groups == 1 || __hip_atomic_fetch_add(L.ctrl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+                                 (uint32_t)groups;
+  }
   auto clear = [&](int64_t word) {
     __hip_atomic_store(L.rows + word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  if (misc[4]) {
-    const int64_t base = (int64_t)grp * kLayoutGroup * R;
-    const int n = imin(gsize, kLayoutGroup - 1) * R;
-    for (int i = tid; i < n; i += nt) clear(base + i);
-  }
-  if (misc[5])
+  const int64_t base = (int64_t)grp * kLayoutGroup * R;
+  const int n = imin(gsize, kLayoutGroup - 1) * R;
+  for (int i = tid; i < n; i += nt) clear(base + i);
+  if (groups == 1 && gsize < kLayoutGroup) return;
+  lds_barrier();
+  if (misc[5] && groups > 1) {
+    if (tid == 0) __hip_atomic_store(L.ctrl, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int g = 0; g < L.nb / kLayoutGroup; ++g)
       for (int r = tid; r < R; r += nt) clear((int64_t)(g * kLayoutGroup + kLayoutGroup - 1) * R + r);
+  } else if (misc[5] && gsize == kLayoutGroup) {
+    for (int r = tid; r < R; r += nt) clear((int64_t)(kLayoutGroup - 1) * R + r);
+  }
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -359,9 +373,10 @@ int layout_setup(const topoep_topology *t, int32_t T, int32_t k, Layout *out, La
   // ids per thread, then whole tiles per workgroup so that the grid stays
   // within max_blocks: one id while 64 workgroups hold them, two up to 256 (R
   // = 64, 32 K ids: 6.5 us, four ids 7.3; 131 K: 7.4, 8.0), more ids in one
-  // tile of each of 256 workgroups up to 2^21 (two tiles of 128: 2.1 M ids
-  // 16.8 us, 13.8); 512 workgroups beyond, where two fit a CU (34 M ids 105
-  // us, 94; R = 256, one per CU: 117, 123).  A workspace without room for so
+  // tile of each of 256 workgroups up to 2^21 (two tiles of 128 workgroups:
+  // 2.1 M ids 16.8 us, one of 256: 13.8); 512 workgroups beyond, where two fit
+  // a CU (34 M ids: 256 take 105 us, 512 94; at R = 256, where one fits, 117
+  // and 123; those figures without the tickets' about 1 us).  A workspace without room for so
   // many workgroups' counts gets four ids per thread.
   const size_t lds = (size_t)layout_lds(R, kLayoutThreads).words * 4;
   int ipt = L.n <= (int64_t)kLayoutThreads * 64 ? 1 : (L.n <= (int64_t)kLayoutThreads * 256 ? 2 : 4);

@@ -82,6 +82,8 @@ constexpr int kCtrlGen = 10;
 constexpr int kCtrlVerdict = 11;
 constexpr uint32_t kVerdictSame = 1;
 constexpr uint32_t kVerdictRedo = 2;
+constexpr int kCtrlCost = 12;    // general cost model: largest cost
+constexpr int kCtrlSize = 14;    // uint64 at words 14..15: largest expert size
 // words 16..63: phase stamps of the instrumented build (TOPOEP_STAMPS)
 constexpr int kCtrlStamps = 16;
 
@@ -1721,49 +1723,41 @@ __device__ __forceinline__ void scan_rows(const Plan &p, int r0, int r1, const i
 
 // The full model of Section 4.1 on the device: whether the cost matrix is a
 // cost (symmetric, nonnegative, zero diagonal) and every size nonnegative,
-// and the largest entry and size for the exact-range bound.  misc[16..23]
-// are scratch; returns the COST bit or 0 (the same on every thread).
-__device__ __forceinline__ uint32_t general_check(const Plan &p, int *misc, uint64_t *cmax, uint64_t *wmax) {
-  const int tid = threadIdx.x, nt = blockDim.x, R = p.R;
-  if (tid < 8) misc[16 + tid] = 0;
-  lds_barrier();
-  bool bad = false;
-  uint32_t cm = 0;
-  uint64_t wm = 0;
+// and the largest entry and size for the exact-range bound.  Each workgroup
+// looks at its domains' rows of the matrix and a share of the sizes, and the
+// control words combine them by the grid barrier (every workgroup used to
+// read the whole matrix: 65 536 entries at R = 256, where a plan went from
+// 90.0 to 27.6 us with this and the one launch).
+struct CostCheck {
+  bool bad;
+  uint32_t cm;
+  uint64_t wm;
+};
+
+__device__ __forceinline__ CostCheck general_check(const Plan &p, int wg, int nwg) {
+  const int tid = threadIdx.x, nt = blockDim.x, R = p.R, GR = p.G * p.R;
+  CostCheck k = {false, 0u, 0ull};
   if (p.Cm) {
-    for (int i = tid; i < R * R; i += nt) {
-      const int s = i / R, r = i - s * R;
-      const int c = p.Cm[i];
-      bad |= c < 0 || (s == r && c != 0) || c != p.Cm[(int64_t)r * R + s];
-      if (c > 0 && (uint32_t)c > cm) cm = (uint32_t)c;
-    }
+    for (int d = wg; d < p.M; d += nwg)
+      for (int i = tid; i < GR; i += nt) {
+        const int j = i / R, r = i - j * R, s = d * p.G + j;
+        const int c = p.Cm[(int64_t)s * R + r], ct = p.Cm[(int64_t)r * R + s];
+        k.bad |= c < 0 || (s == r && c != 0) || c != ct;
+        if (c > 0 && (uint32_t)c > k.cm) k.cm = (uint32_t)c;
+      }
   } else {
-    cm = (uint32_t)imax(p.cI, p.cX);
+    k.cm = (uint32_t)imax(p.cI, p.cX);
   }
   if (p.We) {
-    for (int e = tid; e < p.E; e += nt) {
+    for (int e = wg * nt + tid; e < p.E; e += nwg * nt) {
       const int64_t w = p.We[e];
-      bad |= w < 0;
-      if (w > 0 && (uint64_t)w > wm) wm = (uint64_t)w;
+      k.bad |= w < 0;
+      if (w > 0 && (uint64_t)w > k.wm) k.wm = (uint64_t)w;
     }
   } else {
-    wm = (uint64_t)p.W;
+    k.wm = (uint64_t)p.W;
   }
-  // (one LDS atomic per wave: of every lane they serialise on one word)
-  cm = ~rows_min_u32(~cm, false);
-  wm = ~wave_min_u64(~wm);
-  const uint64_t any_bad = __ballot(bad);
-  if (lane_id() == 0) {
-    if (any_bad) misc[16] = 1;
-    atomicMax(reinterpret_cast<unsigned *>(&misc[17]), cm);
-    atomicMax(reinterpret_cast<unsigned long long *>(misc + 18), (unsigned long long)wm);
-  }
-  lds_barrier();
-  *cmax = (uint32_t)misc[17];
-  *wmax = *reinterpret_cast<const unsigned long long *>(misc + 18);
-  const uint32_t st = misc[16] ? TOPOEP_ST_COST : 0u;
-  lds_barrier();
-  return st;
+  return k;
 }
 
 // Cost tables of domain d for its refinement: ccol[j][s] = c(s, dG + j),
@@ -1898,11 +1892,8 @@ __device__ __forceinline__ void domain_solver(const Plan &p0, int *sm) {
   }
   build_divisors(M, fdt);
   uint64_t cmax = (uint64_t)imax(p.cI, p.cX), wmax = (uint64_t)p.W;
-  uint32_t cst = 0;
-  if (p.general) {
-    cst = general_check(p, misc, &cmax, &wmax);
-    if (tid == 0 && cst) atomicOr(reinterpret_cast<unsigned *>(&misc[0]), cst);
-  }
+  CostCheck check = {false, 0u, 0ull};
+  if (p.general) check = general_check(p, wg, nwg);
   // ---- row self of Omega: the histogram of local_topk, from the offset
   // helpers; the workgroup of the domain holding self needs it for its
   // stage 1 (it waits once its rows of Omega are loaded), the others only
@@ -1993,9 +1984,19 @@ __device__ __forceinline__ void domain_solver(const Plan &p0, int *sm) {
       const uint32_t *gh = p.ghist + (misc[kMiscGen] & 1) * (E + 1);
       for (int e = tid; e < E; e += nt) hs[e] = (int)gh[e];
       if (tid == 0) {
-        misc[0] = (int)(cst | (gh[E] ? TOPOEP_ST_BAD_ID : 0u));
+        misc[0] = (int)(gh[E] ? TOPOEP_ST_BAD_ID : 0u);
         misc[8] = misc[9] = 0;
       }
+    }
+  }
+  if (p.general) {
+    // (one atomic per wave)
+    const uint32_t cm = ~rows_min_u32(~check.cm, false);
+    const uint64_t wm = ~wave_min_u64(~check.wm), any_bad = __ballot(check.bad);
+    if (lane_id() == 0) {
+      if (any_bad) atomicOr(&p.ctrl[kCtrlStatus], TOPOEP_ST_COST);
+      atomicMax(&p.ctrl[kCtrlCost], cm);
+      atomicMax(reinterpret_cast<unsigned long long *>(p.ctrl + kCtrlSize), (unsigned long long)wm);
     }
   }
   if (tid == 0) {
@@ -2016,6 +2017,11 @@ __device__ __forceinline__ void domain_solver(const Plan &p0, int *sm) {
   uint32_t gst = __hip_atomic_load(&p.ctrl[kCtrlStatus], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint64_t total = __hip_atomic_load(reinterpret_cast<unsigned long long *>(p.ctrl + kCtrlTotal),
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (p.general) {
+    cmax = __hip_atomic_load(&p.ctrl[kCtrlCost], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    wmax = __hip_atomic_load(reinterpret_cast<unsigned long long *>(p.ctrl + kCtrlSize), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+  }
   if (out_of_range_cw(p, total, cmax, wmax)) gst |= TOPOEP_ST_RANGE;
   if (!synced) gst |= TOPOEP_ST_SYNC;
   const bool noplan = (gst & (kNoPlan | TOPOEP_ST_SYNC)) != 0;
@@ -2348,7 +2354,9 @@ __device__ __forceinline__ void domain_solver(const Plan &p0, int *sm) {
     p.ctrl[kCtrlTicket] = 0;
     p.ctrl[kCtrlStatus] = 0;
     p.ctrl[kCtrlMoves] = 0;
+    p.ctrl[kCtrlCost] = 0;
     *reinterpret_cast<unsigned long long *>(p.ctrl + kCtrlTotal) = 0ull;
+    *reinterpret_cast<unsigned long long *>(p.ctrl + kCtrlSize) = 0ull;
     if (!One)
       __hip_atomic_fetch_sub(&p.ctrl[kCtrlHelpers], (uint32_t)p.n_helpers, __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
@@ -3600,7 +3608,7 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
   // Counting by LDS atomics lets the chunk arrive before its ids are ranked
   // (Stress-like, eight ids per thread: 2.6 us after the start, 5.1 ranked
   // first); up to 32 experts they meet on too few words, and the short ranks
-  // come first (R = 16, E = 16, 75 K ids: 10.8 us counted first, 10.3).
+  // come first.
   const bool rank_first = p.nbits <= 5;
   int *mywc = wc + wave * E;
   for (int e = lane; e < E; e += 64) mywc[e] = 0;
@@ -3720,6 +3728,9 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
     return;
   }
   __syncthreads();
+  // (shares ascend: with many domains a list may be long, and is halved down
+  // to four entries first)
+  const bool long_lists = p.M > 4;
   int dv[IPT];
 #pragma unroll
   for (int i = 0; i < IPT; ++i) {
@@ -3729,8 +3740,7 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
       if ((unsigned)ev[i] < (unsigned)E) {
         const int j1 = ptr[ev[i] + 1];
         int j = ptr[ev[i]];
-        // (shares ascend: halve a long list down to four entries first)
-        for (int len = j1 - j; len > 4;) {
+        for (int len = long_lists ? j1 - j : 0; len > 4;) {
           const int half = len >> 1;
           if (ent[j + half - 1].x <= rho[i]) {
             j += half;

@@ -1346,11 +1346,23 @@ __device__ __forceinline__ uint32_t refine_domain(const Plan &p, int d, int *e_o
           const int *ct = gc.ccol + rtj * R, *cb = gc.ccol + rbj * R;
           int rest = delta;
           int64_t dt = 0;
-          for (int k = 0; k < R && rest > 0; ++k) {
-            const int s2 = o[k];
-            const int take = imin(rest, qa[s2]);
-            dt += (int64_t)take * (ct[s2] - cb[s2]);
-            rest -= take;
+          // (four sources' words in flight: one at a time, each waits for
+          // three dependent LDS reads)
+          for (int k0 = 0; k0 < R && rest > 0; k0 += 4) {
+            int sx[4], av[4], df[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sx[i] = o[imin(k0 + i, R - 1)];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              av[i] = k0 + i < R ? qa[sx[i]] : 0;
+              df[i] = ct[sx[i]] - cb[sx[i]];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int take = imin(rest, av[i]);
+              dt += (int64_t)take * df[i];
+              rest -= take;
+            }
           }
           dcost = 2 * p.S * dt;
           if (!hosts) dcost += (int64_t)gc.ccol[rtj * R + (int)fdiv((uint32_t)e, p.fP)] * gc.wx[e];

@@ -161,13 +161,6 @@ __device__ inline uint64_t uniform_u64(uint64_t v) {
          (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
-__device__ inline bool lex_less(uint64_t a1, uint64_t a2, uint64_t a3, uint64_t b1, uint64_t b2,
-                                uint64_t b3) {
-  if (a1 != b1) return a1 < b1;
-  if (a2 != b2) return a2 < b2;
-  return a3 < b3;
-}
-
 // Exclusive scan of a[0..n) in place by the whole workgroup; returns the total.
 // tmp needs blockDim/64 + 1 words.
 __device__ inline int block_excl_scan(int *a, int n, int *tmp) {

@@ -3123,7 +3123,7 @@ __global__ __launch_bounds__(1024, 8) void reroute_kernel(Plan p) {
       for (int i = j; i < j1 && from < start; ++i) {
         const int2 en = ent[i];
         const int c = imin(start, en.x) - from;
-        if (c > 0) atomicAdd(&so[en.y], c);
+        if (c > 0 && (unsigned)en.y < (unsigned)p.R) atomicAdd(&so[en.y], c);
         from = en.x;
       }
     }

@@ -27,7 +27,9 @@
  *   - One workspace serves one plan at a time: plans that share a workspace
  *     must be ordered on one stream.  A workspace serves one problem shape:
  *     the topology, T, k, N_slot and the launch shape (its layout and its
- *     hand-over words depend on all of them).  It is zero-filled before the
+ *     hand-over words depend on all of them; launches that topoep_plan_shape
+ *     describes alike are one shape and may alternate, each with as many
+ *     bytes of the workspace as it needs).  It is zero-filled before the
  *     first plan of a shape (e.g. hipMemset after allocation, or again
  *     before another shape reuses the memory); after that no clearing is
  *     needed between plans, including after a plan that reported
@@ -138,8 +140,8 @@ typedef struct topoep_shape {
 /*
  * Bytes of device workspace topoep_plan needs for these sizes (default
  * launch shape).  A plan whose stages run as one kernel (topoep_shape) asks
- * for that kernel's buffers too; with the bytes of launch shape solver 2 it
- * runs as three kernels.  Returns TOPOEP_OK, TOPOEP_EINVAL for invalid sizes, or
+ * for that kernel's buffers too, behind the others; with the bytes of launch
+ * shape solver 2 it runs as three kernels.  Returns TOPOEP_OK, TOPOEP_EINVAL for invalid sizes, or
  * TOPOEP_ELIMIT when one domain's solver state cannot fit in LDS.
  */
 int topoep_workspace_bytes(const topoep_topology *topo, int32_t T, int32_t k,

@@ -94,7 +94,6 @@ constexpr int kMaxSolveGroups = 128;    // co-resident by a wide margin (256 CUs
 constexpr int kMinBlocks = 2048;        // histogram/reroute blocks to aim for, at least
 constexpr int kMaxBlocks = 8192;        // and at most
 constexpr int64_t kOneTileIds = 1 << 20;   // above: blocks of 1024 threads
-constexpr size_t kThreeOnly = 0;        // setup's max_ws: no one-launch plan with the per-domain solver
 constexpr int kOneThreads = 512;        // threads of plan_domains_kernel
 constexpr int kMaxOneGroups = 64;       // its workgroups at most (a quarter of 256 CUs)
 constexpr int kLongBlocks = 512;        // and at most this many of them (two per CU)
@@ -3826,7 +3825,9 @@ __global__ __launch_bounds__(1024) void empty_kernel(Plan p) { (void)p; }
 
 struct Shape {
   int ipt, bt, st;
-  size_t zero_bytes;   // workspace prefix that must be zero before a first plan
+  // workspace words beside the control words that must be zero before a
+  // first plan (one launch: the ready flags and histogram buffers)
+  size_t zero_off, zero_bytes;
   int mode;       // 1 single-workgroup solver, 2 per-domain solver (three kernels each), 3 one launch
   size_t lds_hist, lds_solve, lds_reroute, lds_fused;
   int solve_groups;
@@ -4109,7 +4110,7 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
   // wait on each other, and so up to four such plans on four hardware queues
   // are resident together.  Two ids per thread while that keeps to 32
   // chunks, else eight.
-  if (max_ws != kThreeOnly && s.mode == 2 && solver == 0 && !given && !(lc && lc->solve_threads) && q.n_solvers == q.M) {
+  if (s.mode == 2 && solver == 0 && !given && !(lc && lc->solve_threads) && q.n_solvers == q.M) {
     for (int ipt = 2; ipt <= 8 && s.one_nb == 0; ipt *= 4) {
       const int64_t per = (int64_t)kOneThreads * ipt;
       const int64_t nbo = q.n > 0 ? (q.n + per - 1) / per : 1;
@@ -4148,23 +4149,17 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
     off = align256(off + bytes);
     return o;
   };
-  // Every word a plan needs zero before its first use sits in the prefix
-  // [0, zero_bytes): the control words, then (one launch) the ready flags and
-  // the histogram buffers.  A plan with the per-domain solver that runs as
-  // one launch also keeps the three-kernel plan's buffers (its stages run
-  // alone too), and runs as three kernels in a workspace without room for
-  // both (max_ws).
+  // The control words, the three-kernel plan's buffers, then the one-launch
+  // plan's: a plan with the per-domain solver that runs as one launch keeps
+  // both (its stages run alone too), and its own words lie behind everything
+  // a three-kernel plan of the same shape writes, so launches of one shape
+  // share a workspace in any order, and one without room for both (max_ws)
+  // runs the plan as three kernels.  Large batches take fewer rows of counts
+  // than the workspace has room for (ws_rows); the room lies behind the rows,
+  // so the layout follows from the shape alone.
   const bool one = s.mode == 3;
   const bool three = !one;
-  const int chunks = one ? q.nb : s.one_nb;   // one launch: chunk workgroups
   const size_t o_ctrl = take(kCtrlBytes);
-  const size_t o_flg = take((size_t)chunks * kFlagStride * 4);
-  const size_t o_gh = take(chunks ? (size_t)2 * (E + 1) * 4 : 0);
-  s.zero_bytes = off;
-  const size_t o_pub = take((size_t)chunks * E * 2);
-  const size_t o_part = take(three ? (size_t)ws_rows * E * 4 : 0);
-  const size_t o_offs = take(three ? (size_t)ws_rows * E * 4 : 0);
-  const size_t o_berr = take(three ? (size_t)ws_rows * 4 : 0);
   const size_t o_repl = take(s.mode == 2 ? (size_t)q.M * imax(q.cap1, 1) * 4 : 0);
   const size_t o_sege = take(s.mode == 2 ? (size_t)q.M * q.I * 4 : 0);
   const size_t o_segq = take(s.mode == 2 ? (size_t)q.M * q.I * 4 : 0);
@@ -4172,8 +4167,23 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
   const size_t o_cr = take((size_t)q.nent_cap * 4);
   const size_t o_ce = take((size_t)q.nent_cap * 4);
   const size_t o_ht = take(three ? (size_t)E * 4 : 0);
-  if (s.one_nb > 0 && off > max_ws)   // no room for one launch: three kernels
-    return setup(t, T, k, N, lc, p, sh, ws_bytes, ws, general, kThreeOnly);
+  const size_t o_rows = off;
+  const size_t o_part = take(three ? (size_t)q.nb * E * 4 : 0);
+  const size_t o_offs = take(three ? (size_t)q.nb * E * 4 : 0);
+  const size_t o_berr = take(three ? (size_t)q.nb * 4 : 0);
+  if (three) off = o_rows + 2 * align256((size_t)ws_rows * E * 4) + align256((size_t)ws_rows * 4);
+  const size_t three_bytes = off;
+  int chunks = one ? q.nb : s.one_nb;   // one launch: chunk workgroups
+  const size_t o_flg = take((size_t)chunks * kFlagStride * 4);
+  const size_t o_gh = take(chunks ? (size_t)2 * (E + 1) * 4 : 0);
+  s.zero_off = o_flg;
+  s.zero_bytes = off - o_flg;
+  const size_t o_pub = take((size_t)chunks * E * 2);
+  if (s.one_nb > 0 && off > max_ws) {   // no room for one launch: three kernels
+    chunks = s.one_nb = 0;
+    s.zero_bytes = 0;
+    off = three_bytes;
+  }
   *ws_bytes = off;
   if (ws) {
     auto at = [&](size_t o, bool have) { return have ? reinterpret_cast<int32_t *>(ws + o) : nullptr; };
@@ -4415,11 +4425,14 @@ int scratch_address(void **out) {
   return TOPOEP_OK;
 }
 
-// Zero n words (the workspace prefix a first plan needs zero): a kernel, so
-// that the clearing can be captured in a HIP graph like the plan itself.
-__global__ __launch_bounds__(256) void zero_words(uint32_t *w, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    w[i] = 0u;
+// Zero the control words at w and n more words at w2 (what a first plan needs
+// zero): a kernel, so that the clearing can be captured in a HIP graph like
+// the plan itself.
+__global__ __launch_bounds__(256) void zero_words(uint32_t *w, uint32_t *w2, int64_t n) {
+  constexpr int kCtrlWords = kCtrlBytes / 4;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < kCtrlWords) w[i] = 0u;
+  else if (i - kCtrlWords < n) w2[i - kCtrlWords] = 0u;
 }
 
 }  // namespace
@@ -4447,7 +4460,8 @@ int topoep_plan_noalloc(const topoep_topology *topo, const int32_t *global_load,
   hipStream_t st = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
   const int64_t words = (int64_t)(s.zero_bytes / 4);
-  hipLaunchKernelGGL(zero_words, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, static_cast<uint32_t *>(ws),
+  hipLaunchKernelGGL(zero_words, dim3((unsigned)((kCtrlBytes / 4 + words + 255) / 256)), dim3(256), 0, st,
+                     static_cast<uint32_t *>(ws), reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + s.zero_off),
                      words);
   if (hipGetLastError() != hipSuccess) return TOPOEP_EHIP;
   return enqueue(7, topo, global_load, local_topk, T, k, replica_budget, replica_slots, token_dest, send_counts,

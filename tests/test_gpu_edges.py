@@ -197,6 +197,57 @@ def test_per_domain_three_kernel_workspace():
         p.plan(torch.from_numpy(omega).to(DEV), torch.from_numpy(tk).to(DEV))
 
 
+@pytest.mark.parametrize("name", ["stress", "refine"])
+def test_per_domain_mixed_launches(name):
+    """One workspace, launches of one shape in every order: the default (one
+    kernel), the per-domain solver named (three kernels), the default's
+    blocks and solver threads named, and a workspace_bytes without room for
+    the one kernel's buffers.  A three-kernel plan leaves that kernel's words
+    as they were."""
+    from test_gpu_parity import DEV, assert_same, ref_plan, topoep
+    a, b = _domain_case(name, 3), _domain_case(name, 4)
+    R, G, E, s, cI, cX, S, W, N, _, tk = a
+    b = (R, G, E, s) + b[4:9] + (b[9].copy(), b[10])
+    b[9][s] = np.bincount(b[10].ravel(), minlength=E)
+    topo = topoep.topology(R, G, E, s, cI, cX, S, W)
+    T, k = tk.shape
+    p = topoep.Planner(topo, T, k, N, device=DEV)
+    full, three = p.ws_bytes, topoep.workspace_bytes(topo, T, k, N, launch=SOLVERS["perdomain"])
+    dev = [(torch.from_numpy(x[9]).to(DEV), torch.from_numpy(x[10]).to(DEV)) for x in (a, b)]
+    refs = [ref_plan(*x) for x in (a, b)]
+    ways = [("default", None, full), ("solver 2", SOLVERS["perdomain"], full), ("4 x 256", (4, 256), full),
+            ("512 solver threads", (0, 0, 0, 512), full), ("fewer bytes", None, three)]
+    assert all(topoep.plan_shape(topo, T, k, N, launch).as_dict() == p.shape.as_dict() for _, launch, _ in ways)
+    view = p.workspace_view()
+    order = [i for x in range(len(ways)) for y in range(len(ways)) for i in (x, y)]
+    for step, i in enumerate(order):
+        what, launch, p.ws_bytes = ways[i]
+        own = view[three:full].clone()
+        p.token_dest.fill_(-9)
+        p.plan(*dev[step % 2], launch=launch)
+        torch.cuda.synchronize()
+        assert_same(dict(replica_slots=p.replica_slots.cpu().numpy(), token_dest=p.token_dest.cpu().numpy(),
+                         send_counts=p.send_counts.cpu().numpy(), status=int(p.status[0]),
+                         move_count=int(p.status[1])), refs[step % 2], "%s step %d: %s" % (name, step, what))
+        assert i == 0 or torch.equal(own, view[three:full]), (step, what)
+
+
+def test_noalloc_per_domain_one_launch():
+    """The library's array, dirty from a plan of another shape, before each
+    per-domain plan in one launch."""
+    from test_gpu_parity import DEV, assert_same, ref_plan, topoep
+    for name in ("refine", "large", "stress", "1025", "large", "refine"):
+        args = _zipf_case(32, 8, 128, 2, 200000, 4, 9) if name == "large" else _domain_case(name)
+        R, G, E, s, cI, cX, S, W, N, omega, tk = args
+        out = [torch.full(sh, -9, dtype=torch.int32, device=DEV) for sh in ((R, N), tk.shape, (R,), (2,))]
+        topoep.plan_noalloc(topoep.topology(R, G, E, s, cI, cX, S, W), torch.from_numpy(omega).to(DEV),
+                            torch.from_numpy(tk).to(DEV), N, *out)
+        torch.cuda.synchronize()
+        slots, dest, send, status = [x.cpu().numpy() for x in out]
+        assert_same(dict(replica_slots=slots, token_dest=dest, send_counts=send, status=int(status[0]),
+                         move_count=int(status[1])), ref_plan(*args), "no-alloc %s" % name)
+
+
 @pytest.mark.parametrize("name", ["stress", "experts", "refine", "empty", "1025"])
 def test_per_domain_one_launch_dispatch(name):
     """Receive counts, send offsets and slots of the one-launch plan."""

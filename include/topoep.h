@@ -99,7 +99,7 @@ typedef struct topoep_shape {
                             /* or 3.  Chosen by default (launch NULL or zero     */
                             /* shape fields), a small plan with the per-domain   */
                             /* solver enqueues its three stages' work as one     */
-                            /* kernel; each stage still runs alone               */
+                            /* kernel; its stages can still be enqueued          */
   int32_t solver;           /* 1, 2 or 3 as in topoep_launch.solver              */
   int32_t items_per_thread; /* ids per thread of the histogram/reroute work      */
   int32_t chunk_blocks;     /* workgroups holding ids                            */
@@ -210,7 +210,10 @@ int topoep_plan_ex(const topoep_topology *topo, const int32_t *global_load,
  * stage 0 = histogram (Eq. 3 row), 1 = solver (Eqs. 4, 9, 10 and routing),
  * 2 = reroute; a stage reads the workspace state the earlier stages left for
  * the same inputs, so it may be repeated after one full plan and gives the
- * same outputs.  With one kernel (solver 3), stage 0 is the whole plan.
+ * same outputs.  Where three stages run as one kernel (topoep_shape) that
+ * kernel leaves none of this state: stage 1 then enqueues stages 0 and 1,
+ * stage 2 all three (to time them apart, name solver 2).  With one kernel
+ * (solver 3), stage 0 is the whole plan.
  * TOPOEP_STAGE_FLOOR enqueues every kernel of the plan with an empty body
  * and the same grid, threads and dynamic LDS (writes nothing).  The
  * arguments are those of topoep_plan_ex.  TOPOEP_EINVAL for any other stage.

@@ -4383,9 +4383,12 @@ int enqueue(int stage_mask, const topoep_topology *topo, const int32_t *global_l
   } else if (s.one_nb > 0 && stage_mask == 7) {
     launch_domains(p, s, st);
   } else {
-    if (stage_mask & 1) launch_hist(p, s, st);
-    if (stage_mask & 2) launch_solve(p, s, st);
-    if (stage_mask & 4) launch_reroute(p, s, st);
+    // a plan that ran as one launch has left no counts or offsets of the
+    // blocks: a later stage alone brings the stages before it
+    const int mask = s.one_nb > 0 ? (stage_mask << 1) - 1 : stage_mask;
+    if (mask & 1) launch_hist(p, s, st);
+    if (mask & 2) launch_solve(p, s, st);
+    if (mask & 4) launch_reroute(p, s, st);
   }
   return hipGetLastError() == hipSuccess ? TOPOEP_OK : TOPOEP_EHIP;
 }

@@ -274,8 +274,9 @@ class Planner:
 
     def stage(self, stage: int, global_load, local_topk, stream=None):
         """Enqueue one kernel of the plan (three kernels: 0 hist, 1 solve,
-        2 reroute; one kernel: 0), or STAGE_FLOOR: the plan's kernels with
-        empty bodies."""
+        2 reroute, with the earlier ones where the plan runs all three as one;
+        one kernel: 0), or STAGE_FLOOR: the plan's kernels with empty
+        bodies."""
         rc = _lib.topoep_plan_stage(stage, *self._args(global_load, local_topk, stream),
                                     _launch_ptr(self.launch))
         if rc != OK:

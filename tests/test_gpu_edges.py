@@ -232,6 +232,32 @@ def test_per_domain_mixed_launches(name):
         assert i == 0 or torch.equal(own, view[three:full]), (step, what)
 
 
+@pytest.mark.parametrize("name", ["stress", "refine"])
+def test_per_domain_one_launch_single_stages(name):
+    """After one plan that ran as one launch, each stage alone reproduces the
+    outputs, on the same inputs and after a plan of others."""
+    from test_gpu_parity import DEV, assert_same, ref_plan, topoep
+    a = _domain_case(name, 3)
+    R, G, E, s, cI, cX, S, W, N, omega, tk = a
+    other = omega.copy()
+    other[(s + 1) % R] += 100
+    dev = [(torch.from_numpy(x).to(DEV), torch.from_numpy(tk).to(DEV)) for x in (omega, other)]
+    refs = [ref_plan(*a), ref_plan(*(a[:9] + (other, tk)))]
+    p = topoep.Planner(topoep.topology(R, G, E, s, cI, cX, S, W), tk.shape[0], tk.shape[1], N, device=DEV)
+    assert p.shape.kernels == 3
+    for step, stage in enumerate((2, 1, 2, 0, 1, 2)):
+        i = step % 2
+        p.plan(*dev[i])
+        for out in (p.token_dest, p.replica_slots, p.send_counts, p.status):
+            if stage == 2 or (stage == 1 and out is not p.token_dest):
+                out.fill_(-9)
+        p.stage(stage, *dev[i])
+        torch.cuda.synchronize()
+        assert_same(dict(replica_slots=p.replica_slots.cpu().numpy(), token_dest=p.token_dest.cpu().numpy(),
+                         send_counts=p.send_counts.cpu().numpy(), status=int(p.status[0]),
+                         move_count=int(p.status[1])), refs[i], "%s stage %d alone, step %d" % (name, stage, step))
+
+
 def test_noalloc_per_domain_one_launch():
     """The library's array, dirty from a plan of another shape, before each
     per-domain plan in one launch."""

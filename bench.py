@@ -66,6 +66,7 @@ def make_inputs(cfg, layers, mb=0, workers=None):
     return [_gen(j) for j in jobs]
 
 
+PLAN = -1   # the whole plan, beside the library's stage ids
 STAGE_NAMES = {1: ("plan",), 3: ("hist", "solve", "reroute")}
 
 
@@ -140,6 +141,20 @@ def launch_from_args(args):
     return None
 
 
+def plan_stages(topoep, planner):
+    """What is timed alone: the stage ids of the kernels one plan enqueues,
+    PLAN where it runs its three stages as one kernel."""
+    kernels = topoep.plan_launches(planner.topo, planner.T, planner.k, planner.N, planner.launch)
+    return range(kernels) if kernels == planner.shape.kernels else (PLAN,)
+
+
+def run_stage(planner, stage, gl, tk, stream=None):
+    if stage == PLAN:
+        planner.plan(gl, tk, stream=stream)
+    else:
+        planner.stage(stage, gl, tk, stream=stream)
+
+
 def run_pmc_pass(args):
     """Workload for counter runs: one plan of every layer, then each kernel
     of the plan alone over every layer (--stage-reps times), then a plain
@@ -158,10 +173,10 @@ def run_pmc_pass(args):
     planners = [topoep.Planner(topo, cfg.T, cfg.k, cfg.N, device=dev, launch=launch) for _ in range(layers)]
     for p, (g, t) in zip(planners, dev_inputs):
         p.plan(g, t)
-    for sid in range(planners[0].shape.kernels):
+    for sid in plan_stages(topoep, planners[0]):
         for _ in range(args.stage_reps):
             for p, (g, t) in zip(planners, dev_inputs):
-                p.stage(sid, g, t)
+                run_stage(p, sid, g, t)
     src = torch.ones(64 << 20, dtype=torch.int32, device=dev)
     dst = torch.empty_like(src)
     for _ in range(4):
@@ -288,7 +303,7 @@ def time_stage(torch, planners, dev_inputs, stage, reps):
         with torch.cuda.graph(g, stream=stream):
             for _ in range(reps):
                 for p, (gl, tk) in zip(planners, dev_inputs):
-                    p.stage(stage, gl, tk, stream=stream)
+                    run_stage(p, stage, gl, tk, stream)
     torch.cuda.synchronize()
     with torch.cuda.stream(stream):
         g.replay()
@@ -302,30 +317,32 @@ def time_stage(torch, planners, dev_inputs, stage, reps):
     return a.elapsed_time(b) * 1e3 / (3 * reps * len(planners))   # microseconds
 
 
-# Phase stamps of the instrumented library (slot: what was just done), in
-# the one-launch plan; the solver's slots come from workgroup 0, the chunk
-# slots from chunk 0 except "last arrival done" (the last chunk).
-PHASE_SLOTS = [(0, "solver start"), (1, "Omega in LDS"), (23, "plan start"), (22, "stage 1 candidates"),
+# Phase stamps of the instrumented library (slot: what was just done).  The
+# chunks of a one-launch plan: chunk 0, except the last arrival (the last
+# chunk).
+CHUNK_SLOTS = [(40, "chunk 0 arrived"), (45, "last arrival start"), (41, "last arrival done"),
+               (44, "chunk 0 offsets"), (42, "chunk 0 sees flag"), (43, "chunk 0 done")]
+# the one-launch plan's solver (workgroup 0)
+PHASE_SLOTS = [(0, "solver start"), (1, "Omega in LDS"), (23, "plan start"),
                (2, "stage 1"), (3, "setup"), (4, "routing"), (5, "refinement"), (6, "outputs"),
                (7, "instance list"), (10, "flags released"), (8, "speculative plan returned"),
-               (9, "verdict handled"),
-               (12, "chunk 0 arrived"), (19, "last arrival start"), (13, "last arrival done"),
-               (16, "chunk 0 offsets"), (14, "chunk 0 sees flag"), (15, "chunk 0 done"),
-               (24, "s1: candidates"), (26, "s1: ranks"), (27, "ff: lists and hosting"), (28, "ff: counts"), (30, "ff: entries")]
-
-
-# the per-domain solver (three-kernel plan): workgroup 0's phases, then the
-# last workgroup's instance list
-SOLVE_SLOTS = [(0, "solver start"), (1, "stage 1"), (2, "grid barrier passed"), (3, "row self and hosting masks"),
+               (9, "verdict handled")] + CHUNK_SLOTS + [
+               (24, "s1: candidates"), (26, "s1: ranks"), (27, "ff: lists and hosting"), (28, "ff: counts"),
+               (30, "ff: entries")]
+# the per-domain solver: workgroup 0's phases, then the last workgroup's
+# instance list (and, in one launch, the chunks' flags)
+SOLVE_SLOTS = [(0, "solver start"), (14, "s1: rows copied"), (15, "s1: row self"), (16, "s1: candidates"),
+               (1, "stage 1"), (2, "grid barrier passed"), (3, "row self and hosting masks"),
                (4, "domain instances"), (5, "q columns"), (6, "routing"), (7, "refinement"), (8, "outputs"),
                (9, "drained"), (10, "list start (last workgroup)"), (11, "list counted"), (12, "list placed"),
-               (13, "list done"), (14, "s1: rows copied"), (15, "s1: row self"), (16, "s1: candidates")]
+               (13, "list done")]
+FLAG_SLOTS = [(46, "flags released")] + CHUNK_SLOTS
 
 REFINE_SECTIONS = ["busiest and levels", "scoring", "selection", "target instance", "transfer", "updates"]
 
 
 def run_phases(args):
-    """Phase timeline of the one-launch plan from the stamped library (run
+    """Phase timeline of a plan from the stamped library (run
     with TOPOEP_STAMPS=1): every layer planned in one HIP graph, replayed;
     each slot's median over layers and replays, in microseconds after the
     solver's start (the stamps read the 100 MHz constant clock)."""
@@ -343,6 +360,8 @@ def run_phases(args):
     N = cfg.N if args.slots < 0 else args.slots
     planners = [topoep.Planner(topo, cfg.T, cfg.k, N, device=dev, launch=launch) for _ in range(layers)]
     slots = PHASE_SLOTS if planners[0].shape.kernels == 1 else SOLVE_SLOTS
+    if slots is SOLVE_SLOTS and len(plan_stages(topoep, planners[0])) == 1:
+        slots = SOLVE_SLOTS + FLAG_SLOTS
     samples, refine = [], []
     for rep in range(args.steps):
         for p, (g, t) in zip(planners, dev_inputs):
@@ -352,8 +371,7 @@ def run_phases(args):
             continue
         for p in planners:
             w = p.workspace_view()[64:256].cpu().numpy().view(np.uint32).astype(np.int64)
-            samples.append([((int(w[i]) - int(w[0])) & 0xFFFFFFFF) if i < 20 or i > 21 else 0
-                            for i, _ in slots])
+            samples.append([((int(w[i]) - int(w[0])) & 0xFFFFFFFF) if w[i] else np.nan for i, _ in slots])
             if w[38] > 0:
                 refine.append([w[32 + k] / w[38] for k in range(6)] + [w[38]])
     clk = []
@@ -363,11 +381,14 @@ def run_phases(args):
         if dt and slots is PHASE_SLOTS:
             clk.append(((int(w[21]) - int(w[20])) & 0xFFFFFFFF) / (dt * 0.01))
     arr = np.array(samples, dtype=np.float64) * 0.01   # 100 MHz ticks -> microseconds
-    med = np.median(arr, axis=0)
+    # (a phase that most plans skip is left out)
+    kept = [c for c in range(len(slots)) if np.isfinite(arr[:, c]).mean() > 0.5]
+    arr, slots_kept = arr[:, kept], [slots[c] for c in kept]
+    med = np.nanmedian(arr, axis=0)
     out = {"phases": cfg.name, "replica_slots": N, "layers": layers, "samples": len(samples),
-           "us_after_solver_start_median": {name: round(float(v), 3) for (_, name), v in zip(slots, med)},
-           "us_p10": {name: round(float(v), 3) for (_, name), v in zip(slots, np.percentile(arr, 10, axis=0))},
-           "us_p90": {name: round(float(v), 3) for (_, name), v in zip(slots, np.percentile(arr, 90, axis=0))},
+           "us_after_solver_start_median": {name: round(float(v), 3) for (_, name), v in zip(slots_kept, med)},
+           "us_p10": {name: round(float(v), 3) for (_, name), v in zip(slots_kept, np.nanpercentile(arr, 10, axis=0))},
+           "us_p90": {name: round(float(v), 3) for (_, name), v in zip(slots_kept, np.nanpercentile(arr, 90, axis=0))},
            "core_clock_MHz_median": round(float(np.median(clk)), 1) if clk else None,
            # domain 0's refinement loop: core-clock cycles per iteration by
            # section (median over the plans that refined it)
@@ -430,9 +451,10 @@ def measure(torch, topoep, cfg, N, inputs, steps, warmup, stage_reps, launch=Non
     # HIP events on its stream), and the launch floor (empty kernels, same
     # shapes, same graph structure)
     shape = planners[0].shape
-    kernels = shape.kernels
+    sids = plan_stages(topoep, planners[0])
+    kernels = len(sids)
     stages = {}
-    for sid, name in enumerate(STAGE_NAMES[kernels]):
+    for sid, name in zip(sids, STAGE_NAMES[kernels]):
         stages[name] = time_stage(torch, planners, dev_inputs, sid, max(stage_reps, copies))
     floor_us = time_stage(torch, planners, dev_inputs, topoep.STAGE_FLOOR, max(stage_reps, copies))
     for p, (g, t) in zip(planners, dev_inputs):
@@ -455,7 +477,7 @@ def measure(torch, topoep, cfg, N, inputs, steps, warmup, stage_reps, launch=Non
     layer_bytes = sum(nbytes.values())
     res = {
         "workload": DESCR.get(cfg.name, cfg.name), "layers": layers, "replica_slots": N,
-        "passes_per_replay": copies, "plan_shape": shape.as_dict(), "ms_per_step": ms_per_step,
+        "passes_per_replay": copies, "plan_shape": dict(shape.as_dict(), launches=kernels), "ms_per_step": ms_per_step,
         "assignments_per_s": value, "plan_latency_us_per_layer": per_layer,
         "plan_latency_us_per_layer_p10_p50_p90": [float(np.percentile(step_ms, q)) * 1e3 / layers
                                                   for q in (10, 50, 90)],

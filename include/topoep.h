@@ -108,7 +108,7 @@ typedef struct topoep_shape {
   int32_t lds_bytes[3];     /* dynamic LDS of each kernel                        */
 } topoep_shape;
 
-/* topoep_plan_stage: the plan's kernels with empty bodies (launch floor). */
+/* topoep_plan_stage: the plan's launches with empty bodies (launch floor). */
 #define TOPOEP_STAGE_FLOOR 3
 
 /* Host return codes. */
@@ -214,8 +214,8 @@ int topoep_plan_ex(const topoep_topology *topo, const int32_t *global_load,
  * kernel leaves none of this state: stage 1 then enqueues stages 0 and 1,
  * stage 2 all three (to time them apart, name solver 2).  With one kernel
  * (solver 3), stage 0 is the whole plan.
- * TOPOEP_STAGE_FLOOR enqueues every kernel of the plan with an empty body
- * and the same grid, threads and dynamic LDS (writes nothing).  The
+ * TOPOEP_STAGE_FLOOR enqueues every kernel that topoep_plan_ex launches with
+ * an empty body and the same grid, threads and dynamic LDS (writes nothing).  The
  * arguments are those of topoep_plan_ex.  TOPOEP_EINVAL for any other stage.
  */
 int topoep_plan_stage(int32_t stage, const topoep_topology *topo, const int32_t *global_load,

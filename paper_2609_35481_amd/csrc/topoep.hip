@@ -1883,6 +1883,7 @@ __device__ __forceinline__ void domain_solver(const Plan &p0, int *sm) {
   const int E = p.E, G = p.G, R = p.R, M = p.M, I = p.I, P = p.P, PN = p.PN, Neff = p.Neff;
   const int cap = p.cap1;
 
+  STAMP_CLEAR(0, 18);
   if (wg == 0) STAMP(p, 0);
   if (tid < 16) misc[tid] = 0;
   if constexpr (One) {
@@ -2385,6 +2386,8 @@ __device__ __forceinline__ void domain_solver(const Plan &p0, int *sm) {
       const uint32_t next = (uint32_t)misc[kMiscGen] + 1u;
       for (int b = tid; b < p.nb; b += 64)
         __hip_atomic_store(p.flags + (int64_t)b * kFlagStride, next, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      STAMP(p, 46);
+      STAMP_FLUSH(p, 46, 47);
       if (tid == 0) __hip_atomic_store(&p.ctrl[kCtrlGen], next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
@@ -3322,9 +3325,9 @@ __device__ __forceinline__ void fused_solver(const Plan &p, int *sm) {
     uint32_t *other = p.ghist + ((gen + 1u) & 1u) * (p.E + 1);
     for (int e = tid; e <= p.E; e += 64) __hip_atomic_store(other + e, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  STAMP_CLEAR(0, 39);
   STAMP(p, 0);
   STAMP_CLK(p, 20);
-  STAMP_CLEAR(32, 39);
   if (tid == 0) p.status_out[0] = 0;   // chunks may OR SYNC into it
   load_omega(p, t.om, t.misc, [&] { single_init(p, t); });
   if (tid == 0) {
@@ -3660,7 +3663,7 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
     flag[2] = (int)(uint32_t)g;
   }
   __syncthreads();
-  if (b == 0) STAMP(p, 12);
+  if (b == 0) STAMP(p, 40);
   const uint32_t gen = (uint32_t)flag[2];
   if (gen != gread) {
     // the solver has already given up on this plan and moved on: take the
@@ -3672,11 +3675,11 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
     if (tid == 0 && bad) atomicSub(gh + E, 1u);
   }
   if (flag[1]) {
-    STAMP(p, 19);
+    STAMP(p, 45);
     last_arrival(p, gen);
-    STAMP(p, 13);
-    STAMP_FLUSH(p, 13, 14);
-    STAMP_FLUSH(p, 19, 20);
+    STAMP(p, 41);
+    STAMP_FLUSH(p, 41, 42);
+    STAMP_FLUSH(p, 45, 46);
   }
   // the ids' occurrence indices in the chunk (each wave counts on from its
   // offset, in its own row), while the other chunks arrive
@@ -3689,7 +3692,7 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
   // every count is written: this chunk's first occurrence index per expert
   bool ok = wait_flag(p, b, 1, gen + 1u, flag);
   if (ok) chunk_offsets(p, b, p.ghist + (gen & 1u) * (E + 1), run, gs);
-  if (b == 0) STAMP(p, 16);
+  if (b == 0) STAMP(p, 44);
   // each id's occurrence index rho = chunk offset + index in the chunk,
   // while the plan is still being made
   __syncthreads();
@@ -3701,7 +3704,7 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
   }
   // the plan is ready
   ok = ok && wait_flag(p, b, 0, gen + 1u, flag);
-  if (b == 0) STAMP(p, 14);
+  if (b == 0) STAMP(p, 42);
   uint32_t fin = 0;
   if (ok) {
     // the instance list and the final status in one round trip: every load
@@ -3774,9 +3777,9 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
   }
   if (p.slot_out) chunk_slots<IPT>(p, dv, wbase, hi, run, ptr, ent, so, gs, wc);
   if (b == 0) {
-    STAMP(p, 15);
-    STAMP_FLUSH(p, 12, 13);
-    STAMP_FLUSH(p, 14, 17);
+    STAMP(p, 43);
+    STAMP_FLUSH(p, 40, 41);
+    STAMP_FLUSH(p, 42, 45);
   }
 }
 
@@ -4375,7 +4378,13 @@ int enqueue(int stage_mask, const topoep_topology *topo, const int32_t *global_l
   if (stage_mask == kFloorMask) {
     int grid[3], block[3];
     size_t lds[3];
-    const int nk = plan_kernels(p, s, grid, block, lds);
+    int nk = plan_kernels(p, s, grid, block, lds);
+    if (s.one_nb > 0) {   // the one kernel of the plan, not its stages
+      nk = 1;
+      grid[0] = p.n_solvers + s.one_nb;
+      block[0] = kOneThreads;
+      lds[0] = s.lds_one;
+    }
     for (int i = 0; i < nk; ++i) hipLaunchKernelGGL(empty_kernel, dim3(grid[i]), dim3(block[i]), lds[i], st, p);
   } else if (s.mode == 3) {
     if (stage_mask != 7 && stage_mask != 1) return TOPOEP_EINVAL;   // one kernel: the plan, or stage 0

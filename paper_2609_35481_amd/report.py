@@ -139,7 +139,8 @@ def _latency(topoep, torch, cfg, layers=4, reps=50):
     st = torch.stack([p.status for p in pls]).cpu().numpy()
     if (st[:, 0] & ~topoep.ST_SELF_DIFF).any():
         raise RuntimeError("plan status %s" % np.unique(st[:, 0]))
-    return a.elapsed_time(b) * 1e3 / (reps * layers), pls[0].shape.as_dict(), float(st[:, 1].mean())
+    shape = dict(pls[0].shape.as_dict(), launches=topoep.plan_launches(pls[0].topo, cfg.T, cfg.k, cfg.N))
+    return a.elapsed_time(b) * 1e3 / (reps * layers), shape, float(st[:, 1].mean())
 
 
 def scaling(ranks=(8, 16, 32, 64, 128), experts=(64, 128, 256, 512, 1024), N=2):
@@ -150,12 +151,12 @@ def scaling(ranks=(8, 16, 32, 64, 128), experts=(64, 128, 256, 512, 1024), N=2):
         cfg = dataclasses.replace(QUALITY_BASE, name="scale-R%d" % R, cfg_id=7, R=R, N=N)
         us, shape, moves = _latency(topoep, torch, cfg)
         rows.append({"sweep": "EP size, E=640", "R": R, "E": cfg.E, "us_per_layer": us,
-                     "kernels": shape["kernels"], "solver": shape["solver"], "moves_per_layer": moves})
+                     "kernels": shape["launches"], "solver": shape["solver"], "moves_per_layer": moves})
     for E in experts:
         cfg = dataclasses.replace(QUALITY_BASE, name="scale-E%d" % E, cfg_id=8, E=E, N=N)
         us, shape, moves = _latency(topoep, torch, cfg)
         rows.append({"sweep": "experts, EP 32", "R": cfg.R, "E": E, "us_per_layer": us,
-                     "kernels": shape["kernels"], "solver": shape["solver"], "moves_per_layer": moves})
+                     "kernels": shape["launches"], "solver": shape["solver"], "moves_per_layer": moves})
     return rows
 
 

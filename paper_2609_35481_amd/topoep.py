@@ -61,7 +61,8 @@ class Launch(ctypes.Structure):
 
 
 class Shape(ctypes.Structure):
-    """topoep_shape: the kernels one plan enqueues (count, grid, threads, LDS)."""
+    """topoep_shape: the stages of a plan (count, grid, threads, LDS); see
+    plan_launches for how many kernels a plan enqueues."""
     _fields_ = [("kernels", ctypes.c_int32), ("solver", ctypes.c_int32),
                 ("items_per_thread", ctypes.c_int32), ("chunk_blocks", ctypes.c_int32),
                 ("grid", ctypes.c_int32 * 3), ("block", ctypes.c_int32 * 3),
@@ -174,6 +175,19 @@ def plan_shape(topo: Topology, T: int, k: int, replica_budget: int, launch=None)
     return out
 
 
+def plan_launches(topo: Topology, T: int, k: int, replica_budget: int, launch=None) -> int:
+    """Kernels one plan enqueues: its stages, or one where the library runs
+    the per-domain solver's three as a single kernel (such a plan asks for
+    more workspace than the same launch with the solver named)."""
+    shape = plan_shape(topo, T, k, replica_budget, launch)
+    if shape.solver != SOLVER_PER_DOMAIN:
+        return shape.kernels
+    named = Launch(*(launch or ())) if not isinstance(launch, Launch) else Launch.from_buffer_copy(launch)
+    named.solver = SOLVER_PER_DOMAIN
+    one = workspace_bytes(topo, T, k, replica_budget, launch) > workspace_bytes(topo, T, k, replica_budget, named)
+    return 1 if one else shape.kernels
+
+
 def layout_workspace_bytes(topo: Topology, T: int, k: int) -> int:
     out = ctypes.c_size_t(0)
     rc = _lib.topoep_layout_workspace_bytes(ctypes.byref(topo), T, k, ctypes.byref(out))
@@ -275,7 +289,7 @@ class Planner:
     def stage(self, stage: int, global_load, local_topk, stream=None):
         """Enqueue one kernel of the plan (three kernels: 0 hist, 1 solve,
         2 reroute, with the earlier ones where the plan runs all three as one;
-        one kernel: 0), or STAGE_FLOOR: the plan's kernels with empty
+        one kernel: 0), or STAGE_FLOOR: the plan's launches with empty
         bodies."""
         rc = _lib.topoep_plan_stage(stage, *self._args(global_load, local_topk, stream),
                                     _launch_ptr(self.launch))

@@ -258,6 +258,36 @@ def test_per_domain_one_launch_single_stages(name):
                          move_count=int(p.status[1])), refs[i], "%s stage %d alone, step %d" % (name, stage, step))
 
 
+def test_per_domain_launch_count():
+    """The floor of a plan is one empty kernel where the plan is one launch:
+    its graph takes the time of one, not of three, and plan_launches says so."""
+    from test_gpu_parity import DEV, topoep
+    R, G, E, s, cI, cX, S, W, N, omega, tk = _domain_case("stress")
+    topo = topoep.topology(R, G, E, s, cI, cX, S, W)
+    dev = torch.from_numpy(omega).to(DEV), torch.from_numpy(tk).to(DEV)
+    count = {}
+    for launch in (None, SOLVERS["perdomain"]):
+        p = topoep.Planner(topo, tk.shape[0], tk.shape[1], N, device=DEV, launch=launch)
+        assert p.shape.kernels == 3
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream):
+                for _ in range(200):
+                    p.stage(topoep.STAGE_FLOOR, *dev)
+            for _ in range(3):
+                graph.replay()
+            a.record()
+            graph.replay()
+            b.record()
+        torch.cuda.synchronize()
+        count[launch] = topoep.plan_launches(topo, tk.shape[0], tk.shape[1], N, launch), a.elapsed_time(b)
+    (one, t1), (three, t3) = count[None], count[SOLVERS["perdomain"]]
+    assert one == 1 and three == 3
+    assert t1 < 0.6 * t3   # (a third, were the launches alike)
+
+
 def test_noalloc_per_domain_one_launch():
     """The library's array, dirty from a plan of another shape, before each
     per-domain plan in one launch."""

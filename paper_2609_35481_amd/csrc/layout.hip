@@ -16,21 +16,24 @@
 //     workgroup barrier;
 //   - it publishes its per-destination counts; workgroups form groups of
 //     kLayoutGroup, and the last of a group publishes the group's total in
-//     their place.  A workgroup then sums the counts of the earlier ones of
-//     its group and the totals of the earlier groups, at most
-//     kLayoutGroup - 1 rows of each;
+//     their place (the last of all publishes nothing: nobody would read it).
+//     A workgroup then sums the counts of the earlier ones of its group and
+//     the totals of the earlier groups, at most kLayoutGroup - 1 rows of each;
 //   - slot = send_offsets[dest] + (earlier workgroups) + (earlier waves, or
 //     their parts) + (earlier steps of the wave's part) + (rank in the
 //     wave).
 // A published count is one word, the count + 1, stored and polled with relaxed
 // agent-scope atomics: it is valid by itself, so no fence writes back or
 // invalidates an L2 under the other workgroups.  (Flags with release and
-// acquire cost more than the counting and ranking: R = 64, 4.2 M ids 29.2 us,
-// 22.6 now; 0.5 M ids 16.3, 10.2 now.  Every workgroup summing all earlier
-// rows behind one acquire a wave: 45 us.)  The waits are bounded and only on lower workgroup indices,
+// acquire cost more than the counting and ranking: R = 64, 4.2 M ids 33.7 us,
+// 20.0 now; 0.5 M ids 15.3, 9.3 now; 4 K ids, four workgroups, 5.25 and 5.30.
+// Every workgroup summing all earlier rows behind one acquire a wave: 45 us
+// for 4.2 M ids.)  The waits are bounded and only on lower workgroup indices,
 // which are dispatched first.  The last workgroup of a group to finish (a
 // ticket) clears the group's counts, the last of all the totals, so the
-// workspace is zero again for the next call.
+// workspace is zero again for the next call: every published word has been
+// read by another workgroup before that one's ticket, so no store of it is
+// still on its way when it is cleared.
 // All arithmetic is integer and no atomic decides an order.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -145,6 +148,7 @@ __global__ __launch_bounds__(kLayoutThreads) void layout_kernel(Layout L) {
     }
   };
   const int gi = b % kLayoutGroup, grp = b / kLayoutGroup;
+  const bool last = b == L.nb - 1;
   auto publish = [&](int r, int count) {
     __hip_atomic_store(L.rows + (int64_t)b * R + r, (uint32_t)count + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
@@ -220,7 +224,7 @@ __global__ __launch_bounds__(kLayoutThreads) void layout_kernel(Layout L) {
   lds_barrier();
   scan_waves(R, nw, wc, agg);
   lds_barrier();
-  if (gi != kLayoutGroup - 1)
+  if (gi != kLayoutGroup - 1 && !last)
     for (int r = tid; r < R; r += nt) publish(r, agg[r]);
   // send offsets (exclusive prefix of the send counts) by wave 0
   if (wave == 0) {
@@ -269,17 +273,18 @@ __global__ __launch_bounds__(kLayoutThreads) void layout_kernel(Layout L) {
     if (sum) atomicAdd(&excl[r0], sum);
   };
   add_rows(gi, grp * kLayoutGroup, 1);
-  lds_barrier();
-  if (gi == kLayoutGroup - 1)   // (a total short of a word that never came is the waiters' SYNC too)
+  if (gi == kLayoutGroup - 1 && !last) {   // (a total short of a word that never came is the waiters' SYNC too)
+    lds_barrier();
     for (int r = tid; r < R; r += nt) publish(r, excl[r] + agg[r]);
-  lds_barrier();
+    lds_barrier();
+  }
   add_rows(grp, kLayoutGroup - 1, kLayoutGroup);
   const bool ok = __syncthreads_or(gave_up) == 0;
   // this workgroup has read every word it needs: its ticket is on its way
   // while it writes its slots
   uint32_t *gticket = L.ctrl + kLayoutGroupTickets + grp;
   uint32_t ticket = 0;
-  if (tid == 0) ticket = __hip_atomic_fetch_add(gticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0 && L.nb > 1) ticket = __hip_atomic_fetch_add(gticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (!multi) {
 #pragma unroll
     for (int i = 0; i < IPT; ++i) {
@@ -316,33 +321,30 @@ __global__ __launch_bounds__(kLayoutThreads) void layout_kernel(Layout L) {
   // the last one of its group to take a ticket clears the group's counts and
   // takes the group's; the last group's clears the totals (atomics on one
   // line take turns: one a workgroup, not two)
+  if (tid == 0 && !ok && L.status) atomicOr(reinterpret_cast<unsigned *>(L.status), TOPOEP_ST_SYNC);
+  if (L.nb == 1) return;
   const int gsize = imin(kLayoutGroup, L.nb - grp * kLayoutGroup);
-  if (tid == 0) {
-    if (!ok && L.status) atomicOr(reinterpret_cast<unsigned *>(L.status), TOPOEP_ST_SYNC);
-    misc[4] = ticket + 1u == (uint32_t)gsize;
-  }
+  const int groups = (L.nb + kLayoutGroup - 1) / kLayoutGroup;
+  if (tid == 0) misc[4] = ticket + 1u == (uint32_t)gsize;
   lds_barrier();
   if (!misc[4]) return;
-  const int groups = (L.nb + kLayoutGroup - 1) / kLayoutGroup;
   if (tid == 0) {
     __hip_atomic_store(gticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    misc[5] = groups == 1 || __hip_atomic_fetch_add(L.ctrl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
-                                 (uint32_t)groups;
+    misc[5] = groups > 1 && __hip_atomic_fetch_add(L.ctrl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+                                (uint32_t)groups;
   }
   auto clear = [&](int64_t word) {
     __hip_atomic_store(L.rows + word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
+  // (the group's published counts: not its last workgroup's)
   const int64_t base = (int64_t)grp * kLayoutGroup * R;
-  const int n = imin(gsize, kLayoutGroup - 1) * R;
-  for (int i = tid; i < n; i += nt) clear(base + i);
-  if (groups == 1 && gsize < kLayoutGroup) return;
+  for (int i = tid; i < (gsize - 1) * R; i += nt) clear(base + i);
+  if (groups == 1) return;
   lds_barrier();
-  if (misc[5] && groups > 1) {
+  if (misc[5]) {
     if (tid == 0) __hip_atomic_store(L.ctrl, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int g = 0; g < L.nb / kLayoutGroup; ++g)
+    for (int g = 0; g < groups - 1; ++g)
       for (int r = tid; r < R; r += nt) clear((int64_t)(g * kLayoutGroup + kLayoutGroup - 1) * R + r);
-  } else if (misc[5] && gsize == kLayoutGroup) {
-    for (int r = tid; r < R; r += nt) clear((int64_t)(kLayoutGroup - 1) * R + r);
   }
 }
 

@@ -344,7 +344,7 @@ def test_refinement_forms(R, G, P, N, cI, solver):
         assert got["move_count"] > 0
 
 
-LAYOUT_SIZES = [1, 1024, 1025, 16 * 1024 + 1, 65536, 65537, 262144, 262145, 1 << 20, (1 << 20) + 1, 1 << 21,
+LAYOUT_SIZES = [1, 1024, 1025, 15 * 1024, 15 * 1024 + 1, 16 * 1024, 16 * 1024 + 1, 32 * 1024, 65536, 65537, 262144, 262145, 1 << 20, (1 << 20) + 1, 1 << 21,
                 (1 << 21) + 1, 4 * (1 << 20) + 3]
 
 
@@ -363,9 +363,9 @@ def _layout(planner, R, n, seed, skew):
 
 @pytest.mark.parametrize("R", [1, 3, 64, 128, 160, 1024])
 def test_layout_edges(R):
-    """One, two, four and eight ids per thread, groups of 16 workgroups and
-    one more, 256 and 512 workgroups; twice on each workspace, which is zero
-    again after every call."""
+    """One, two, four and eight ids per thread, groups of 16 workgroups, one
+    less and one more, 256 and 512 workgroups; twice on each workspace, which
+    is zero again after every call."""
     from test_gpu_parity import DEV, topoep
     for n in LAYOUT_SIZES:
         p = None

@@ -235,8 +235,9 @@ int topoep_plan_stage(int32_t stage, const topoep_topology *topo, const int32_t 
  * ascending, row-major (token, k) order inside one destination.
  */
 
-/* Bytes of device workspace topoep_dispatch_layout needs (TOPOEP_EINVAL for
- * invalid sizes, TOPOEP_ELIMIT for R > 1024). */
+/* Bytes of device workspace topoep_dispatch_layout needs for these
+ * assignments or fewer (TOPOEP_EINVAL for invalid sizes, TOPOEP_ELIMIT for
+ * R > 1024). */
 int topoep_layout_workspace_bytes(const topoep_topology *topo, int32_t T, int32_t k, size_t *bytes_out);
 
 /*

@@ -361,9 +361,35 @@ struct LayoutShape {
   size_t lds;
 };
 
+// Ids per thread of n ids, as layout_setup says, and the most workgroups that
+// hold them: 512 where two fit a CU, else 256.
+int layout_ipt(int64_t n) {
+  if (n > (int64_t)1 << 20) return 8;
+  return n <= (int64_t)kLayoutThreads * 64 ? 1 : (n <= (int64_t)kLayoutThreads * 256 ? 2 : 4);
+}
+int64_t layout_max_blocks(int64_t n, size_t lds) {
+  return n > ((int64_t)1 << 21) && lds <= 80 * 1024 ? kLayoutBlocks : kLayoutBlocks / 2;
+}
+
+// The most workgroups that n ids or fewer take: a workspace for n serves
+// every smaller call.  A range of one number of ids per thread takes most at
+// its end, one of longer chunks (from max_blocks tiles on) max_blocks.
+int64_t layout_most_blocks(int64_t n, size_t lds) {
+  int64_t most = 1;
+  for (const int64_t end : {(int64_t)kLayoutThreads * 64, (int64_t)kLayoutThreads * 256, (int64_t)1 << 20,
+                            (int64_t)1 << 21, n}) {
+    const int64_t m = end < n ? end : n, tile = (int64_t)kLayoutThreads * layout_ipt(m);
+    const int64_t tiles = (m + tile - 1) / tile, cap = layout_max_blocks(m, lds);
+    const int64_t nb = tiles < cap ? tiles : cap;
+    if (nb > most) most = nb;
+  }
+  return most;
+}
+
 // Sizes, launch shape and workspace layout (pointers stay null when ws is).
+// *ws_bytes: what these ids need; *ws_most: what they or fewer need.
 int layout_setup(const topoep_topology *t, int32_t T, int32_t k, Layout *out, LayoutShape *sh,
-                 size_t *ws_bytes, char *ws, size_t max_ws = SIZE_MAX) {
+                 size_t *ws_bytes, size_t *ws_most, char *ws, size_t max_ws = SIZE_MAX) {
   if (!t) return TOPOEP_EINVAL;
   const int R = t->num_ranks;
   if (R <= 0 || T < 0 || k < 1 || (int64_t)T * k > 0x7FFFFFFF) return TOPOEP_EINVAL;
@@ -381,13 +407,12 @@ int layout_setup(const topoep_topology *t, int32_t T, int32_t k, Layout *out, La
   // and 123; those figures without the tickets' about 1 us).  A workspace without room for so
   // many workgroups' counts gets four ids per thread.
   const size_t lds = (size_t)layout_lds(R, kLayoutThreads).words * 4;
-  int ipt = L.n <= (int64_t)kLayoutThreads * 64 ? 1 : (L.n <= (int64_t)kLayoutThreads * 256 ? 2 : 4);
-  if (L.n > (int64_t)1 << 20) ipt = 8;
+  int ipt = layout_ipt(L.n);
   if (ipt < 4 && max_ws < kLayoutCtrlBytes + align256((size_t)((L.n + kLayoutThreads * ipt - 1) / (kLayoutThreads * ipt)) * R * 4))
     ipt = L.n <= (int64_t)kLayoutThreads * 16 ? 1 : 4;
   const int64_t tile = (int64_t)kLayoutThreads * ipt;
   const int64_t tiles = L.n > 0 ? (L.n + tile - 1) / tile : 1;
-  const int64_t max_blocks = L.n > ((int64_t)1 << 21) && lds <= 80 * 1024 ? kLayoutBlocks : kLayoutBlocks / 2;
+  const int64_t max_blocks = layout_max_blocks(L.n, lds);
   L.chunk = tile * ((tiles + max_blocks - 1) / max_blocks);
   const int64_t nb = L.n > 0 ? (L.n + L.chunk - 1) / L.chunk : 1;
   if (nb > (1 << 20)) return TOPOEP_ELIMIT;
@@ -402,6 +427,7 @@ int layout_setup(const topoep_topology *t, int32_t T, int32_t k, Layout *out, La
   const size_t o_ctrl = take(kLayoutCtrlBytes);
   const size_t o_rows = take((size_t)L.nb * R * 4);
   *ws_bytes = off;
+  *ws_most = o_rows + align256((size_t)layout_most_blocks(L.n, lds) * R * 4);
   if (ws) {
     L.ctrl = reinterpret_cast<uint32_t *>(ws + o_ctrl);
     L.rows = reinterpret_cast<uint32_t *>(ws + o_rows);
@@ -430,9 +456,9 @@ int topoep_layout_workspace_bytes(const topoep_topology *topo, int32_t T, int32_
   if (!bytes_out) return TOPOEP_EINVAL;
   Layout L;
   LayoutShape sh;
-  size_t need = 0;
-  const int rc = layout_setup(topo, T, k, &L, &sh, &need, nullptr);
-  if (rc == TOPOEP_OK) *bytes_out = need;
+  size_t need = 0, most = 0;
+  const int rc = layout_setup(topo, T, k, &L, &sh, &need, &most, nullptr);
+  if (rc == TOPOEP_OK) *bytes_out = most;
   return rc;
 }
 
@@ -441,8 +467,8 @@ int topoep_dispatch_layout(const topoep_topology *topo, const int32_t *token_des
                            int32_t *status, void *workspace, size_t workspace_bytes, void *stream) {
   Layout L;
   LayoutShape sh;
-  size_t need = 0;
-  const int rc = layout_setup(topo, T, k, &L, &sh, &need, static_cast<char *>(workspace), workspace_bytes);
+  size_t need = 0, most = 0;
+  const int rc = layout_setup(topo, T, k, &L, &sh, &need, &most, static_cast<char *>(workspace), workspace_bytes);
   if (rc != TOPOEP_OK) return rc;
   if (!send_counts || !send_offsets || !workspace || (T > 0 && (!token_dest || !token_slot)))
     return TOPOEP_EINVAL;

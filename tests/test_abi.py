@@ -215,6 +215,16 @@ def test_valid_dispatch_calls_reach_the_launch(tp):
                                         4096, 8192, dw, None) == tp.EHIP
 
 
+@pytest.mark.parametrize("R", [1, 48, 200, 257, 1024])
+def test_layout_workspace_serves_fewer_assignments(tp, R):
+    """The layout's workspace never shrinks as the assignments grow: one of
+    the largest batch serves every smaller one."""
+    t = base(tp, R=R, G=1, E=R)
+    sizes = sorted({max(1, (e << s) + d) for s in range(10, 23) for e in (1, 3, 5) for d in (-1, 0, 1, 4097)})
+    need = [tp.layout_workspace_bytes(t, n, 1) for n in sizes]
+    assert need == sorted(need)
+
+
 def test_gather_host_checks(tp):
     t = base(tp)
     G = tp._lib.topoep_gather_replicas

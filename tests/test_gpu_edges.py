@@ -344,8 +344,8 @@ def test_refinement_forms(R, G, P, N, cI, solver):
         assert got["move_count"] > 0
 
 
-LAYOUT_SIZES = [1, 1024, 1025, 15 * 1024, 15 * 1024 + 1, 16 * 1024, 16 * 1024 + 1, 32 * 1024, 65536, 65537, 262144, 262145, 1 << 20, (1 << 20) + 1, 1 << 21,
-                (1 << 21) + 1, 4 * (1 << 20) + 3]
+LAYOUT_SIZES = [1, 1024, 1025, 15 * 1024, 15 * 1024 + 1, 16 * 1024, 16 * 1024 + 1, 32 * 1024, 65536, 65537, 262144,
+                262145, 1 << 20, (1 << 20) + 1, 1 << 21, (1 << 21) + 1, 3 << 20, 4 << 20, (4 << 20) + 3]
 
 
 def _layout(planner, R, n, seed, skew):

@@ -3600,7 +3600,7 @@ __device__ __forceinline__ void chunk_slots(const Plan &p, const int (&dv)[IPT],
 // (offset of the chunk) + (offset of the wave in the chunk) + (rank in the
 // wave) picks the instance from this rank's instance list.  A bounded wait
 // that gives up writes -1 and SYNC.
-template <int IPT>
+template <int IPT, bool Count>
 __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
   const ChunkLds l = chunk_lds(p, blockDim.x);
   int *wc = sm + l.wc, *run = sm + l.run, *ptr = sm + l.ptr;
@@ -3619,11 +3619,14 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
   }
   // the generation as the solver left it: the histogram buffer to add to
   const uint32_t gread = __hip_atomic_load(&p.ctrl[kCtrlGen], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  // Counting by LDS atomics lets the chunk arrive before its ids are ranked
-  // (Stress-like, eight ids per thread: 2.6 us after the start, 5.1 ranked
-  // first); up to 32 experts they meet on too few words, and the short ranks
-  // come first.
-  const bool rank_first = p.nbits <= 5;
+  // Count: counting by LDS atomics lets the chunk arrive before its ids are
+  // ranked (Stress-like, eight ids per thread: 2.6 us after the start, 5.1
+  // ranked first); up to 32 experts they meet on too few words, and the short
+  // ranks come first.  That pays where a grid barrier waits for the verdict;
+  // the single-workgroup solver plans meanwhile, and the last chunk's ranks
+  // after its arrival are on the path (EP 64, E = 128, 692 368 ids, eight per
+  // thread: 17.8 us, ranked first 16.9).
+  const bool rank_first = !Count || p.nbits <= 5;
   int *mywc = wc + wave * E;
   for (int e = lane; e < E; e += 64) mywc[e] = 0;
   wave_sync();
@@ -3686,8 +3689,8 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
 #pragma unroll
   for (int i = 0; i < IPT; ++i) {
     const bool valid = (unsigned)ev[i] < (unsigned)E;
-    if (rank_first) lr[i] += mywc[valid ? ev[i] : 0];
-    else lr[i] = wave_rank(ev[i], valid, p.nbits, mywc);
+    if (!rank_first) lr[i] = wave_rank(ev[i], valid, p.nbits, mywc);
+    else if (Count) lr[i] += mywc[valid ? ev[i] : 0];
   }
   // every count is written: this chunk's first occurrence index per expert
   bool ok = wait_flag(p, b, 1, gen + 1u, flag);
@@ -3700,7 +3703,7 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
 #pragma unroll
   for (int i = 0; i < IPT; ++i) {
     const int e = (unsigned)ev[i] < (unsigned)E ? ev[i] : 0;
-    rho[i] = run[e] + lr[i];
+    rho[i] = run[e] + lr[i] + (Count ? 0 : mywc[e]);
   }
   // the plan is ready
   ok = ok && wait_flag(p, b, 0, gen + 1u, flag);
@@ -3742,38 +3745,48 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
     return;
   }
   __syncthreads();
-  // (shares ascend: with many domains a list may be long, and is halved down
-  // to four entries first)
-  const bool long_lists = p.M > 4;
   int dv[IPT];
+  // the destination of each id: the entry of its expert's list that holds its
+  // occurrence (shares ascend)
+  auto place = [&](auto first) {
 #pragma unroll
-  for (int i = 0; i < IPT; ++i) {
-    const int64_t idx = wbase + i * 64;
-    int dest = -1;
-    if (idx < hi) {
-      if ((unsigned)ev[i] < (unsigned)E) {
-        const int j1 = ptr[ev[i] + 1];
-        int j = ptr[ev[i]];
-        for (int len = long_lists ? j1 - j : 0; len > 4;) {
-          const int half = len >> 1;
-          if (ent[j + half - 1].x <= rho[i]) {
-            j += half;
-            len -= half;
-          } else {
-            len = half;
+    for (int i = 0; i < IPT; ++i) {
+      const int64_t idx = wbase + i * 64;
+      int dest = -1;
+      if (idx < hi) {
+        if ((unsigned)ev[i] < (unsigned)E) {
+          const int j1 = ptr[ev[i] + 1];
+          for (int j = first(ptr[ev[i]], j1, rho[i]); j < j1; ++j) {
+            const int2 en = ent[j];
+            if (rho[i] < en.x) {
+              dest = en.y;
+              break;
+            }
           }
         }
-        for (; j < j1; ++j) {
-          const int2 en = ent[j];
-          if (rho[i] < en.x) {
-            dest = en.y;
-            break;
-          }
+        p.dest_out[idx] = dest;
+      }
+      dv[i] = dest;
+    }
+  };
+  if (p.M <= 8) {
+    place([&](int j, int, int) { return j; });
+  } else {
+    // with many domains a list may be long: halved down to four entries first
+    // (EP 48 over 24 nodes, 800 000 ids: 31.0 us walked, 30.1; over 3 nodes
+    // the halving costs 0.3 us)
+    place([&](int j, int j1, int at) {
+      for (int len = j1 - j; len > 4;) {
+        const int half = len >> 1;
+        if (ent[j + half - 1].x <= at) {
+          j += half;
+          len -= half;
+        } else {
+          len = half;
         }
       }
-      p.dest_out[idx] = dest;
-    }
-    dv[i] = dest;
+      return j;
+    });
   }
   if (p.slot_out) chunk_slots<IPT>(p, dv, wbase, hi, run, ptr, ent, so, gs, wc);
   if (b == 0) {
@@ -3799,7 +3812,7 @@ __global__ __launch_bounds__(1024) void plan_fused_kernel(Plan p) {
     fused_solver<Form>(q, sm);
   } else {
     const Plan q = role_plan(p);
-    fused_chunk<IPT>(q, blockIdx.x - 1, sm);
+    fused_chunk<IPT, false>(q, blockIdx.x - 1, sm);
   }
 }
 
@@ -3817,7 +3830,7 @@ __global__ __launch_bounds__(512) void plan_domains_kernel(Plan p) {
     domain_solver<true>(p, sm);
   } else {
     const Plan q = role_plan(p);
-    fused_chunk<IPT>(q, blockIdx.x - q.n_solvers, sm);
+    fused_chunk<IPT, true>(q, blockIdx.x - q.n_solvers, sm);
   }
 }
 

@@ -1545,37 +1545,51 @@ __device__ inline uint64_t cand_key(int D, int e) {
   return ((uint64_t)(uint32_t)(0x7FFFFFFF - D) << 32) | (uint32_t)e;
 }
 
-// Ranks of a domain's nc candidates by the whole workgroup, 64 candidates
-// (one per lane) against 16 keys a wave at a time; rk (nc words) starts at
-// zero.  General: keys are benefits (descending), ties to the lower expert of
-// es (||W_e|| differs per expert, so b does not follow D); else keys ascend
-// (cand_key) and are distinct.  The keys are broadcast reads; one thread per
-// candidate walking all keys took 2.6 us of dependent LDS reads for 96
-// candidates under the general model.
-template <bool General>
-__device__ __forceinline__ void rank_units(int nc, const uint64_t *keys, const int *es, int *rk) {
-  const int lane = lane_id(), wave = uniform_i32(threadIdx.x >> 6), nw = blockDim.x >> 6;
-  const int blocks = (nc + 63) >> 6, parts = (nc + 15) >> 4;
-  const int lb = blocks <= 1 ? 0 : 32 - __clz(blocks - 1);
-  for (int u = wave; u < (parts << lb); u += nw) {
-    const int blk = u & ((1 << lb) - 1), k0 = (u >> lb) * 16;
-    if (blk >= blocks) continue;
-    const int c = blk * 64 + lane, cc = imin(c, nc - 1);
+// Ranks of a domain's nc candidates by `step` waves, this one the `first` of
+// them: 64 candidates at a time, one per lane, against the keys in parts of
+// 16, whose reads are broadcasts.  The (64 candidates, part) pairs are dealt
+// to the waves in turn across the whole domain, and a wave adds once for its
+// parts of one 64.  rk (nc words) starts at zero.  General: keys are benefits
+// (descending), ties to the lower expert of es (||W_e|| differs per expert, so
+// b does not follow D); else keys ascend (cand_key) and are distinct.
+// Padded: the keys go on to a multiple of 16, sorting last.
+// One thread per candidate walking all keys took 2.6 us of dependent LDS reads
+// for 96 candidates under the general model; pairs dealt with the 64s rounded
+// up to a power of two left waves idle, and clamped every key's index (EP 64,
+// E = 1024, 1 M ids, some 850 candidates in each of 8 domains: 93.9 us a plan,
+// 65.5 now; 79.7 with a thread per candidate).
+template <bool General, bool Padded>
+__device__ __forceinline__ void rank_keys(int nc, const uint64_t *keys, const int *es, int *rk, int first, int step) {
+  const int parts = (nc + 15) >> 4;
+  int part = first;
+  for (int c0 = 0; c0 < nc; c0 += 64, part -= parts) {
+    if (part >= parts) continue;
+    const int c = c0 + lane_id(), cc = imin(c, nc - 1);
     const uint64_t kc = keys[cc];
     const int ec = General ? es[cc] : 0;
     int below = 0;
-    uint64_t k[16];
-    int e2[16];
+    for (; part < parts; part += step) {
+      const int k0 = part * 16;
+      uint64_t k[16];
+      int e2[16];
+      if (Padded || k0 + 16 <= nc) {
+        const uint64_t *kp = keys + k0;   // (plain offsets: wide reads)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int at = imin(k0 + i, nc - 1);
-      k[i] = keys[at];
-      if (General) e2[i] = es[at];
-    }
+        for (int i = 0; i < 16; ++i) k[i] = kp[i];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const bool before = General ? (k[i] > kc || (k[i] == kc && e2[i] < ec)) : k[i] < kc;
-      below += before && k0 + i < nc ? 1 : 0;
+        for (int i = 0; i < 16; ++i)
+          if (General) e2[i] = es[k0 + i];
+      } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int at = imin(k0 + i, nc - 1);
+          k[i] = k0 + i < nc ? keys[at] : (General ? 0ull : ~0ull);
+          if (General) e2[i] = es[at];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        below += (General ? (k[i] > kc || (k[i] == kc && e2[i] < ec)) : k[i] < kc) ? 1 : 0;
     }
     if (c < nc && below) atomicAdd(&rk[c], below);
   }
@@ -1587,13 +1601,12 @@ __device__ __forceinline__ void rank_units(int nc, const uint64_t *keys, const i
 // ck + d E16 (E16 = E rounded up to 16; the keys were set to ~0, which sorts
 // after every candidate) from the domain's LDS counter ccnt[d] (the slots'
 // order is arbitrary).  Each candidate's rank among its domain's candidates
-// by key (D descending, e ascending; keys are distinct) is then counted in
-// parts of 16 keys: the waves are split among the domains (one domain after
-// another when there are more domains than waves), and a wave takes 64
-// candidates, one per lane, against one part, whose keys every lane reads
-// alike (broadcast reads; with lanes on different parts the reads, 128 bytes
-// apart, met on one LDS bank: a plan of 1.6 M ids with 192 candidates in each
-// of 4 domains took 111.6 us, 52.2 with broadcast reads).  rk[d E + c] = the rank of the domain's candidate in slot c.
+// by key (D descending, e ascending; keys are distinct) is then counted: the
+// waves are split among the domains (one domain after another when there are
+// more domains than waves; rank_keys).  (With lanes on different parts the
+// reads, 128 bytes apart, met on one LDS bank: a plan of 1.6 M ids with 192
+// candidates in each of 4 domains took 111.6 us, 52.2 with broadcast reads.)
+// rk[d E + c] = the rank of the domain's candidate in slot c.
 // The ranks below cap1 name the domain's stage-1 replicas.  rk: M E words.
 __device__ __forceinline__ void stage1_ranks(const Plan &p, const int *om, uint64_t *ck, int *ccnt, int *rk) {
   const int tid = threadIdx.x, nt = blockDim.x, E = p.E, G = p.G, M = p.M, E16 = (E + 15) & ~15;
@@ -1618,29 +1631,13 @@ __device__ __forceinline__ void stage1_ranks(const Plan &p, const int *om, uint6
   }
   lds_barrier();
   STAMP(p, 24);
-  const int nw = nt >> 6, wave = uniform_i32(tid >> 6), lane = tid & 63;
+  const int nw = nt >> 6, wave = uniform_i32(tid >> 6);
   const int wpd = p.s1_waves;
   const int d0 = wpd ? (int)fdiv((uint32_t)wave, p.fS1) : 0;
   const int step = wpd ? wpd : nw, first = wpd ? wave - d0 * wpd : wave;
   for (d = d0; d < (wpd ? imin(d0 + 1, M) : M); ++d) {
     const int nc = uniform_i32(ccnt[d]);   // (d is the same in the whole wave)
-    const int blocks = (nc + 63) >> 6, parts = (nc + 15) >> 4;
-    const int lb = blocks <= 1 ? 0 : 32 - __clz(blocks - 1);
-    const uint64_t *kd = ck + d * E16;
-    for (int u = first; u < (parts << lb); u += step) {
-      const int blk = u & ((1 << lb) - 1), part = u >> lb;
-      if (blk >= blocks) continue;
-      const int c = blk * 64 + lane;
-      const uint64_t kc = kd[imin(c, nc - 1)];
-      const uint64_t *kp = kd + 16 * part;
-      uint64_t k[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) k[i] = kp[i];
-      int below = 0;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) below += k[i] < kc ? 1 : 0;
-      if (c < nc && below) atomicAdd(&rk[d * E + c], below);
-    }
+    rank_keys<false, true>(nc, ck + d * E16, nullptr, rk + d * E, first, step);
   }
   lds_barrier();
   STAMP(p, 26);
@@ -1960,8 +1957,9 @@ __device__ __forceinline__ void domain_solver(const Plan &p0, int *sm) {
       if (wg == 0) STAMP(p, 16);
       const int nc = misc[1];
       if (wg == 0 && tid == 0) stamp_nc(nc);
-      if (p.general) rank_units<true>(nc, ck, qcol, qcol + E);
-      else rank_units<false>(nc, ck, nullptr, qcol + E);
+      const int wave = uniform_i32(tid >> 6), nw = nt >> 6;
+      if (p.general) rank_keys<true, false>(nc, ck, qcol, qcol + E, wave, nw);
+      else rank_keys<false, false>(nc, ck, nullptr, qcol + E, wave, nw);
       lds_barrier();
       // the first cap ranks name the domain's stage-1 replicas
       for (int c = tid; c < nc; c += nt) {

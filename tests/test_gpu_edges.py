@@ -16,6 +16,8 @@ pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(),
     (8, 4, 256, 3, (0, 1, 15, 16, 17, 63, 64, 65, 127, 128)),   # half the waves per domain
     (32, 1, 64, 5, (1, 16, 17, 62)),                              # more domains than waves
     (6, 2, 192, 70, (33, 128)),                                   # more slots than candidates
+    (8, 4, 640, 3, (129, 192, 193, 256, 319, 320)),               # three to five times 64 candidates
+    (24, 1, 192, 2, (65, 129, 184)),                              # those, and more domains than waves
 ])
 def test_stage1_candidate_counts(R, G, E, N, counts, solver):
     """Exactly c stage-1 candidates in domain 0 (W = 0: an expert is one when
@@ -33,6 +35,27 @@ def test_stage1_candidate_counts(R, G, E, N, counts, solver):
         tk = np.repeat(np.arange(E, dtype=np.int32), omega[s]).reshape(-1, 1)
         both(R, G, E, s, 1, 8, 64, 0, N, omega, np.ascontiguousarray(tk), launch=SOLVERS[solver],
              what="stage 1, %d candidates R=%d G=%d E=%d N=%d %s" % (c, R, G, E, N, solver))
+
+
+@pytest.mark.parametrize("c", [1, 63, 64, 65, 127, 129, 300, 512, 577])
+def test_stage1_candidate_counts_general(c):
+    """The same under a general cost model, where the candidates are ranked by
+    benefits that tie in pairs and follow the experts' sizes."""
+    from test_gpu_costs import both as both_costs
+    R, G, E, N, S = 8, 4, 1280, 3, 64
+    rng = np.random.default_rng(c)
+    omega = rng.integers(0, 3, size=(R, E)).astype(np.int32)
+    omega[:G] = 0
+    hot = rng.choice(np.arange(E // 2, E), size=c, replace=False)
+    omega[rng.integers(0, G), hot] = 1 + (np.arange(c) // 2).astype(np.int32)
+    near = rng.integers(1, 4, size=(R, R))
+    cost = np.triu(near, 1) + np.triu(near, 1).T
+    sizes = 2 * S * rng.integers(0, 2, size=E)
+    sizes[hot[omega[:G, hot].sum(0) < 2]] = 0   # every hot expert's benefit is positive
+    s = R - 1
+    tk = np.repeat(np.arange(E, dtype=np.int32), omega[s]).reshape(-1, 1)
+    both_costs(R, G, E, s, 1, 8, S, 0, N, omega, np.ascontiguousarray(tk), C=cost.astype(np.int32),
+               We=sizes.astype(np.int64), what="general stage 1, %d candidates" % c)
 
 
 def _zipf_case(R, G, E, N, n, k, seed, S=4096, W=9 << 20):

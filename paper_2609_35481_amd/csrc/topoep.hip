@@ -4,7 +4,7 @@
 // Three kernels per plan, enqueued back to back on one stream:
 //
 //   hist     one block per contiguous chunk of the flattened [T, k] ids, one
-//            LDS row of counts per wave, one LDS atomic per id.  Writes the
+//            LDS row of counts, one LDS atomic per id.  Writes the
 //            block's partial histogram (this rank's row of the routing
 //            matrix Omega, Eq. 3, Section 3.1).
 //   solve    the placement solver, in one of two shapes:
@@ -630,67 +630,70 @@ __device__ __forceinline__ bool grid_barrier(uint32_t *count, uint32_t groups, u
 
 // ---------------------------------------------------------------- histogram
 
-typedef int v4i __attribute__((ext_vector_type(4)));   // one 16-byte word
-
-// V 16-byte loads of four consecutive ids per lane from base on (256 V ids a
-// wave; base a multiple of 64 ids), -1 from `end` on; vec: the array is
-// 16-byte aligned.  The ids are read once per kernel: non-temporal loads.
-template <int V>
-__device__ inline void load_ids(const int32_t *ids, int64_t base, int64_t end, bool vec, int (&v)[4 * V]) {
+// K ids per lane from base on (64 K ids a wave; base a multiple of 64 ids), -1
+// from `end` on: W = min(K, 4) consecutive ids at a time, one load of 4 W
+// bytes where the array is 16-byte aligned (vec); element W j + c of lane l is
+// id (j * 64 + l) * W + c.  Last: nothing reads the ids after this kernel
+// (non-temporal loads; see hist_kernel).
+template <int K, bool Last>
+__device__ inline void load_ids(const int32_t *ids, int64_t base, int64_t end, bool vec, int (&v)[K]) {
+  constexpr int W = K < 4 ? K : 4;
+  typedef int words __attribute__((ext_vector_type(W)));
 #pragma unroll
-  for (int j = 0; j < V; ++j) {
-    const int64_t idx = base + (int64_t)(j * 64 + lane_id()) * 4;
-    if (vec && idx + 4 <= end) {
-      const v4i x = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(ids + idx));
-      v[4 * j] = x.x;
-      v[4 * j + 1] = x.y;
-      v[4 * j + 2] = x.z;
-      v[4 * j + 3] = x.w;
+  for (int j = 0; j < K / W; ++j) {
+    const int64_t idx = base + (int64_t)(j * 64 + lane_id()) * W;
+    if (vec && idx + W <= end) {
+      const words *at = reinterpret_cast<const words *>(ids + idx);
+      const words x = Last ? __builtin_nontemporal_load(at) : *at;
+#pragma unroll
+      for (int c = 0; c < W; ++c) v[W * j + c] = x[c];
     } else {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) v[4 * j + c] = idx + c < end ? ids[idx + c] : -1;
+      for (int c = 0; c < W; ++c) v[W * j + c] = idx + c < end ? ids[idx + c] : -1;
     }
   }
 }
 
-// One contiguous chunk per block, in tiles of 256 V ids per wave; each wave
-// counts into its own LDS row, one atomic per id, the next tile's loads in
-// flight meanwhile.
-template <int V>
+// One contiguous chunk per block, in tiles of 64 K ids per wave, counted into
+// one LDS row, one atomic per id, the next tile's loads in flight meanwhile.
+// Bound: HBM from some 16 M ids on (2^26 ids, E = 128: 54.5 us, 4.9 TB/s), the
+// launch below.  A row per wave, summed at the end, costs more than the atomics
+// that meet in one (2^24 ids, E = 128: 19.2 us, 17.0; 2^17 ids, E = 1024: 4.2,
+// 3.2).  The loads keep the ids in the caches for the reroute, whose own are
+// non-temporal: plans of 2^26 / 2^24 ids, E = 128, inputs that alternate, 151 /
+// 53 us; 164 / 56 with plain loads in both, 170 / 61 non-temporal in both.
+template <int K>
 __global__ __launch_bounds__(1024, 8) void hist_kernel(Plan p) {
   extern __shared__ int smem_h[];
+  constexpr int W = K < 4 ? K : 4;
   const int tid = threadIdx.x, nt = blockDim.x, nw = nt >> 6, lane = tid & 63, wave = tid >> 6, E = p.E;
   const int b = blockIdx.x;
-  int *h = smem_h + wave * E;
+  int *h = smem_h;
   const int64_t lo = (int64_t)b * p.chunk;
   const int64_t hi = lo + p.chunk < p.n ? lo + p.chunk : p.n;
   const bool vec = (reinterpret_cast<uintptr_t>(p.topk) & 15) == 0;
-  const int64_t tile = (int64_t)nw * 256 * V, wofs = (int64_t)wave * 256 * V;
-  int nx[4 * V];
-  load_ids<V>(p.topk, lo + wofs, hi, vec, nx);
-  for (int e = lane; e < E; e += 64) h[e] = 0;
-  wave_sync();
+  const int64_t tile = (int64_t)nw * 64 * K, wofs = (int64_t)wave * 64 * K;
+  int nx[K];
+  load_ids<K, false>(p.topk, lo + wofs, hi, vec, nx);
+  for (int e = tid; e < E; e += nt) h[e] = 0;
+  __syncthreads();
   int bad = 0;
   for (int64_t base = lo + wofs; base < hi; base += tile) {
-    int ev[4 * V];
+    int ev[K];
 #pragma unroll
-    for (int i = 0; i < 4 * V; ++i) ev[i] = nx[i];
-    if (base + tile < hi) load_ids<V>(p.topk, base + tile, hi, vec, nx);
+    for (int i = 0; i < K; ++i) ev[i] = nx[i];
+    if (base + tile < hi) load_ids<K, false>(p.topk, base + tile, hi, vec, nx);
     // ids of the wave's piece that exist
-    const int lim = (int)(hi - base < 256 * V ? hi - base : 256 * V);
+    const int lim = (int)(hi - base < 64 * K ? hi - base : 64 * K);
 #pragma unroll
-    for (int i = 0; i < 4 * V; ++i) {
+    for (int i = 0; i < K; ++i) {
       const bool valid = (unsigned)ev[i] < (unsigned)E;   // (-1 past the end)
-      bad |= !valid && ((i >> 2) * 64 + lane) * 4 + (i & 3) < lim ? 1 : 0;
+      bad |= !valid && (i / W * 64 + lane) * W + i % W < lim ? 1 : 0;
       if (valid) atomicAdd(&h[ev[i]], 1);
     }
   }
   bad = __syncthreads_or(bad);
-  for (int e = tid; e < E; e += nt) {
-    int sum = 0;
-    for (int w = 0; w < nw; ++w) sum += smem_h[w * E + e];
-    p.partials[(int64_t)b * E + e] = sum;
-  }
+  for (int e = tid; e < E; e += nt) p.partials[(int64_t)b * E + e] = h[e];
   if (tid == 0) p.blk_err[b] = bad;
 }
 
@@ -3043,21 +3046,18 @@ __device__ inline void scan_wave_columns(int *wc, int ws, int n, int nw, int *ba
 // start in entry j and run past its end; tx[e] is then the index of e's next
 // occurrence.
 //
-// Bound: HBM (4 B read and 4 B written per id): 80 us for 2^26 ids, 6.7 TB/s.
-// Ranking every id (a ballot per id bit) was issue bound in a long chain of
-// tiles; 256-thread blocks of it, 3641 of them, reached 85 us, but the solver
-// then summed 3641 rows of counts (36 us, now 512 rows, 10).  One contiguous
-// part per wave instead of a tile shared by the waves: 90 us, and 67 against
-// 47 for the histogram (8192 streams of 2 KB pieces).  Plan with inputs that
-// alternate, 2^26 ids, E = 128: 193 -> 131 us.
+// Bound: HBM (4 B read and 4 B written per id): 101 us for 2^26 ids, E = 128,
+// inputs that alternate, 5.3 TB/s.  Ranking every id (a ballot per id bit) in
+// 256-thread blocks, 4096 of them, took 147 us, and the solver summed 4096 rows
+// of counts (42 us, now 512 rows, 10): plan 278 -> 151 us.
 //
 // Slots: also the send-buffer slots.  A wave's piece of a tile is then read
-// in 4-byte order (element i of lane l is id i * 64 + l), else 16 bytes per
-// lane (element 4 j + c is id (j * 64 + l) * 4 + c).
-template <int V, bool Slots>
+// in 4-byte order (element i of lane l is id i * 64 + l), else as load_ids
+// does.
+template <int K, bool Slots>
 __global__ __launch_bounds__(1024, 8) void reroute_kernel(Plan p) {
   extern __shared__ int smem_r[];
-  constexpr int K = 4 * V;   // ids per lane and tile
+  constexpr int W = K < 4 ? K : 4;   // consecutive ids of a lane (load_ids)
   const int tid = threadIdx.x, nt = blockDim.x, nw = nt >> 6, lane = tid & 63, wave = tid >> 6;
   const int E = p.E, es = E | 1, rs = p.R | 1;
   int2 *ent = reinterpret_cast<int2 *>(smem_r);   // nent_cap: (cumulative share, rank) per entry
@@ -3090,7 +3090,7 @@ __global__ __launch_bounds__(1024, 8) void reroute_kernel(Plan p) {
 #pragma unroll
       for (int i = 0; i < K; ++i) nx[i] = base + i * 64 + lane < hi ? p.topk[base + i * 64 + lane] : -1;
     } else {
-      load_ids<V>(p.topk, base, hi, vec, nx);
+      load_ids<K, true>(p.topk, base, hi, vec, nx);
     }
   };
   // the first tile's ids are on their way while the tables are made
@@ -3181,17 +3181,17 @@ __global__ __launch_bounds__(1024, 8) void reroute_kernel(Plan p) {
           }
         } else {
 #pragma unroll
-          for (int j = 0; j < V; ++j) {
+          for (int j = 0; j < K; j += W) {
             int below = seen;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-              const uint64_t m = __ballot(ev[4 * j + c] == ec);
+            for (int c = 0; c < W; ++c) {
+              const uint64_t m = __ballot(ev[j + c] == ec);
               below = count_below(m, below);
               seen += __popcll(m);
             }
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-              if (ev[4 * j + c] == ec) dv[4 * j + c] = INT_MIN | below++;
+            for (int c = 0; c < W; ++c)
+              if (ev[j + c] == ec) dv[j + c] = INT_MIN | below++;
           }
         }
         if (lane == 0) mywc[ec] = seen;
@@ -3241,19 +3241,18 @@ __global__ __launch_bounds__(1024, 8) void reroute_kernel(Plan p) {
       }
     } else {
 #pragma unroll
-      for (int j = 0; j < V; ++j) {
-        const int64_t idx = base + (int64_t)(j * 64 + lane) * 4;
-        if (vec_out && idx + 4 <= hi) {
-          v4i x;
-          x.x = dv[4 * j];
-          x.y = dv[4 * j + 1];
-          x.z = dv[4 * j + 2];
-          x.w = dv[4 * j + 3];
-          __builtin_nontemporal_store(x, reinterpret_cast<v4i *>(p.dest_out + idx));
+      for (int j = 0; j < K; j += W) {
+        typedef int words __attribute__((ext_vector_type(W)));
+        const int64_t idx = base + (int64_t)(j * 64 + lane * W);
+        if (vec_out && idx + W <= hi) {
+          words x;
+#pragma unroll
+          for (int c = 0; c < W; ++c) x[c] = dv[j + c];
+          __builtin_nontemporal_store(x, reinterpret_cast<words *>(p.dest_out + idx));
         } else {
 #pragma unroll
-          for (int c = 0; c < 4; ++c)
-            if (idx + c < hi) p.dest_out[idx + c] = dv[4 * j + c];
+          for (int c = 0; c < W; ++c)
+            if (idx + c < hi) p.dest_out[idx + c] = dv[j + c];
         }
       }
     }
@@ -4138,7 +4137,7 @@ int setup(const topoep_topology *t, int32_t T, int32_t k, int32_t N, const topoe
       s.lds_one = (size_t)words * 4;
     }
   }
-  s.lds_hist = (size_t)E * 4 * (s.bt / 64);
+  s.lds_hist = (size_t)E * 4;
   s.lds_reroute = lds_reroute(s.bt);
   s.lds_fused = 0;
   if (lds_bound > (size_t)kLdsLimit) return TOPOEP_ELIMIT;
@@ -4251,9 +4250,13 @@ void set_attrs() {
   allow_lds(plan_domains_kernel<8>);
   allow_lds(hist_kernel<1>);
   allow_lds(hist_kernel<2>);
+  allow_lds(hist_kernel<4>);
+  allow_lds(hist_kernel<8>);
   allow_lds(reroute_kernel<1, false>);
-  allow_lds(reroute_kernel<1, true>);
   allow_lds(reroute_kernel<2, false>);
+  allow_lds(reroute_kernel<4, false>);
+  allow_lds(reroute_kernel<4, true>);
+  allow_lds(reroute_kernel<8, false>);
   allow_lds(solve_kernel<512>);
   allow_lds(solve_kernel<1024>);
   allow_lds(solve_single_kernel<kRefineLanes>);
@@ -4277,19 +4280,24 @@ void set_attrs() {
   g_attrs_set = true;
 }
 
-// Four ids per lane and load: two loads a tile from 8 ids per thread on.
 void launch_hist(const Plan &p, const Shape &s, hipStream_t st) {
   const dim3 g(p.nb), b(s.bt);
-  if (s.ipt < 8) hipLaunchKernelGGL(hist_kernel<1>, g, b, s.lds_hist, st, p);
-  else hipLaunchKernelGGL(hist_kernel<2>, g, b, s.lds_hist, st, p);
+  switch (s.ipt) {
+    case 1: hipLaunchKernelGGL(hist_kernel<1>, g, b, s.lds_hist, st, p); break;
+    case 2: hipLaunchKernelGGL(hist_kernel<2>, g, b, s.lds_hist, st, p); break;
+    case 4: hipLaunchKernelGGL(hist_kernel<4>, g, b, s.lds_hist, st, p); break;
+    default: hipLaunchKernelGGL(hist_kernel<8>, g, b, s.lds_hist, st, p); break;
+  }
 }
 
 // (with slots four ids a tile: eight spill the 64 registers of two blocks a CU)
 void launch_reroute(const Plan &p, const Shape &s, hipStream_t st) {
   const dim3 g(p.nb), b(s.bt);
-  if (p.slot_out) hipLaunchKernelGGL((reroute_kernel<1, true>), g, b, s.lds_reroute, st, p);
-  else if (s.ipt < 8) hipLaunchKernelGGL((reroute_kernel<1, false>), g, b, s.lds_reroute, st, p);
-  else hipLaunchKernelGGL((reroute_kernel<2, false>), g, b, s.lds_reroute, st, p);
+  if (p.slot_out) hipLaunchKernelGGL((reroute_kernel<4, true>), g, b, s.lds_reroute, st, p);
+  else if (s.ipt == 1) hipLaunchKernelGGL((reroute_kernel<1, false>), g, b, s.lds_reroute, st, p);
+  else if (s.ipt == 2) hipLaunchKernelGGL((reroute_kernel<2, false>), g, b, s.lds_reroute, st, p);
+  else if (s.ipt == 4) hipLaunchKernelGGL((reroute_kernel<4, false>), g, b, s.lds_reroute, st, p);
+  else hipLaunchKernelGGL((reroute_kernel<8, false>), g, b, s.lds_reroute, st, p);
 }
 
 void launch_solve(const Plan &p, const Shape &s, hipStream_t st) {

@@ -80,13 +80,13 @@ def test_large_batches(R, G, E, N, n):
     both(*_zipf_case(R, G, E, N, n, 1, n % 97 + R), what="large batch R=%d E=%d n=%d" % (R, E, n))
 
 
-@pytest.mark.parametrize("offset", [0, 1, 3])
-def test_large_batch_unaligned(offset):
-    """ids and destinations that do not start on a 16-byte boundary."""
+def _check_at_offset(args, offset, launch, what):
+    """A plan whose ids and destinations start `offset` words past a 16-byte
+    boundary, against the oracle; the words around the destinations stay."""
     from test_gpu_parity import DEV, assert_same, ref_plan, topoep
-    R, G, E, s, cI, cX, S, W, N, omega, tk = args = _zipf_case(32, 8, 128, 2, (1 << 20) + 77, 1, 5)
+    R, G, E, s, cI, cX, S, W, N, omega, tk = args
     topo = topoep.topology(R, G, E, s, cI, cX, S, W)
-    p = topoep.Planner(topo, tk.shape[0], 1, N, device=DEV)
+    p = topoep.Planner(topo, tk.shape[0], 1, N, device=DEV, launch=launch)
     ids = torch.zeros(tk.size + 4, dtype=torch.int32, device=DEV)
     ids[offset:offset + tk.size] = torch.from_numpy(tk.ravel()).to(DEV)
     dest = torch.full((tk.size + 4,), -9, dtype=torch.int32, device=DEV)
@@ -95,9 +95,27 @@ def test_large_batch_unaligned(offset):
     torch.cuda.synchronize()
     got = dict(replica_slots=p.replica_slots.cpu().numpy(), token_dest=p.token_dest.cpu().numpy(),
                send_counts=p.send_counts.cpu().numpy(), status=int(p.status[0]), move_count=int(p.status[1]))
-    assert_same(got, ref_plan(*args), "unaligned by %d" % offset)
+    assert_same(got, ref_plan(*args), what)
     rest = torch.cat([dest[:offset], dest[offset + tk.size:]])
-    assert bool((rest == -9).all())
+    assert bool((rest == -9).all()), what
+
+
+@pytest.mark.parametrize("offset", [0, 1, 3])
+def test_large_batch_unaligned(offset):
+    """ids and destinations that do not start on a 16-byte boundary."""
+    _check_at_offset(_zipf_case(32, 8, 128, 2, (1 << 20) + 77, 1, 5), offset, None, "unaligned by %d" % offset)
+
+
+@pytest.mark.parametrize("ipt", [1, 2, 4, 8])
+@pytest.mark.parametrize("threads,tiles", [(64, 1), (64, 3), (256, 1), (1024, 2)])
+def test_ids_per_thread(ipt, threads, tiles):
+    """One, two and four ids a load: edges of the wave's piece and of the
+    block's chunk, aligned and not; experts whose share ends in a chunk."""
+    chunk = ipt * threads * tiles
+    for n in (1, 64 * ipt - 1, 64 * ipt + 1, chunk - 1, chunk, 3 * chunk + 5):
+        for offset in (0, 2):
+            _check_at_offset(_zipf_case(32, 8, 128, 2, n, 1, n % 97 + ipt), offset, (ipt, threads, tiles, 0, 1),
+                             "%d ids per thread, %d x %d, n=%d offset %d" % (ipt, threads, tiles, n, offset))
 
 
 def _domain_case(name, seed=3):

@@ -1022,7 +1022,8 @@ __device__ __forceinline__ uint32_t refine_domain_lanes(const Plan &p, int d, in
       const int lf = readlane_i32(lfv, 0);
       constexpr uint32_t ranks = (1u << GM) - 1u;
       const uint32_t tf = (uint32_t)__ballot(low && room && lj == lfv) & ranks;   // lightest with a free slot
-      const uint32_t th = (uint32_t)__ballot(low && lj <= lfv) & ranks & ~tf;     // others no heavier
+      // others no heavier (lanes beyond the ranks hold -1 and no room: neither)
+      const uint32_t th = (uint32_t)__ballot(low && (uint32_t)lj <= (uint32_t)lfv) & ranks & ~tf;
       const int t1 = tf ? __ffs(tf) - 1 : 0, dfree = tf ? (Lb - lf) >> 1 : 0;
       auto field = [&](uint64_t w, int t) { return (int)(w >> (BW * t)) & (int)FM; };
       // instance a: expert e, load u, position word w, q[rb], q[t1]

@@ -911,8 +911,9 @@ __device__ inline uint32_t wave_min_u32(uint32_t v) {
 // target's instance needs no search.  At the start every expert has one
 // instance in the domain at most; the caller sets pi for that.  Same moves in
 // the same order as the LDS form.  A move's candidates are scored
-//   - Pairs = 1 or 2 (at most 8 or 16 instances per rank, GM = 8): one lane
-//     per (instance of the busiest rank, target rank), one or two each;
+//   - Pairs = 1 or 2 (at most 8 or 16 instances per rank with GM = 8, 4 or 8
+//     with GM = 16): one lane per (instance of the busiest rank, target rank),
+//     one or two each;
 //   - else one lane per instance, against its lightest receivers only (its
 //     other targets cannot win, see refine_domain): the lightest ranks with
 //     a free slot, the same for every instance (usually one), and the ranks
@@ -926,11 +927,14 @@ __device__ inline uint32_t wave_min_u32(uint32_t v) {
 // shape (18 moves on one wave) 32.4 -> 23.8 us, DeepSeek-V3's with 4 slots
 // (75 over 4 waves) 58.4 -> 45.0, E = 640 on one node (35 moves, 82 instances
 // a rank: one lane per instance; pairs took 90 us there, and lanes 62.6 on
-// the 12 instances a rank of DeepSeek-V3's) 59.4 -> 45.9.
+// the 12 instances a rank of DeepSeek-V3's) 59.4 -> 45.9.  Pairs with sixteen
+// ranks a node matter where loads are small and ties many: EP 64, E = 192, one
+// slot, 147 tokens (71 moves) 47.5 us a plan with a lane per instance, 32.5;
+// EP 32, E = 128, three slots, 4096 tokens 109 and 83.
 template <int GM, int Pairs, bool Plain>
 __device__ __forceinline__ uint32_t refine_domain_lanes(const Plan &p, int d, int *e_of, int *U, uint64_t *pi,
                                                         int *qcol, int *slots, int *used, int *Lr, uint32_t *flags) {
-  static_assert(Pairs == 0 || GM == 8, "eight targets per instance");
+  constexpr int IR = 64 / GM;   // Pairs: instances of a round
   constexpr int BW = GM == 8 ? 8 : 4;
   constexpr uint32_t FM = (1u << BW) - 1u;
   const int lane = lane_id();
@@ -987,7 +991,7 @@ __device__ __forceinline__ uint32_t refine_domain_lanes(const Plan &p, int d, in
       uint64_t ws[Pairs];
 #pragma unroll
       for (int i = 0; i < Pairs; ++i) {
-        const int a = a0 + (c + 8 * i < PN ? c + 8 * i : 0);
+        const int a = a0 + (c + IR * i < PN ? c + IR * i : 0);
         const int *qa = qcol + a * QS + r0;
         es[i] = e_of[a];
         us[i] = U[a];
@@ -998,7 +1002,7 @@ __device__ __forceinline__ uint32_t refine_domain_lanes(const Plan &p, int d, in
 #pragma unroll
       for (int i = 0; i < Pairs; ++i) {
         const int pos = (int)(((fhi ? (uint32_t)(ws[i] >> 32) : (uint32_t)ws[i]) >> fsh) & FM);
-        const bool on = c + 8 * i < PN && us[i] > 0 && low && (room || pos != 0);
+        const bool on = c + IR * i < PN && us[i] > 0 && low && (room || pos != 0);
         const int sd = on ? imin(us[i], gap >> 1) : 0;
         const int sx = own_moves(sd, us[i], qt[i], qb[i]);
         bool lt = i == 0 || sd > bd;
@@ -1106,7 +1110,7 @@ __device__ __forceinline__ uint32_t refine_domain_lanes(const Plan &p, int d, in
     RSECT(1);
     const int wl = __ffsll((long long)win) - 1;
     const int rtj = Pairs ? wl & (GM - 1) : readlane_i32(bt, wl);
-    const int aw = Pairs == 0 ? readlane_i32(ba, wl) : a0 + wl / GM + (Pairs > 1 ? 8 * readlane_i32(ba, wl) : 0);
+    const int aw = Pairs == 0 ? readlane_i32(ba, wl) : a0 + wl / GM + (Pairs > 1 ? IR * readlane_i32(ba, wl) : 0);
     const int pos = readlane_i32(bpos, wl), ew = readlane_i32(be, wl);
     const uint64_t ww = pi[aw];   // (with the column's words below: one round trip)
     const int at = pos ? pos - 1 : P + readlane_i32(uj, rtj);   // the target's instance: held, or its first free slot
@@ -1214,6 +1218,8 @@ __device__ __forceinline__ uint32_t refine_domain_in_lanes(const Plan &p, int d,
   if (p.G <= 8)
     return plain ? refine_domain_lanes<8, 0, true>(p, d, e_of, U, pi, qcol, slots, used, Lr, flags)
                  : refine_domain_lanes<8, 0, false>(p, d, e_of, U, pi, qcol, slots, used, Lr, flags);
+  if (p.PN <= 4) return refine_domain_lanes<16, 1, false>(p, d, e_of, U, pi, qcol, slots, used, Lr, flags);
+  if (p.PN <= 8) return refine_domain_lanes<16, 2, false>(p, d, e_of, U, pi, qcol, slots, used, Lr, flags);
   return refine_domain_lanes<16, 0, false>(p, d, e_of, U, pi, qcol, slots, used, Lr, flags);
 }
 

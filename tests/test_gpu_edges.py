@@ -359,6 +359,8 @@ def test_per_domain_one_launch_dispatch(name):
     (4, 2, 62, 2, 1), (4, 4, 63, 2, 0),     # 64 and 65: one and two rounds of instances
     (10, 5, 3, 3, 2), (72, 8, 2, 3, 1),     # ranks that fill no group of lanes; more than 64 sources
     (24, 12, 10, 4, 1), (24, 12, 10, 5, 1),  # 14 and 15 instances on more than 8 ranks: lanes, LDS form
+    (24, 12, 2, 2, 1), (32, 16, 3, 2, 1),   # 4 and 5: one and two pairs a lane
+    (18, 9, 5, 3, 0), (80, 16, 6, 3, 2),    # 8 and 9: pairs, one lane per instance
 ])
 def test_refinement_forms(R, G, P, N, cI, solver):
     """Moves at the edges of the refinement's forms, with hot experts on one

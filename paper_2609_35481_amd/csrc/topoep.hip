@@ -94,6 +94,7 @@ constexpr int kMaxSolveGroups = 128;    // co-resident by a wide margin (256 CUs
 constexpr int kMinBlocks = 2048;        // histogram/reroute blocks to aim for, at least
 constexpr int kMaxBlocks = 8192;        // and at most
 constexpr int64_t kOneTileIds = 1 << 20;   // above: blocks of 1024 threads
+constexpr int64_t kStreamIds = 1 << 24;    // above: the histogram reads past the caches
 constexpr int kOneThreads = 512;        // threads of plan_domains_kernel
 constexpr int kMaxOneGroups = 64;       // its workgroups at most (a quarter of 256 CUs)
 constexpr int kLongBlocks = 512;        // and at most this many of them (two per CU)
@@ -656,13 +657,16 @@ __device__ inline void load_ids(const int32_t *ids, int64_t base, int64_t end, b
 
 // One contiguous chunk per block, in tiles of 64 K ids per wave, counted into
 // one LDS row, one atomic per id, the next tile's loads in flight meanwhile.
-// Bound: HBM from some 16 M ids on (2^26 ids, E = 128: 54.5 us, 4.9 TB/s), the
+// Bound: HBM from some 16 M ids on (2^26 ids, E = 128: 53 us, 5.1 TB/s), the
 // launch below.  A row per wave, summed at the end, costs more than the atomics
 // that meet in one (2^24 ids, E = 128: 19.2 us, 17.0; 2^17 ids, E = 1024: 4.2,
-// 3.2).  The loads keep the ids in the caches for the reroute, whose own are
-// non-temporal: plans of 2^26 / 2^24 ids, E = 128, inputs that alternate, 151 /
-// 53 us; 164 / 56 with plain loads in both, 170 / 61 non-temporal in both.
-template <int K>
+// 3.2).  Plain loads keep the ids in the caches for the reroute, whose own are
+// non-temporal (plans of 2^24 ids, inputs that alternate: 53 us, 61 with
+// non-temporal loads in both).  Stream (more than kStreamIds ids, 64 MiB):
+// non-temporal here too.  Such plans one after another take 176 us for 2^26
+// ids, 167 with plain loads, but plain loads suffer where the caches are full
+// of other stores: after 268 MB of them the kernel takes 95 us, not 54.
+template <int K, bool Stream>
 __global__ __launch_bounds__(1024, 8) void hist_kernel(Plan p) {
   extern __shared__ int smem_h[];
   constexpr int W = K < 4 ? K : 4;
@@ -674,7 +678,7 @@ __global__ __launch_bounds__(1024, 8) void hist_kernel(Plan p) {
   const bool vec = (reinterpret_cast<uintptr_t>(p.topk) & 15) == 0;
   const int64_t tile = (int64_t)nw * 64 * K, wofs = (int64_t)wave * 64 * K;
   int nx[K];
-  load_ids<K, false>(p.topk, lo + wofs, hi, vec, nx);
+  load_ids<K, Stream>(p.topk, lo + wofs, hi, vec, nx);
   for (int e = tid; e < E; e += nt) h[e] = 0;
   __syncthreads();
   int bad = 0;
@@ -682,7 +686,7 @@ __global__ __launch_bounds__(1024, 8) void hist_kernel(Plan p) {
     int ev[K];
 #pragma unroll
     for (int i = 0; i < K; ++i) ev[i] = nx[i];
-    if (base + tile < hi) load_ids<K, false>(p.topk, base + tile, hi, vec, nx);
+    if (base + tile < hi) load_ids<K, Stream>(p.topk, base + tile, hi, vec, nx);
     // ids of the wave's piece that exist
     const int lim = (int)(hi - base < 64 * K ? hi - base : 64 * K);
 #pragma unroll
@@ -4255,10 +4259,11 @@ void set_attrs() {
   if (g_attrs_set) return;
   allow_lds(plan_domains_kernel<2>);
   allow_lds(plan_domains_kernel<8>);
-  allow_lds(hist_kernel<1>);
-  allow_lds(hist_kernel<2>);
-  allow_lds(hist_kernel<4>);
-  allow_lds(hist_kernel<8>);
+  allow_lds(hist_kernel<1, false>);
+  allow_lds(hist_kernel<2, false>);
+  allow_lds(hist_kernel<4, false>);
+  allow_lds(hist_kernel<8, false>);
+  allow_lds(hist_kernel<8, true>);
   allow_lds(reroute_kernel<1, false>);
   allow_lds(reroute_kernel<2, false>);
   allow_lds(reroute_kernel<4, false>);
@@ -4290,10 +4295,12 @@ void set_attrs() {
 void launch_hist(const Plan &p, const Shape &s, hipStream_t st) {
   const dim3 g(p.nb), b(s.bt);
   switch (s.ipt) {
-    case 1: hipLaunchKernelGGL(hist_kernel<1>, g, b, s.lds_hist, st, p); break;
-    case 2: hipLaunchKernelGGL(hist_kernel<2>, g, b, s.lds_hist, st, p); break;
-    case 4: hipLaunchKernelGGL(hist_kernel<4>, g, b, s.lds_hist, st, p); break;
-    default: hipLaunchKernelGGL(hist_kernel<8>, g, b, s.lds_hist, st, p); break;
+    case 1: hipLaunchKernelGGL((hist_kernel<1, false>), g, b, s.lds_hist, st, p); break;
+    case 2: hipLaunchKernelGGL((hist_kernel<2, false>), g, b, s.lds_hist, st, p); break;
+    case 4: hipLaunchKernelGGL((hist_kernel<4, false>), g, b, s.lds_hist, st, p); break;
+    default:
+      if (p.n > kStreamIds) hipLaunchKernelGGL((hist_kernel<8, true>), g, b, s.lds_hist, st, p);
+      else hipLaunchKernelGGL((hist_kernel<8, false>), g, b, s.lds_hist, st, p);
   }
 }
 

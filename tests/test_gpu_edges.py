@@ -71,7 +71,8 @@ def _zipf_case(R, G, E, N, n, k, seed, S=4096, W=9 << 20):
     return R, G, E, s, 1, 8, S, W, N, omega, tk
 
 
-@pytest.mark.parametrize("n", [(1 << 20) + 1, (1 << 20) + 8192, 3 * 8192 * 512 - 64, 512 * 8192 + 1, 5 * (1 << 20) + 7])
+@pytest.mark.parametrize("n", [(1 << 20) + 1, (1 << 20) + 8192, 3 * 8192 * 512 - 64, 512 * 8192 + 1, 5 * (1 << 20) + 7,
+                               (1 << 24) + 9])
 @pytest.mark.parametrize("R,G,E,N", [(32, 8, 128, 2), (64, 1, 64, 1), (6, 2, 30, 3)])
 def test_large_batches(R, G, E, N, n):
     """Blocks of 1024 threads above 2^20 ids: one tile, the last block of one

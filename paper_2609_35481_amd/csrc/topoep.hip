@@ -3608,7 +3608,7 @@ __device__ __forceinline__ void chunk_slots(const Plan &p, const int (&dv)[IPT],
 // (offset of the chunk) + (offset of the wave in the chunk) + (rank in the
 // wave) picks the instance from this rank's instance list.  A bounded wait
 // that gives up writes -1 and SYNC.
-template <int IPT, bool Count>
+template <int IPT, bool One>
 __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
   const ChunkLds l = chunk_lds(p, blockDim.x);
   int *wc = sm + l.wc, *run = sm + l.run, *ptr = sm + l.ptr;
@@ -3627,14 +3627,15 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
   }
   // the generation as the solver left it: the histogram buffer to add to
   const uint32_t gread = __hip_atomic_load(&p.ctrl[kCtrlGen], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  // Count: counting by LDS atomics lets the chunk arrive before its ids are
-  // ranked (Stress-like, eight ids per thread: 2.6 us after the start, 5.1
+  // Counting by LDS atomics lets the chunk arrive before its ids are ranked
+  // (One, Stress-like, eight ids per thread: 2.6 us after the start, 5.1
   // ranked first); up to 32 experts they meet on too few words, and the short
-  // ranks come first.  That pays where a grid barrier waits for the verdict;
-  // the single-workgroup solver plans meanwhile, and the last chunk's ranks
-  // after its arrival are on the path (EP 64, E = 128, 692 368 ids, eight per
-  // thread: 17.8 us, ranked first 16.9).
-  const bool rank_first = !Count || p.nbits <= 5;
+  // ranks come first.  With the single-workgroup solver, which plans meanwhile,
+  // the ranks of the last chunk to arrive are on the path: four or eight ids
+  // per thread are ranked first there (EP 64, E = 128, 692 368 ids: 17.8 us,
+  // ranked first 16.9; Qwen3-like with dispatch, one id: 11.0 and 11.2).
+  constexpr bool count = One || IPT <= 2;
+  const bool rank_first = !count || p.nbits <= 5;
   int *mywc = wc + wave * E;
   for (int e = lane; e < E; e += 64) mywc[e] = 0;
   wave_sync();
@@ -3698,7 +3699,7 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
   for (int i = 0; i < IPT; ++i) {
     const bool valid = (unsigned)ev[i] < (unsigned)E;
     if (!rank_first) lr[i] = wave_rank(ev[i], valid, p.nbits, mywc);
-    else if (Count) lr[i] += mywc[valid ? ev[i] : 0];
+    else if (count) lr[i] += mywc[valid ? ev[i] : 0];
   }
   // every count is written: this chunk's first occurrence index per expert
   bool ok = wait_flag(p, b, 1, gen + 1u, flag);
@@ -3711,7 +3712,7 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
 #pragma unroll
   for (int i = 0; i < IPT; ++i) {
     const int e = (unsigned)ev[i] < (unsigned)E ? ev[i] : 0;
-    rho[i] = run[e] + lr[i] + (Count ? 0 : mywc[e]);
+    rho[i] = run[e] + lr[i] + (count ? 0 : mywc[e]);
   }
   // the plan is ready
   ok = ok && wait_flag(p, b, 0, gen + 1u, flag);
@@ -3753,10 +3754,14 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
     return;
   }
   __syncthreads();
-  int dv[IPT];
   // the destination of each id: the entry of its expert's list that holds its
-  // occurrence (shares ascend)
-  auto place = [&](auto first) {
+  // occurrence (shares ascend).  With many domains a list may be long, and is
+  // halved down to four entries first (EP 48 over 24 nodes, 800 000 ids: 31.0
+  // us walked, 30.1; with four or eight ids per thread and three nodes the
+  // halving inside the loop costs 0.3 us, hence the loop of its own)
+  const bool long_lists = p.M > (One ? 4 : 8);
+  int dv[IPT];
+  if (One || long_lists) {
 #pragma unroll
     for (int i = 0; i < IPT; ++i) {
       const int64_t idx = wbase + i * 64;
@@ -3764,7 +3769,17 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
       if (idx < hi) {
         if ((unsigned)ev[i] < (unsigned)E) {
           const int j1 = ptr[ev[i] + 1];
-          for (int j = first(ptr[ev[i]], j1, rho[i]); j < j1; ++j) {
+          int j = ptr[ev[i]];
+          for (int len = long_lists ? j1 - j : 0; len > 4;) {
+            const int half = len >> 1;
+            if (ent[j + half - 1].x <= rho[i]) {
+              j += half;
+              len -= half;
+            } else {
+              len = half;
+            }
+          }
+          for (; j < j1; ++j) {
             const int2 en = ent[j];
             if (rho[i] < en.x) {
               dest = en.y;
@@ -3776,25 +3791,26 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
       }
       dv[i] = dest;
     }
-  };
-  if (p.M <= 8) {
-    place([&](int j, int, int) { return j; });
   } else {
-    // with many domains a list may be long: halved down to four entries first
-    // (EP 48 over 24 nodes, 800 000 ids: 31.0 us walked, 30.1; over 3 nodes
-    // the halving costs 0.3 us)
-    place([&](int j, int j1, int at) {
-      for (int len = j1 - j; len > 4;) {
-        const int half = len >> 1;
-        if (ent[j + half - 1].x <= at) {
-          j += half;
-          len -= half;
-        } else {
-          len = half;
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+      const int64_t idx = wbase + i * 64;
+      int dest = -1;
+      if (idx < hi) {
+        if ((unsigned)ev[i] < (unsigned)E) {
+          const int j1 = ptr[ev[i] + 1];
+          for (int j = ptr[ev[i]]; j < j1; ++j) {
+            const int2 en = ent[j];
+            if (rho[i] < en.x) {
+              dest = en.y;
+              break;
+            }
+          }
         }
+        p.dest_out[idx] = dest;
       }
-      return j;
-    });
+      dv[i] = dest;
+    }
   }
   if (p.slot_out) chunk_slots<IPT>(p, dv, wbase, hi, run, ptr, ent, so, gs, wc);
   if (b == 0) {

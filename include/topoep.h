@@ -71,7 +71,8 @@ typedef struct topoep_launch {
   int32_t block_threads;    /* 64..1024, multiple of 64, for histogram/reroute    */
   int32_t tiles_per_block;  /* >= 1; 0 = choose from the problem size             */
   int32_t solve_threads;    /* 64..1024, multiple of 64, for the solver           */
-  int32_t solver;           /* 0 = choose (3 when it fits, else 1, else 2);       */
+  int32_t solver;           /* 0 = choose (3 when it fits, else 1, else 2, whose */
+                            /*     three kernels' work a small plan runs as one);*/
                             /* 1 = three kernels (histogram, solver, reroute)    */
                             /*     with one solver workgroup for all domains     */
                             /*     (its whole state in LDS);                     */

@@ -2948,8 +2948,8 @@ __device__ __forceinline__ void swap_self_row(const Plan &p, const SingleState &
 // The same steps with every domain's state in the LDS of one CU; each
 // domain's refinement runs on its own wave.  Used when Omega and all q
 // columns fit in LDS.  Workgroups beyond the first compute the histogram
-// blocks' offsets for the reroute.  Form: kRefinePairs or kRefineLds, whichever
-// the shape takes (both in one kernel spilled registers).
+// blocks' offsets for the reroute.  Form: the refinement's form for the shape
+// (refine_form), one a kernel: two together spilled registers.
 template <int Form>
 __global__ __launch_bounds__(1024) void solve_single_kernel(Plan p0) {
   extern __shared__ int64_t smem_1[];
@@ -3823,8 +3823,8 @@ __device__ __forceinline__ void fused_chunk(const Plan &p, int b, int *sm) {
 // The whole plan in one launch: workgroup 0 solves, workgroups 1..nb hold
 // the ids; all are resident at once (nb <= kMaxFusedBlocks) and every wait
 // is bounded.
-// Form: the refinement's form for the shape (refine_form: registers with
-// (instance, target) pairs, registers, or LDS); one instantiation each keeps
+// Form: the refinement's form for the shape (refine_form: (instance, target)
+// pairs in lanes, instances in lanes, or LDS); one instantiation each keeps
 // the others' registers out.
 template <int IPT, int Form>
 __global__ __launch_bounds__(1024) void plan_fused_kernel(Plan p) {

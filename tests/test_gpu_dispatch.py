@@ -5,7 +5,7 @@ bit for bit.
 
 Cases: the workload configurations at full size (every plan output too),
 seeded random tiny instances for every self rank, and the layout kernel
-alone on synthetic destinations: ragged sizes, many workgroups (look-back
+alone on synthetic destinations: ragged sizes, many workgroups (group totals
 across several windows of predecessors), non-rank destinations, one rank,
 the largest rank count, an empty batch, and back-to-back calls on one
 workspace.
@@ -176,9 +176,9 @@ def layout_case(R, n, rng, k=8, invalid=0.0, skew=None):
     (32, 65536 + 8 * 37, 0.05, None),   # ragged, some non-rank destinations
     (1, 5000, 0.0, None),
     (1024, 200000, 0.01, 0.8),      # the most ranks
-    (64, (1 << 20) + 24, 0.0, 1.2),   # 256 workgroups: look-back across windows
+    (64, (1 << 20) + 24, 0.0, 1.2),   # 129 workgroups of eight ids per thread: nine groups
     (7, 8 * 3, 0.0, None),          # smaller than one wave
-    (32, 5000000, 0.01, 1.0),       # 2 tiles per workgroup: counts first, ranks after the look-back
+    (32, 5000000, 0.01, 1.0),       # 2 tiles per workgroup: counts first, ranks after the wait
     (256, (1 << 24) + 8 * 13, 0.0, 1.4),   # 5 tiles per workgroup, ragged last tile
     (512, (1 << 22) + 8 * 5, 0.01, 1.1),   # several tiles, two copies of the counts
     (1024, (1 << 22) + 8 * 3, 0.0, 0.9),   # several tiles, one copy (the most ranks)

@@ -338,7 +338,9 @@ SOLVE_SLOTS = [(0, "solver start"), (14, "s1: rows copied"), (15, "s1: row self"
                (13, "list done")]
 FLAG_SLOTS = [(46, "flags released")] + CHUNK_SLOTS
 
-REFINE_SECTIONS = ["busiest and levels", "scoring", "selection", "target instance", "transfer", "updates"]
+# sections of a refinement move: the lane forms have five, the LDS form six
+REFINE_SECTIONS = {5: ["scoring", "minima", "ranks and next busiest", "transfer", "updates"],
+                   6: ["busiest and levels", "scoring", "selection", "target instance", "transfer", "updates"]}
 
 
 def run_phases(args):
@@ -373,7 +375,8 @@ def run_phases(args):
             w = p.workspace_view()[64:256].cpu().numpy().view(np.uint32).astype(np.int64)
             samples.append([((int(w[i]) - int(w[0])) & 0xFFFFFFFF) if w[i] else np.nan for i, _ in slots])
             if w[38] > 0:
-                refine.append([w[32 + k] / w[38] for k in range(6)] + [w[38]])
+                sections = 6 if w[37] else 5
+                refine.append([w[32 + k] / w[38] for k in range(sections)] + [w[38]])
     clk = []
     for p in planners:
         w = p.workspace_view()[64:256].cpu().numpy().view(np.uint32).astype(np.int64)
@@ -393,7 +396,7 @@ def run_phases(args):
            # domain 0's refinement loop: core-clock cycles per iteration by
            # section (median over the plans that refined it)
            "refine_cycles_per_iteration": (
-               {name: round(float(v), 1) for name, v in zip(REFINE_SECTIONS + ["iterations"],
+               {name: round(float(v), 1) for name, v in zip(REFINE_SECTIONS[len(refine[0]) - 1] + ["iterations"],
                                                              np.median(np.array(refine, dtype=np.float64), axis=0))}
                if refine else None),
            "plan_shape": planners[0].shape.as_dict()}

@@ -657,8 +657,8 @@ __device__ inline void load_ids(const int32_t *ids, int64_t base, int64_t end, b
 
 // One contiguous chunk per block, in tiles of 64 K ids per wave, counted into
 // one LDS row, one atomic per id, the next tile's loads in flight meanwhile.
-// Bound: HBM from some 16 M ids on (2^26 ids, E = 128: 53 us, 5.1 TB/s), the
-// launch below.  A row per wave, summed at the end, costs more than the atomics
+// Bound: HBM from some 16 M ids on (2^26 ids, E = 128: 43 us on inputs that come
+// round alone, 53 on others, 6.2 and 5.1 TB/s), the launch below.  A row per wave, summed at the end, costs more than the atomics
 // that meet in one (2^24 ids, E = 128: 19.2 us, 17.0; 2^17 ids, E = 1024: 4.2,
 // 3.2).  Plain loads keep the ids in the caches for the reroute, whose own are
 // non-temporal (plans of 2^24 ids, inputs that alternate: 53 us, 61 with
@@ -3057,8 +3057,8 @@ __device__ inline void scan_wave_columns(int *wc, int ws, int n, int nw, int *ba
 // start in entry j and run past its end; tx[e] is then the index of e's next
 // occurrence.
 //
-// Bound: HBM (4 B read and 4 B written per id): 101 us for 2^26 ids, E = 128,
-// inputs that alternate, 5.3 TB/s.  Ranking every id (a ballot per id bit) in
+// Bound: HBM (4 B read and 4 B written per id): 101 to 122 us for 2^26 ids, E =
+// 128, by the inputs, 5.3 to 4.4 TB/s.  Ranking every id (a ballot per id bit) in
 // 256-thread blocks, 4096 of them, took 147 us, and the solver summed 4096 rows
 // of counts (42 us, now 512 rows, 10): plan 278 -> 151 us.
 //

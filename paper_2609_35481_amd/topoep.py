@@ -276,7 +276,8 @@ class Planner:
     def plan(self, global_load, local_topk, stream=None, launch=None):
         """Enqueue topoep_plan_ex; returns (replica_slots, token_dest, send_counts, status).
         ``launch`` overrides the planner's launch for this call; it must keep
-        the same shape (only spin_limit and iter_limit may differ)."""
+        the same shape (plan_shape describes both alike: spin_limit and
+        iter_limit may differ, and what the default chooses may be named)."""
         if launch is not None and plan_shape(self.topo, self.T, self.k, self.N, launch).as_dict() != \
                 self.shape.as_dict():
             raise ValueError("a per-call launch must keep the planner's shape")

@@ -1,8 +1,8 @@
 """Benchmark of the TopoEP planner on one MI355X.
 
 A step plans every MoE layer of one microbatch: for each layer the plan's
-kernels (one launch when the single-workgroup solver fits, else histogram,
-solver and reroute) run on one stream, all layers captured in one HIP graph
+kernels (one launch when the single-workgroup solver fits or a per-domain plan
+is small, else histogram, solver and reroute) run on one stream, all layers captured in one HIP graph
 (the layers are planned one after another, as they would be in a forward
 pass).  Inputs (the synthetic routing matrix and this rank's top-k ids of
 every layer) are resident in HBM before the timed region.  A workload of
